@@ -5,17 +5,24 @@
 // whose dim is a multiple of 64; k_gate_gemm in dynamics.hip covers the rest.
 //
 // Each workgroup owns a 256 x 256 tile (audio rows x visual columns); its
-// eight waves (two per SIMD, so one wave's loads, waits and LDS reads hide
-// under the other's MFMAs) own 128 x 64 blocks as 4 x 2 blocks of
-// v_mfma_f32_32x32x16_bf16, so a wave reads 6 fragments from LDS per 8
+// eight waves (two per SIMD) own 128 x 64 blocks as 8 x 4 blocks of
+// v_mfma_f32_16x16x32_bf16, so a wave reads 12 fragments from LDS per 32
 // MFMAs.  K streams through two 64-element LDS stages (2 x 64 KiB), filled
-// by 16-byte direct-to-LDS loads while the other stage is consumed; the
-// 128-byte rows are stored with their 16-byte chunks XOR-swizzled by the
-// row index, so the fragment reads of consecutive rows hit distinct banks
-// without padding.  Every output element sees the same sequence of MFMAs
-// (K in order, 16 at a time) as in k_gate_gemm, so the results are the same
-// bits.  The epilogue scales by the inverse audio norms and folds the
-// column maxima into order-preserving keys with atomicMax.
+// by 16-byte direct-to-LDS loads; the 128-byte rows are stored with their
+// 16-byte chunks XOR-swizzled by the row index, so the fragment reads of
+// consecutive rows hit distinct banks without padding.  Every output
+// element sums K in order, 32 elements per MFMA, whatever its tile.  The
+// epilogue scales by the inverse audio norms and folds the column maxima
+// into order-preserving keys with atomicMax.
+//
+// What bounds it is power: at the long clips' sizes the clock falls to
+// 1.5-1.7 GHz, and the rate follows the energy of a product rather than its
+// schedule.  In registers alone the 16x16x32 form sustains 2.07 PFLOP/s and
+// the 32x32x16 form 1.82 (with every fragment read from LDS 1.86 and 1.68),
+// because it moves half as many accumulator bytes per product.  A 290 s clip
+// (7250 x 83520 x 3584) takes 3.33 ms (1.30 PFLOP/s) against 3.62 with
+// 32x32x16, a 60 s clip 158 us against 176.  Four waves of 128 x 128 (a third
+// fewer LDS reads) took 4.06 ms: one wave per SIMD leaves its waits bare.
 //
 // Workgroups are dealt to the eight XCDs round-robin by index, so the host
 // lists the tiles so that each XCD gets whole column blocks of one band of
@@ -24,6 +31,7 @@
 // blocks of visual rows.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.hpp"
 #include "dynamics_plan.hpp"
@@ -32,23 +40,24 @@ namespace apack {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __attribute__((address_space(1))) void* glb_ptr_t;
 
 constexpr int kTile = 256;                     // rows and columns per workgroup
 constexpr int kK = kGemm256K;                  // K elements per LDS stage
-constexpr int kStages = 2;                     // stages in flight (loads kStages-1 ahead)
 constexpr int kRowB = kK * 2;                  // bytes of one row per stage
 constexpr int kChunks = kRowB / 16;            // 16-byte chunks per row
 constexpr int kOpB = kTile * kRowB;            // one operand's stage
 constexpr int kStageB = 2 * kOpB;
 constexpr int kWaves = 8;
 constexpr int kWN = 4;                         // waves along the visual columns
-constexpr int kBI = kTile / (kWaves / kWN) / 32; // 32-row blocks per wave
-constexpr int kBJ = kTile / kWN / 32;            // 32-column blocks per wave
+constexpr int kBI = kTile / (kWaves / kWN) / 16;  // 16-row blocks per wave
+constexpr int kBJ = kTile / kWN / 16;             // 16-column blocks per wave
+constexpr int kReads = kBI + kBJ;                 // fragments of one 32-element K slice
+constexpr int kMfmas = kBI * kBJ;                 // MFMAs of one slice
 constexpr int kLoadsPerWave = kOpB / 1024 / kWaves;  // 1 KiB loads per wave per operand
-static_assert(kBI * kBJ == 8 && kBI + kBJ == 6, "the K-slice schedule interleaves 6 fragment reads with 8 MFMAs");
+static_assert(kK == 64 && kMfmas >= 2 * kReads && kMfmas >= 3 * 2 * kLoadsPerWave, "slots of the K-slice schedule");
 constexpr int kXcds = 8;
 
 // Chunk c of row r sits at chunk c ^ swz(r).  A 16-byte LDS read is served
@@ -79,27 +88,37 @@ __device__ __forceinline__ void operand_offsets(int64_t r0, int64_t n_rows, int 
   }
 }
 
-__device__ __forceinline__ void issue_operand(char* lds, const char* base, const uint32_t (&off)[kLoadsPerWave],
-                                              int wave) {
-#pragma unroll
-  for (int i = 0; i < kLoadsPerWave; ++i) {
-    const int j = wave * kLoadsPerWave + i;
-    __builtin_amdgcn_global_load_lds((glb_ptr_t)(base + off[i]), (lds_ptr_t)(lds + j * 1024), 16, 0, 0);
-  }
+// Load l of a wave's share of a stage (l < kLoadsPerWave: audio, else visual).
+__device__ __forceinline__ void issue_load(char* stage, const char* base_a, const char* base_b,
+                                           const uint32_t (&off_a)[kLoadsPerWave],
+                                           const uint32_t (&off_b)[kLoadsPerWave], int wave, int l) {
+  const int i = l % kLoadsPerWave, j = wave * kLoadsPerWave + i;
+  if (l < kLoadsPerWave)
+    __builtin_amdgcn_global_load_lds((glb_ptr_t)(base_a + off_a[i]), (lds_ptr_t)(stage + j * 1024), 16, 0, 0);
+  else
+    __builtin_amdgcn_global_load_lds((glb_ptr_t)(base_b + off_b[i]), (lds_ptr_t)(stage + kOpB + j * 1024), 16, 0, 0);
 }
 
-// MFMA operand of rows row .. row+31 (row a multiple of 32 plus lane % 32)
-// and K elements [16 ks, 16 ks + 16): lane l holds 8 elements at
-// 16 ks + 8 (l / 32).
+// p as a scalar (it is the same in every lane), so that the loads that add a
+// per-lane offset to it take the scalar-base form.
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+}
+
+// MFMA operand of rows row .. row+15 (row a multiple of 16 plus lane % 16)
+// and K elements [32 ks, 32 ks + 32): lane l holds 8 elements at
+// 32 ks + 8 (l / 16).
 __device__ __forceinline__ bf16x8 lds_frag(const char* lds, int row, int ks, int lane) {
-  const int c = (ks * 2 + (lane >> 5)) ^ swz(row);
+  const int c = (ks * 4 + (lane >> 4)) ^ swz(row);
   return *reinterpret_cast<const bf16x8*>(lds + row * kRowB + c * 16);
 }
 
 __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gate_gemm256(
     const ClipDev* __restrict__ clips, const GemmTileDev* __restrict__ tiles, int dim, const uint16_t* __restrict__ xv,
     const uint16_t* __restrict__ xa, const double* __restrict__ na, uint32_t* __restrict__ maxkey) {
-  __shared__ __attribute__((aligned(16))) char lds[kStages * kStageB];
+  __shared__ __attribute__((aligned(16))) char lds[2 * kStageB];
   const GemmTileDev tl = tiles[blockIdx.x];
   if (tl.clip < 0) return;  // padding of an XCD's share
   const ClipDev c = clips[tl.clip];
@@ -110,11 +129,11 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / kWN, wn = wave % kWN;
 
-  f32x16 acc[kBI][kBJ];
+  f32x4 acc[kBI][kBJ];
 #pragma unroll
   for (int i = 0; i < kBI; ++i)
 #pragma unroll
-    for (int j = 0; j < kBJ; ++j) acc[i][j] = f32x16{};
+    for (int j = 0; j < kBJ; ++j) acc[i][j] = f32x4{};
 
   const int n_k = dim / kK;
   uint32_t off_a[kLoadsPerWave], off_b[kLoadsPerWave];
@@ -123,74 +142,81 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   const char* base_a = reinterpret_cast<const char*>(A + tl.m0 * dim);
   const char* base_b = reinterpret_cast<const char*>(B + tl.n0 * dim);
   auto issue = [&](int k_stage) {
-    char* st = lds + (k_stage % kStages) * kStageB;
-    issue_operand(st, base_a + (size_t)k_stage * kK * 2, off_a, wave);
-    issue_operand(st + kOpB, base_b + (size_t)k_stage * kK * 2, off_b, wave);
+#pragma unroll
+    for (int l = 0; l < 2 * kLoadsPerWave; ++l)
+      issue_load(lds + (k_stage & 1) * kStageB, base_a + (size_t)k_stage * kRowB, base_b + (size_t)k_stage * kRowB, off_a,
+                 off_b, wave, l);
   };
-  // Loads run kStages - 1 stages ahead of the MFMAs.
-  for (int p = 0; p < kStages - 1 && p < n_k; ++p) issue(p);
-  for (int it = 0; it < n_k; ++it) {
-    const int buf = it % kStages;
-    // Stage it has landed: each wave waits until at most the loads of the
-    // later stages it issued are outstanding, then the barrier makes every
-    // wave's share visible and guarantees the stage about to be refilled
-    // (read at it - 1) is no longer read.
-    const int ahead = std::min(kStages - 2, n_k - 1 - it);   // stages issued after this one
-    if (ahead >= 2)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * 2 * kLoadsPerWave) : "memory");
-    else if (ahead == 1)
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoadsPerWave) : "memory");
+  // Fragments of the slice in hand and of the next one; read r of a slice in
+  // the order its MFMAs first need them: fa[0], fb[0 ..], fa[1 ..].
+  bf16x8 fa[2][kBI], fb[2][kBJ];
+  const int row_a = wm * kBI * 16 + (lane & 15), row_b = wn * kBJ * 16 + (lane & 15);
+  auto read = [&](const char* stage, int ks, int r) {
+    if (r >= 1 && r <= kBJ)
+      fb[ks][r - 1] = lds_frag(stage + kOpB, row_b + 16 * (r - 1), ks, lane);
     else
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    const char* la = lds + buf * kStageB;
-    const char* lb = la + kOpB;
-    // Fragments of K slice ks + 1 are read while slice ks's MFMAs run.
-    bf16x8 fa[2][kBI], fb[2][kBJ];
-    auto read = [&](int ks, int h) {
-#pragma unroll
-      for (int i = 0; i < kBI; ++i) fa[h][i] = lds_frag(la, wm * kBI * 32 + i * 32 + (lane & 31), ks, lane);
-#pragma unroll
-      for (int j = 0; j < kBJ; ++j) fb[h][j] = lds_frag(lb, wn * kBJ * 32 + j * 32 + (lane & 31), ks, lane);
-    };
-    // The first slice's reads go out before the next stage's loads are
-    // issued, so their latency runs under the load issue rather than ahead
-    // of the first MFMA.
-    read(0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    if (it + kStages - 1 < n_k) issue(it + kStages - 1);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int ks = 0; ks < kK / 16; ++ks) {
-      const int h = ks & 1;
-      // Slices run at raised wave priority, so a wave in its MFMAs issues
-      // ahead of the other wave on the SIMD while that one waits at the
-      // stage barrier or issues loads.
-      __builtin_amdgcn_s_setprio(1);
-      if (ks + 1 < kK / 16) read(ks + 1, h ^ 1);
-#pragma unroll
-      for (int i = 0; i < kBI; ++i)
-#pragma unroll
-        for (int j = 0; j < kBJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[h][i], fb[h][j], acc[i][j], 0, 0, 0);
-      // Slice ks + 1's six fragment reads go one after each of slice ks's
-      // first six MFMAs (the scheduler would otherwise sink each read to its
-      // first use); nothing crosses into the next slice.
-#pragma unroll
-      for (int g = 0; g < 6; ++g) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      __builtin_amdgcn_s_setprio(0);
-    }
+      fa[ks][r == 0 ? 0 : r - kBJ] = lds_frag(stage, row_a + 16 * (r == 0 ? 0 : r - kBJ), ks, lane);
+  };
+  issue(0);
+  if (n_k > 1) {
+    issue(1);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoadsPerWave) : "memory");
+  } else {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int r = 0; r < kReads; ++r) read(lds, 0, r);
+  __builtin_amdgcn_sched_barrier(0);
+  // One stage, its two slices' MFMAs back to back.  Slice 0's run over the
+  // reads of slice 1; then every wave waits for its loads of stage it + 1
+  // (issued one stage ago) and its last reads of stage it, so that past the
+  // barrier stage it + 1 is whole and this stage's buffer is free; slice 1's
+  // MFMAs run over the first reads of stage it + 1 and the loads of stage
+  // it + 2.  The scheduling barriers hold one fragment read behind every
+  // second MFMA and one load behind every third: loads issued in a burst
+  // stop the MFMAs behind them (spaced every MFMA 169 us on the 60 s clip,
+  // second 162, third 158, fourth 158; every second one is 1% faster on the
+  // 290 s clip, every fourth 4% slower).
+  auto stage = [&](int it, auto load_tag, auto next_tag) {
+    constexpr bool kLoad = decltype(load_tag)::value, kNext = decltype(next_tag)::value;
+    char* cur = lds + (it & 1) * kStageB;
+    const char* next = lds + ((it + 1) & 1) * kStageB;
+    const char* next_a = uniform_ptr(base_a + (size_t)(it + 2) * kRowB);
+    const char* next_b = uniform_ptr(base_b + (size_t)(it + 2) * kRowB);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      if (ks == 1 && kNext) {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int g = 0; g < kMfmas; ++g) {
+        const int i = g / kBJ, j = g % kBJ;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0);
+        if (g % 2 == 0 && g / 2 < kReads && (ks == 0 || kNext)) {
+          read(ks == 0 ? cur : next, ks ^ 1, g / 2);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (ks == 1 && kLoad && g % 3 == 2 && g / 3 < 2 * kLoadsPerWave) {
+          issue_load(cur, next_a, next_b, off_a, off_b, wave, g / 3);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  int it = 0;
+  for (; it + 2 < n_k; ++it) stage(it, std::true_type{}, std::true_type{});
+  if (it + 1 < n_k) stage(it++, std::false_type{}, std::true_type{});
+  stage(it, std::false_type{}, std::false_type{});
 
   // Epilogue.  Inverse audio norms of the tile's rows in LDS (-inf past the
   // clip's audio, so those rows never win); acc[i][j][e] of lane l is audio
-  // row 32 (kBI wm + i) + 8(e/4) + 4(l/32) + e%4, visual column
-  // 32 (kBJ wn + j) + l%32.
+  // row 16 (kBI wm + i) + 4(l/16) + e, visual column 16 (kBJ wn + j) + l%16.
   __syncthreads();
   float* inv = reinterpret_cast<float*>(lds);
   for (int r = tid; r < kTile; r += kWaves * 64) {
@@ -209,13 +235,14 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
     for (int i = 0; i < kBI; ++i)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float s = inv[wm * kBI * 32 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)];
+      for (int e = 0; e < 4; ++e) {
+        const float s = inv[wm * kBI * 16 + i * 16 + 4 * (lane >> 4) + e];
         m = fmaxf(m, s == -INFINITY ? -INFINITY : acc[i][j][e] * s);
       }
+    m = fmaxf(m, __shfl_xor(m, 16));
     m = fmaxf(m, __shfl_xor(m, 32));
-    const int64_t col = tl.n0 + wn * kBJ * 32 + j * 32 + (lane & 31);
-    if (lane < 32 && col < n_v && m > -INFINITY) atomicMax(&maxkey[c.vis_off + col], order_key(m));
+    const int64_t col = tl.n0 + wn * kBJ * 16 + j * 16 + (lane & 15);
+    if (lane < 16 && col < n_v && m > -INFINITY) atomicMax(&maxkey[c.vis_off + col], order_key(m));
   }
 }
 
