@@ -185,6 +185,10 @@ struct Raw8<bf16_t> {
       o[2 * i + 1] = valid ? (double)__uint_as_float(w[i] & 0xFFFF0000u) : 0.0;
     }
   }
+  __device__ __forceinline__ double at(int e) const {
+    const uint32_t w = e < 2 ? u.x : e < 4 ? u.y : e < 6 ? u.z : u.w;
+    return (double)__uint_as_float(e & 1 ? w & 0xFFFF0000u : w << 16);
+  }
 };
 template <>
 struct Raw8<float> {
@@ -198,6 +202,9 @@ struct Raw8<float> {
     const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = valid ? (double)v[e] : 0.0;
+  }
+  __device__ __forceinline__ double at(int e) const {
+    return (double)(e == 0 ? a.x : e == 1 ? a.y : e == 2 ? a.z : e == 3 ? a.w : e == 4 ? b.x : e == 5 ? b.y : e == 6 ? b.z : b.w);
   }
 };
 
@@ -973,45 +980,164 @@ __global__ __launch_bounds__(kPlanBlk) void k_plan(ClipDev* __restrict__ clips, 
 }
 
 // ---------------------------------------------------------------------------
-// Gram of an anchor frame's P tokens in fp64 on the matrix cores
-// (v_mfma_f64_16x16x4f64).  One workgroup per 16 x 16 tile of the upper
-// triangle of an anchor frame, looping over the batch's (anchor, tile)
-// items; its kGramSplit waves take contiguous slices of the embedding and
-// add their partial tiles in wave order through LDS.  Each tile is written
-// twice, (i, j) and (j, i), so S is exactly symmetric.
+// fp64 Gram tiles on the matrix cores (v_mfma_f64_16x16x4f64), for the
+// anchor Grams and the spatial CKA.  A wave takes a 2 x 2 block of 16 x 16
+// tiles (three tiles of a block on the diagonal) over a slice of the
+// embedding, so each row it loads and widens feeds two MFMAs: widening one
+// element to fp64 costs about as much as the half MFMA it feeds, and with
+// one tile per wave the vector ALU, not the matrix core, set the rate
+// (anchor Grams of a ragged batch 808 -> 190 us, 20 -> 86 TFLOP/s counting
+// both triangles; spatial Gram of a 60 s clip 394 -> 110 us).
 // MFMA operands: lane l supplies A[l % 16][k = l / 16] and B[k = l / 16][l % 16];
 // accumulator element e of lane l is D[4e + l / 16][l % 16].  Each lane
 // loads 8 consecutive elements of its row and feeds them to 8 MFMAs, lane
 // group g = l / 16 covering elements [k0 + 8g, k0 + 8g + 8) of a 32-element
-// step; A and B use the same assignment, so every product enters once.
+// step; A and B use the same assignment, so every product enters once, and
+// every tile sums its products in the same order.
 // ---------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kGramTile = 16;
-constexpr int kGramWaves = 4;  // tiles per workgroup of the spatial Gram
-constexpr int kGramSplit = 8;  // K slices (waves) per workgroup of the anchor Gram
+constexpr int kGramSplit = 8;     // K slices (waves) per workgroup of the anchor Gram
+constexpr int kSpatialSplit = 4;  // and of the spatial Gram
+constexpr int64_t kSpatialBlocks = 1 << 20;  // workgroups of the spatial Gram at most (a multiple of 8)
 constexpr int kGramBlocks = 512;  // workgroups of the anchor Gram at most: two per CU
-constexpr int kGramAhead = 4;  // K steps in flight per wave
 
-// Eight consecutive input elements held as loaded, widened to fp64 on use.
-template <class T>
-__global__ __launch_bounds__(kGramSplit * 64) void k_gram(const ClipDev* __restrict__ clips, int n_clips,
-                                                          const int32_t* __restrict__ anchors,
-                                                          const FramePlanDev* __restrict__ plan, int dim,
-                                                          const T* __restrict__ xv, double* __restrict__ gram) {
-  __shared__ double red[kGramSplit - 1][4 * 64];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
+// Tile block (bi, bj), bj >= bi, number t of the row-major upper triangle of
+// an nb x nb grid of blocks.
+__device__ __forceinline__ void upper_block(int t, int nb, int& bi, int& bj) {
+  bi = 0;
+  while (t >= nb - bi) {
+    t -= nb - bi;
+    ++bi;
+  }
+  bj = bi + t;
+}
+
+// acc[u][v] += A_u B_v^T over the 32-element steps [s0, s1): row[u] and
+// row[N + v] are this lane's rows of the block's N row and N column tiles.
+// DIAG: the column tiles are the row tiles (row[N ..] is unused) and the
+// tile below the diagonal is left out.  MEANS: 0 leaves the rows as they
+// are, 1 subtracts mean[0] from each, 2 mean[second[r]] from row r (second
+// is the same for the whole wave).  The next step's loads are issued before
+// this step's MFMAs (a step past the end re-reads the row's last elements
+// and is not used), and each element is widened under the MFMAs of the one
+// before it.
+template <class T, int N, bool DIAG, int MEANS>
+__device__ __forceinline__ void gram_block(const T* const (&row)[2 * N], const double* const (&mean)[2],
+                                           const bool (&second)[2 * N], int dim, int s0, int s1, int g,
+                                           f64x4 (&acc)[N][N]) {
+  constexpr int NR = DIAG ? N : 2 * N;
+  Raw8<T> raw[2][NR];
+  double mu[2][MEANS > 0 ? MEANS : 1][8];
+  auto load = [&](int s, int h) {
+    const int kk = 32 * s + 8 * g;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) raw[h][r].load(row[r], kk, dim);
+#pragma unroll
+    for (int r = 0; r < MEANS; ++r) {
+      const double2* m = reinterpret_cast<const double2*>(mean[r] + min(kk, dim - 8));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double2 x = m[e];
+        mu[h][r][2 * e] = x.x;
+        mu[h][r][2 * e + 1] = x.y;
+      }
+    }
+  };
+  auto step = [&](int s, int h, auto whole_tag) {
+    constexpr bool kWhole = decltype(whole_tag)::value;   // every lane's elements lie below dim
+    const bool valid = kWhole || 32 * s + 8 * g < dim;
+    double w[2][NR];
+    auto widen = [&](int e) {
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        double x = raw[h][r].at(e);
+        if constexpr (MEANS == 1) x -= mu[h][0][e];
+        if constexpr (MEANS == 2) x -= second[r] ? mu[h][1][e] : mu[h][0][e];
+        w[e & 1][r] = valid ? x : 0.0;
+      }
+    };
+    widen(0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+#pragma unroll
+      for (int u = 0; u < N; ++u)
+#pragma unroll
+        for (int v = DIAG ? u : 0; v < N; ++v)
+          acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(w[e & 1][u], w[e & 1][DIAG ? v : N + v], acc[u][v], 0, 0, 0);
+      if (e + 1 < 8) widen(e + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (s0 >= s1) return;
+  const int whole = min(s1, dim / 32);   // steps of 32 whole elements
+  load(s0, 0);
+  int s = s0;
+  for (; s + 1 < whole; s += 2) {
+    load(s + 1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    step(s, 0, std::true_type{});
+    load(s + 2, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    step(s + 1, 1, std::true_type{});
+  }
+  if (s < whole) {
+    load(s + 1, 1);
+    step(s, 0, std::true_type{});
+    if (s + 1 < s1) step(s + 1, 1, std::false_type{});
+  } else if (s < s1) {
+    step(s, 0, std::false_type{});
+  }
+}
+
+// Adds the waves' partial tiles in wave order through LDS; wave 0 holds the
+// sums afterwards.  Every thread calls it.
+template <int NW, int N>
+__device__ __forceinline__ void gram_reduce(f64x4 (&acc)[N][N], double (&red)[NW - 1][16 * 64], int wave, int lane) {
+  if (wave > 0) {
+#pragma unroll
+    for (int t = 0; t < N * N; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[wave - 1][(4 * t + e) * 64 + lane] = acc[t / N][t % N][e];
+  }
+  __syncthreads();
+  if (wave == 0) {
+#pragma unroll
+    for (int q = 0; q < NW - 1; ++q)
+#pragma unroll
+      for (int t = 0; t < N * N; ++t)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[t / N][t % N][e] += red[q][(4 * t + e) * 64 + lane];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Gram of an anchor frame's P tokens.  One workgroup per block of N x N
+// tiles of the upper triangle of an anchor frame, looping over the batch's
+// (anchor, block) items; its kGramSplit waves take contiguous slices of the
+// embedding and add their partial tiles in wave order.  Each tile is written
+// twice, (i, j) and (j, i), so S is exactly symmetric.  The tiles hold the
+// same bits for either N.
+// ---------------------------------------------------------------------------
+template <class T, int N>
+__device__ __forceinline__ void anchor_grams(const ClipDev* __restrict__ clips, int n_clips,
+                                             const int32_t* __restrict__ anchors,
+                                             const FramePlanDev* __restrict__ plan, int dim, const T* __restrict__ xv,
+                                             double* __restrict__ gram, double (&red)[kGramSplit - 1][16 * 64],
+                                             int blk, int n_blk) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4,
+            r16 = lane & 15;
   // This wave's K slice, in 32-element steps.
   const int nsteps = (dim + 31) / 32;
   const int per = (nsteps + kGramSplit - 1) / kGramSplit;
   const int s_begin = min(nsteps, wave * per), s_end = min(nsteps, s_begin + per);
-  const int lim = min(dim, 32 * s_end);
   // Anchors go to XCDs round-robin (workgroup b runs on XCD b % 8), so an
   // anchor's rows are fetched into one L2; the XCD's slots share its
-  // anchors' tiles in turn.  Every workgroup walks the same anchor sequence.
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, nslot = gridDim.x >> 3;
+  // anchors' blocks in turn.  Every workgroup walks the same anchor sequence.
+  const int xcd = blk & 7, slot = blk >> 3, nslot = n_blk >> 3;
   int c = 0;
   int64_t seg_before = 0;  // anchors of clips [0, c)
-  int64_t jbase = 0;       // tiles of this XCD's earlier anchors
+  int64_t jbase = 0;       // blocks of this XCD's earlier anchors
   for (int64_t an = xcd;; an += 8) {
     while (c < n_clips) {
       const int64_t ns = clips[c].n_frames > 0 ? clips[c].n_seg : 0;
@@ -1021,201 +1147,191 @@ __global__ __launch_bounds__(kGramSplit * 64) void k_gram(const ClipDev* __restr
     }
     if (c >= n_clips) return;
     const ClipDev cc = clips[c];
-    const int P = cc.per_frame, nt = (P + kGramTile - 1) / kGramTile, tiles = nt * (nt + 1) / 2;
+    const int P = cc.per_frame, nb = (P + N * kGramTile - 1) / (N * kGramTile), blocks = nb * (nb + 1) / 2;
     const int f = anchors[cc.frame_off + (an - seg_before)];
     const int64_t j0 = jbase + ((slot - jbase % nslot) % nslot + nslot) % nslot;
-    const int64_t jend = jbase + tiles;
+    const int64_t jend = jbase + blocks;
     jbase = jend;
     if (plan[cc.frame_off + f].budget == 0) continue;  // the same for the whole workgroup
     for (int64_t jj = j0; jj < jend; jj += nslot) {
-      int t = (int)(jj - (jend - tiles)), ti = 0;
-      while (t >= nt - ti) {  // row-major upper triangle: tile (ti, tj), tj >= ti
-        t -= nt - ti;
-        ++ti;
+      int bi, bj;
+      upper_block((int)(jj - (jend - blocks)), nb, bi, bj);
+      const T* x = xv + (cc.vis_off + (int64_t)f * P) * dim;
+      const T* row[2 * N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) {
+        row[u] = x + (int64_t)min((N * bi + u) * kGramTile + r16, P - 1) * dim;
+        row[N + u] = x + (int64_t)min((N * bj + u) * kGramTile + r16, P - 1) * dim;
       }
-      const int tj = ti + t;
-      const int64_t row0 = cc.vis_off + (int64_t)f * P;
-      const int ra = min(ti * kGramTile + r16, P - 1), rb = min(tj * kGramTile + r16, P - 1);
-      const T* xa = xv + (row0 + ra) * dim;
-      const T* xb = xv + (row0 + rb) * dim;
-      // kGramAhead steps loaded ahead of the MFMAs (the next group's loads
-      // are issued before this group's MFMAs); steps past the slice add
-      // zero products.
-      Raw8<T> pa[kGramAhead], pb[kGramAhead];
+      const double* const none[2] = {nullptr, nullptr};
+      const bool first[2 * N] = {};
+      f64x4 acc[N][N];
 #pragma unroll
-      for (int u = 0; u < kGramAhead; ++u) {
-        const int kk = 32 * (s_begin + u) + 8 * g;
-        pa[u].load(xa, kk, dim);
-        pb[u].load(xb, kk, dim);
-      }
-      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-      for (int s0 = s_begin; s0 < s_end; s0 += kGramAhead) {
-        Raw8<T> qa[kGramAhead], qb[kGramAhead];
-#pragma unroll
-        for (int u = 0; u < kGramAhead; ++u) {
-          const int kk = 32 * (s0 + kGramAhead + u) + 8 * g;
-          qa[u].load(xa, kk, dim);
-          qb[u].load(xb, kk, dim);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < kGramAhead; ++u) {
-          const bool valid = 32 * (s0 + u) + 8 * g < lim;
-          double a[8], b[8];
-          pa[u].get(a, valid);
-          pb[u].get(b, valid);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[e], acc, 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < kGramAhead; ++u) {
-          pa[u] = qa[u];
-          pb[u] = qb[u];
-        }
-      }
-      // Partial tiles added in wave order.
-      if (wave > 0) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) red[wave - 1][e * 64 + lane] = acc[e];
-      }
-      __syncthreads();
+      for (int t = 0; t < N * N; ++t) acc[t / N][t % N] = f64x4{0.0, 0.0, 0.0, 0.0};
+      if (bi == bj)
+        gram_block<T, N, true, 0>(row, none, first, dim, s_begin, s_end, g, acc);
+      else
+        gram_block<T, N, false, 0>(row, none, first, dim, s_begin, s_end, g, acc);
+      gram_reduce<kGramSplit, N>(acc, red, wave, lane);
       if (wave == 0) {
-#pragma unroll
-        for (int q = 0; q < kGramSplit - 1; ++q)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[e] += red[q][e * 64 + lane];
         // Raw dot products: k_dafps forms the cosines from them and the
         // diagonal, which went through the same MFMA sequence.
         double* G = gram + cc.gram_off + (int64_t)f * P * P;
-        const int col = tj * kGramTile + r16;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int row = ti * kGramTile + 4 * e + g;
-          if (row >= P || col >= P) continue;
-          G[(int64_t)row * P + col] = acc[e];
-          G[(int64_t)col * P + row] = acc[e];
-        }
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+          for (int v = 0; v < N; ++v) {
+            if (bi == bj && u > v) continue;
+            const int col = (N * bj + v) * kGramTile + r16;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int r = (N * bi + u) * kGramTile + 4 * e + g;
+              if (r >= P || col >= P) continue;
+              G[(int64_t)r * P + col] = acc[u][v][e];
+              G[(int64_t)col * P + r] = acc[u][v][e];
+            }
+          }
       }
       __syncthreads();
     }
   }
+}
+
+// Blocks of 2 x 2 tiles where single tiles would make more than two rounds
+// of the grid; fewer items than that leave compute units idle, so a few
+// anchors go tile by tile (120 against 360 items for the 8 anchors of a
+// 60 s clip: 38 us in blocks).
+template <class T>
+__global__ __launch_bounds__(kGramSplit * 64) void k_gram(const ClipDev* __restrict__ clips, int n_clips,
+                                                          const int32_t* __restrict__ anchors,
+                                                          const FramePlanDev* __restrict__ plan, int dim,
+                                                          const T* __restrict__ xv, double* __restrict__ gram) {
+  __shared__ double red[kGramSplit - 1][16 * 64];
+  int64_t tiles = 0;
+  for (int c = 0; c < n_clips; ++c) {
+    const int nt = (clips[c].per_frame + kGramTile - 1) / kGramTile;
+    tiles += clips[c].n_frames > 0 ? (int64_t)clips[c].n_seg * (nt * (nt + 1) / 2) : 0;
+  }
+  if (tiles <= 2 * (int64_t)gridDim.x)
+    anchor_grams<T, 1>(clips, n_clips, anchors, plan, dim, xv, gram, red, blockIdx.x, gridDim.x);
+  else
+    anchor_grams<T, 2>(clips, n_clips, anchors, plan, dim, xv, gram, red, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------
 // Spatial CKA at w = 1 (alternative alignment scorer): for frame f, the rows
 // R = [A~; V~] stack the audio tokens of its adaptive-pool bin and its P
 // visual tokens, each centred in fp64 by its own mean (a_f and v_f of
-// k_pool).  One wave per 16 x 16 tile of the upper triangle of R R^T (fp64
-// MFMA, operand layout as in k_gram) adds the squared entries of its tile
-// to the audio-audio, audio-visual and visual-visual sums; off-diagonal
-// tiles of the symmetric blocks count twice, and the cross block counts
-// once, in its audio-row orientation.  The per-tile sums go to
-// part[frame][tile][3] and k_spatial_reduce adds them in tile order.
+// k_pool); both parts are padded to whole tiles, so a tile's rows share one
+// mean.  One workgroup per tile block of the upper triangle of R R^T (its
+// waves split the embedding) adds the squared entries to the audio-audio,
+// audio-visual and visual-visual sums; off-diagonal tiles of the symmetric
+// blocks count twice, and the cross block counts once, in its audio-row
+// orientation.  The per-block sums go to part[frame][block][3] and
+// k_spatial_reduce adds them.
 // ---------------------------------------------------------------------------
 template <class T>
-__device__ __forceinline__ void load8_centred(const T* x, const double* mu, double (&o)[8]) {
-  load8(x, o);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] -= mu[e];
-}
-
-template <class T>
-__global__ __launch_bounds__(kGramWaves * 64) void k_spatial_gram(const ClipDev* __restrict__ clips,
-                                                                  const FrameDev* __restrict__ frames, int dim,
-                                                                  const T* __restrict__ xv, const T* __restrict__ xa,
-                                                                  const double* __restrict__ vmean,
-                                                                  const double* __restrict__ amean, int tiles,
-                                                                  double* __restrict__ part) {
-  const FrameDev fr = frames[blockIdx.x];
-  const ClipDev c = clips[fr.clip];
-  const int64_t frame = c.frame_off + fr.f;
-  const int P = c.per_frame;
-  const int64_t lo = ((int64_t)fr.f * c.n_audio) / c.n_frames;
-  const int64_t hi = (((int64_t)fr.f + 1) * c.n_audio + c.n_frames - 1) / c.n_frames;
-  const int na = (int)(hi - lo), m = na + P;
-  const int nt = (m + kGramTile - 1) / kGramTile;
-  const int t0 = blockIdx.y * kGramWaves + (threadIdx.x >> 6);
-  if (t0 >= tiles) return;
-  const int lane = threadIdx.x & 63, g = lane >> 4, r16 = lane & 15;
-  double* out = part + (frame * tiles + t0) * 3;
-  if (t0 >= nt * (nt + 1) / 2) {  // past this frame's triangle: contributes nothing
-    if (lane < 3) out[lane] = 0.0;
-    return;
-  }
-  int t = t0, ti = 0;
-  while (t >= nt - ti) {
-    t -= nt - ti;
-    ++ti;
-  }
-  const int tj = ti + t;
-  // Row r of R: audio row lo + r (centred by a_f) or visual token r - na (by v_f).
-  auto row_ptr = [&](int r, const T*& x, const double*& mu) {
-    r = min(r, m - 1);
-    if (r < na) {
-      x = xa + (c.aud_off + lo + r) * dim;
-      mu = amean + frame * dim;
-    } else {
-      x = xv + (c.vis_off + (int64_t)fr.f * P + (r - na)) * dim;
-      mu = vmean + frame * dim;
+__global__ __launch_bounds__(kSpatialSplit * 64) void k_spatial_gram(
+    const ClipDev* __restrict__ clips, const FrameDev* __restrict__ frames, int64_t n_frames, int dim,
+    const T* __restrict__ xv, const T* __restrict__ xa, const double* __restrict__ vmean,
+    const double* __restrict__ amean, int blocks, double* __restrict__ part) {
+  __shared__ double red[kSpatialSplit - 1][16 * 64];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4,
+            r16 = lane & 15;
+  // Item i: the blocks of one frame are 8 apart, so they run on one XCD
+  // (workgroup b runs on XCD b % 8) and share its rows in that L2.
+  const int64_t items = (n_frames + 7) / 8 * 8 * blocks;
+  for (int64_t i = blockIdx.x; i < items; i += gridDim.x) {
+    const int64_t item = (i >> 3) / blocks * 8 + (i & 7);
+    const int t0 = (int)((i >> 3) % blocks);
+    if (item >= n_frames) continue;
+    const FrameDev fr = frames[item];
+    const ClipDev c = clips[fr.clip];
+    const int64_t frame = c.frame_off + fr.f;
+    const int P = c.per_frame;
+    const int64_t lo = ((int64_t)fr.f * c.n_audio) / c.n_frames;
+    const int64_t hi = (((int64_t)fr.f + 1) * c.n_audio + c.n_frames - 1) / c.n_frames;
+    const int na = (int)(hi - lo), ta = (na + kGramTile - 1) / kGramTile;   // audio tiles come first
+    const int nt = ta + (P + kGramTile - 1) / kGramTile, nb = (nt + 1) / 2;
+    double* out = part + (frame * blocks + t0) * 3;
+    if (t0 >= nb * (nb + 1) / 2) {  // past this frame's triangle: contributes nothing
+      if (tid < 3) out[tid] = 0.0;
+      continue;
     }
-  };
-  const T *pa, *pb;
-  const double *ma, *mb;
-  row_ptr(ti * kGramTile + r16, pa, ma);
-  row_ptr(tj * kGramTile + r16, pb, mb);
-  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < dim; k0 += 32) {
-    const int kk = k0 + 8 * g;
-    double a[8], b[8];
-    if (kk < dim) {
-      load8_centred(pa + kk, ma + kk, a);
-      load8_centred(pb + kk, mb + kk, b);
-    } else {
+    int bi, bj;
+    upper_block(t0, nb, bi, bj);
+    // Tile t's row of this lane, clamped into its part.
+    auto row_of = [&](int t) {
+      t = min(t, nt - 1);
+      return t < ta ? xa + (c.aud_off + lo + min(t * kGramTile + r16, na - 1)) * dim
+                    : xv + (c.vis_off + (int64_t)fr.f * P + min((t - ta) * kGramTile + r16, P - 1)) * dim;
+    };
+    const T* const row[4] = {row_of(2 * bi), row_of(2 * bi + 1), row_of(2 * bj), row_of(2 * bj + 1)};
+    const int nsteps = (dim + 31) / 32, per = (nsteps + kSpatialSplit - 1) / kSpatialSplit;
+    const int s_begin = min(nsteps, wave * per), s_end = min(nsteps, s_begin + per);
+    f64x4 acc[2][2];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) a[e] = b[e] = 0.0;
+    for (int t = 0; t < 4; ++t) acc[t >> 1][t & 1] = f64x4{0.0, 0.0, 0.0, 0.0};
+    // Row tiles come first, so a block whose first row tile is visual has
+    // one mean.
+    const double* const mean[2] = {2 * bi < ta ? amean + frame * dim : vmean + frame * dim, vmean + frame * dim};
+    const bool second[4] = {false, 2 * bi + 1 >= ta, 2 * bj >= ta, 2 * bj + 1 >= ta};
+    const bool one = 2 * bi >= ta;
+    if (bi == bj && one)
+      gram_block<T, 2, true, 1>(row, mean, second, dim, s_begin, s_end, g, acc);
+    else if (bi == bj)
+      gram_block<T, 2, true, 2>(row, mean, second, dim, s_begin, s_end, g, acc);
+    else if (one)
+      gram_block<T, 2, false, 1>(row, mean, second, dim, s_begin, s_end, g, acc);
+    else
+      gram_block<T, 2, false, 2>(row, mean, second, dim, s_begin, s_end, g, acc);
+    gram_reduce<kSpatialSplit, 2>(acc, red, wave, lane);
+    if (wave == 0) {
+      double sum[3] = {0.0, 0.0, 0.0};   // audio-audio, audio-visual, visual-visual
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int w = 0; w < 2; ++w) {
+          const int ti = 2 * bi + u, tj = 2 * bj + w;
+          if (tj < ti || tj >= nt) continue;   // tj >= ti: an audio row tile or two visual ones
+          const int kind = (ti < ta ? 0 : 1) + (tj < ta ? 0 : 1);
+          const int row_end = ti < ta ? na : P, col_end = tj < ta ? na : P;
+          const int row0 = (ti < ta ? ti : ti - ta) * kGramTile, col = (tj < ta ? tj : tj - ta) * kGramTile + r16;
+          const double times = kind != 1 && ti != tj ? 2.0 : 1.0;
+          double s = 0.0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (row0 + 4 * e + g < row_end && col < col_end) s += times * (acc[u][w][e] * acc[u][w][e]);
+#pragma unroll
+          for (int q = 0; q < 3; ++q) sum[q] += kind == q ? s : 0.0;
+        }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const double s = wave_sum(sum[q]);
+        if (lane == 0) out[q] = s;
+      }
     }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[e], acc, 0, 0, 0);
-  }
-  double s_aa = 0.0, s_av = 0.0, s_vv = 0.0;
-  const int col = tj * kGramTile + r16;
-  const double twice = ti == tj ? 1.0 : 2.0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int row = ti * kGramTile + 4 * e + g;
-    if (row >= m || col >= m) continue;
-    const double x2 = acc[e] * acc[e];
-    if (row < na && col < na)
-      s_aa += twice * x2;
-    else if (row >= na && col >= na)
-      s_vv += twice * x2;
-    else if (row < na)  // audio row, visual column; its transpose is not counted
-      s_av += x2;
-  }
-  s_aa = wave_sum(s_aa);
-  s_av = wave_sum(s_av);
-  s_vv = wave_sum(s_vv);
-  if (lane == 0) {
-    out[0] = s_aa;
-    out[1] = s_av;
-    out[2] = s_vv;
+    __syncthreads();
   }
 }
 
-// c_f = S_av / (sqrt(S_aa) sqrt(S_vv)) from the tile sums, in tile order;
-// 0 when a side is degenerate: its centred Gram norm sqrt(S) at most
-// kCkaDegenerate of its raw trace (the sum of its tokens' squared norms).
+// c_f = S_av / (sqrt(S_aa) sqrt(S_vv)) from the block sums; 0 when a side is
+// degenerate: its centred Gram norm sqrt(S) at most kCkaDegenerate of its
+// raw trace (the sum of its tokens' squared norms).  One wave per frame, its
+// lanes over the blocks and the tokens, each sum in a fixed order (one
+// thread per frame had walked them one load at a time, 34 us on a 60 s clip;
+// now 4).
 __global__ __launch_bounds__(kBlk) void k_spatial_reduce(const ClipDev* __restrict__ clips,
                                                          const FrameDev* __restrict__ frames, int64_t n_frames,
-                                                         int tiles, const double* __restrict__ part,
+                                                         int blocks, const double* __restrict__ part,
                                                          const double* __restrict__ nv, const double* __restrict__ na,
                                                          double* __restrict__ cka) {
-  const int64_t f = (int64_t)blockIdx.x * kBlk + threadIdx.x;
+  const int64_t f = (int64_t)blockIdx.x * (kBlk / 64) + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   if (f >= n_frames) return;
   double s_aa = 0.0, s_av = 0.0, s_vv = 0.0;
-  for (int t = 0; t < tiles; ++t) {
-    const double* q = part + (f * tiles + t) * 3;
+  for (int t = lane; t < blocks; t += 64) {
+    const double* q = part + (f * blocks + t) * 3;
     s_aa += q[0];
     s_av += q[1];
     s_vv += q[2];
@@ -1225,11 +1341,16 @@ __global__ __launch_bounds__(kBlk) void k_spatial_reduce(const ClipDev* __restri
   const int64_t lo = ((int64_t)fr.f * c.n_audio) / c.n_frames;
   const int64_t hi = (((int64_t)fr.f + 1) * c.n_audio + c.n_frames - 1) / c.n_frames;
   double tr_a = 0.0, tr_v = 0.0;
-  for (int64_t r = lo; r < hi; ++r) tr_a += na[c.aud_off + r];
+  for (int64_t r = lo + lane; r < hi; r += 64) tr_a += na[c.aud_off + r];
   const int64_t row0 = c.vis_off + (int64_t)fr.f * c.per_frame;
-  for (int p = 0; p < c.per_frame; ++p) tr_v += nv[row0 + p];
+  for (int p = lane; p < c.per_frame; p += 64) tr_v += nv[row0 + p];
+  s_aa = wave_sum(s_aa);
+  s_av = wave_sum(s_av);
+  s_vv = wave_sum(s_vv);
+  tr_a = wave_sum(tr_a);
+  tr_v = wave_sum(tr_v);
   const double sa = sqrt(s_aa), sv = sqrt(s_vv);
-  cka[f] = (sa <= kCkaDegenerate * tr_a || sv <= kCkaDegenerate * tr_v) ? 0.0 : s_av / (sa * sv);
+  if (lane == 0) cka[f] = (sa <= kCkaDegenerate * tr_a || sv <= kCkaDegenerate * tr_v) ? 0.0 : s_av / (sa * sv);
 }
 
 // v_max_f64 / v_min_f64 as single instructions.  In IEEE mode the
@@ -1751,12 +1872,13 @@ apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& 
     if ((st = launch_status("k_norms")) != APACK_OK) return st;
   }
   if (prm.alignment == APACK_ALIGN_SPATIAL_CKA && nf > 0) {
-    const unsigned gy = (unsigned)((pl.spatial_tiles + kGramWaves - 1) / kGramWaves);
-    hipLaunchKernelGGL(k_spatial_gram<T>, dim3(nf, gy), dim3(kGramWaves * 64), 0, s, dp.clips, dp.frames, dim, xv,
-                       xa, dp.v, dp.a, pl.spatial_tiles, dp.spatial);
+    const int64_t items = ((int64_t)nf + 7) / 8 * 8 * pl.spatial_blocks;
+    hipLaunchKernelGGL(k_spatial_gram<T>, dim3((unsigned)std::min<int64_t>(items, kSpatialBlocks)),
+                       dim3(kSpatialSplit * 64), 0, s, dp.clips, dp.frames, (int64_t)nf, dim, xv, xa, dp.v, dp.a,
+                       pl.spatial_blocks, dp.spatial);
     if ((st = launch_status("k_spatial_gram")) != APACK_OK) return st;
-    hipLaunchKernelGGL(k_spatial_reduce, dim3((unsigned)((nf + kBlk - 1) / kBlk)), dim3(kBlk), 0, s, dp.clips,
-                       dp.frames, (int64_t)nf, pl.spatial_tiles, dp.spatial, dp.nv, dp.na, dp.cka);
+    hipLaunchKernelGGL(k_spatial_reduce, dim3((unsigned)((nf + kBlk / 64 - 1) / (kBlk / 64))), dim3(kBlk), 0, s, dp.clips,
+                       dp.frames, (int64_t)nf, pl.spatial_blocks, dp.spatial, dp.nv, dp.na, dp.cka);
     if ((st = launch_status("k_spatial_reduce")) != APACK_OK) return st;
   }
   auto cka = prm.window <= 2 ? k_cka<2> : prm.window <= 4 ? k_cka<4> : prm.window <= 8 ? k_cka<8> : k_cka<kMaxWindow>;

@@ -63,24 +63,26 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
     tokens += nv;
     kept += c.budget;
     gram += nv * a.tokens_per_frame;
-    const int64_t nt = (a.tokens_per_frame + 15) / 16;
-    pl.gram_items += (int64_t)a.n_frames * (nt * (nt + 1) / 2);
+    const int64_t nb = (a.tokens_per_frame + 31) / 32;
+    pl.gram_items += (int64_t)a.n_frames * (nb * (nb + 1) / 2);
     vis_end = std::max(vis_end, a.vis_off + nv);
     aud_end = std::max(aud_end, a.aud_off + a.n_audio);
     pl.max_per_frame = std::max(pl.max_per_frame, a.tokens_per_frame);
     pl.clips.push_back(c);
   }
-  // Spatial CKA: one 16 x 16 tile per upper-triangle block of the stacked
-  // [co-timed audio; visual] rows of a frame, sized for the largest frame.
+  // Spatial CKA: one block of 2 x 2 tiles (16 x 16) per upper-triangle block
+  // of a frame's co-timed audio rows and visual rows, each padded to whole
+  // tiles, sized for the largest frame.
   if (p->alignment == APACK_ALIGN_SPATIAL_CKA) {
-    int64_t m = 0;
+    int64_t nt = 0;
     for (int s = 0; s < n_seq; ++s) {
       const apack_av_seq& a = seqs[s];
       if (a.n_frames == 0) continue;
-      m = std::max<int64_t>(m, (a.n_audio + a.n_frames - 1) / a.n_frames + 1 + a.tokens_per_frame);
+      const int64_t bin = (a.n_audio + a.n_frames - 1) / a.n_frames + 1;
+      nt = std::max<int64_t>(nt, (bin + 15) / 16 + (a.tokens_per_frame + 15) / 16);
     }
-    const int64_t nt = (m + 15) / 16;
-    pl.spatial_tiles = (int32_t)(nt * (nt + 1) / 2);
+    const int64_t nb = (nt + 1) / 2;
+    pl.spatial_blocks = (int32_t)(nb * (nb + 1) / 2);
   }
   pl.total_frames = frames;
   pl.total_tokens = vis_end;
@@ -144,7 +146,7 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   pl.off_sim = c.used;
   c.take<double>(tokens);
   pl.off_spatial = c.used;
-  c.take<double>((size_t)frames * pl.spatial_tiles * 3);
+  c.take<double>((size_t)frames * pl.spatial_blocks * 3);
   pl.off_anchors = c.used;
   c.take<int32_t>(frames);
   pl.off_sqp = c.used;

@@ -58,7 +58,7 @@ struct DynPlan {
   int64_t total_frames = 0, total_tokens = 0, total_audio = 0, total_kept = 0, total_gram = 0;
   int max_per_frame = 1;
   int64_t gemm_tiles = 0;            // gate GEMM workgroups over all clips
-  int32_t spatial_tiles = 0;         // spatial CKA Gram tiles per frame (0 unless selected)
+  int32_t spatial_blocks = 0;        // spatial CKA Gram blocks (2 x 2 tiles) per frame (0 unless selected)
   std::vector<GemmTileDev> gemm;
   std::vector<GemmTileDev> gemm256;  // 256 x 256 tiles (dim a multiple of 64), XCD-ordered
   bool use256 = false;               // set per call: bf16 inputs and gemm256 planned
@@ -67,7 +67,7 @@ struct DynPlan {
   size_t off_v = 0, off_a = 0, off_q = 0, off_band_v = 0, off_band_a = 0, off_vq = 0, off_qq = 0;
   size_t off_cka = 0, off_nv = 0, off_rv = 0, off_na = 0, off_maxkey = 0, off_plan = 0, off_gram = 0, off_scratch = 0;
   size_t off_spatial = 0, off_sim = 0, off_anchors = 0, off_sqp = 0;
-  int64_t gram_items = 0;            // (frame, Gram tile) pairs over all clips: the anchor Gram's items at most
+  int64_t gram_items = 0;            // (frame, Gram block) pairs over all clips: the anchor Gram's items at most
   size_t ws_bytes = 0;
 };
 

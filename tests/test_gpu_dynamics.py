@@ -312,3 +312,21 @@ def test_scorer_is_deterministic():
     for key in ("cka", "score", "budget", "segment", "gate", "kept"):
         assert np.array_equal(a[key].view(np.uint8), b[key].view(np.uint8)), key
     assert a["n_kept"] == b["n_kept"]
+
+
+@pytest.mark.parametrize("dim,per_frame,audio", [
+    (8, 15, 40),      # one partial K step: most K slices of a Gram are empty
+    (40, 16, 97),     # a partial last K step; a whole tile of tokens
+    (264, 17, 200),   # one token past a tile
+    (520, 32, 64),    # a whole 2 x 2 tile block
+    (1032, 33, 400),  # one token past a block; audio bins of two tiles
+])
+@pytest.mark.parametrize("alignment", ["gated_cka", "spatial_cka"])
+def test_gram_blocks_at_their_edges(dim, per_frame, audio, alignment):
+    """Anchor and spatial Grams where the tile blocks, the padding between
+    audio and visual tiles and the K slices have remainders."""
+    case = W.dynamics_small("offset", seed=92, dim=dim, frames=18, per_frame=per_frame, audio=audio)
+    case.params = dict(case.params, alignment=alignment)
+    want = _oracle(case)
+    _certify(want)
+    _compare(case, _run(case), want)
