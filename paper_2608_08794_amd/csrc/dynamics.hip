@@ -10,7 +10,8 @@
 //   k_norms      squared norms of every visual and audio token of the clips
 //                (fp64), from k_pool's per-slice sums, and 1/|x| of the
 //                visual tokens
-//   k_gate_gemm  only where the gate fired: X_A . X_V^T on bf16 MFMA, scaled
+//   k_gate_gemm256, k_gate_gemm_any (gate_gemm.hip)
+//                only where the gate fired: X_A . X_V^T on bf16 MFMA, scaled
 //                by 1/|a_j|, max over audio tokens in-lane, merged across
 //                tiles by atomicMax on order-preserving uint keys
 //   k_plan       one 1024-thread workgroup per clip, arrays in LDS:
@@ -39,8 +40,6 @@ namespace apack {
 namespace {
 
 typedef unsigned short bf16_t;
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kBlk = 256;
 
@@ -532,138 +531,6 @@ __global__ __launch_bounds__(kBlk) void k_norms(int64_t n_vis, int64_t n_aud, in
 }
 
 // ---------------------------------------------------------------------------
-// Gate GEMM: for every visual token i, max_j (x_A[j] . x_V[i]) / |x_A[j]|.
-// C = X_A X_V^T in 128 x 128 tiles (4 waves, 64 x 64 each), K through
-// padded, double-buffered LDS in steps of 64 elements.
-// ---------------------------------------------------------------------------
-template <class T> struct GMma;
-template <> struct GMma<bf16_t> {
-  using frag = bf16x8;
-  static constexpr int kstep = 16, lane_k = 8;
-  static __device__ __forceinline__ f32x16 mma(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-};
-template <> struct GMma<float> {
-  using frag = float;
-  static constexpr int kstep = 2, lane_k = 1;
-  static __device__ __forceinline__ f32x16 mma(frag a, frag b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-};
-
-constexpr int kGB = 128;   // tile rows and columns
-constexpr int kGK = 64;    // K elements per LDS stage
-
-template <class T>
-__global__ __launch_bounds__(kBlk) void k_gate_gemm(const ClipDev* __restrict__ clips,
-                                                    const GemmTileDev* __restrict__ tiles, int dim,
-                                                    const T* __restrict__ xv, const T* __restrict__ xa,
-                                                    const double* __restrict__ na, uint32_t* __restrict__ maxkey) {
-  using M = GMma<T>;
-  constexpr int kRowBytes = kGK * (int)sizeof(T);
-  constexpr int kPitch = kRowBytes + 16;
-  constexpr int kUnits = kRowBytes / 16;          // 16-byte units per tile row
-  constexpr int kPer = kGB * kUnits / kBlk;       // units per thread per tile
-  constexpr int kEl = 16 / (int)sizeof(T);        // elements per unit
-  __shared__ __attribute__((aligned(16))) char lds_a[2][kGB * kPitch];
-  __shared__ __attribute__((aligned(16))) char lds_b[2][kGB * kPitch];
-
-  const GemmTileDev tl = tiles[blockIdx.x];
-  const ClipDev c = clips[tl.clip];
-  if (!c.gate) return;
-  const int64_t n_a = c.n_audio, n_v = (int64_t)c.n_frames * c.per_frame;
-  const T* A = xa + c.aud_off * dim;
-  const T* B = xv + c.vis_off * dim;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wr = wave >> 1, wc = wave & 1;
-
-  uint4 ra[kPer], rb[kPer];
-  auto gload = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int u = tid + i * kBlk;
-      const int row = u / kUnits, col = u % kUnits;
-      const int kk = k0 + col * kEl;
-      uint4 x = make_uint4(0, 0, 0, 0), y = make_uint4(0, 0, 0, 0);
-      if (tl.m0 + row < n_a && kk < dim) x = *reinterpret_cast<const uint4*>(A + (tl.m0 + row) * (int64_t)dim + kk);
-      if (tl.n0 + row < n_v && kk < dim) y = *reinterpret_cast<const uint4*>(B + (tl.n0 + row) * (int64_t)dim + kk);
-      ra[i] = x;
-      rb[i] = y;
-    }
-  };
-  auto lstore = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int u = tid + i * kBlk;
-      const int row = u / kUnits, col = u % kUnits;
-      *reinterpret_cast<uint4*>(lds_a[buf] + row * kPitch + col * 16) = ra[i];
-      *reinterpret_cast<uint4*>(lds_b[buf] + row * kPitch + col * 16) = rb[i];
-    }
-  };
-  auto frag = [&](const char* lds, int row, int ks) {
-    const char* p = lds + row * kPitch + (ks * M::kstep + (lane >> 5) * M::lane_k) * (int)sizeof(T);
-    return *reinterpret_cast<const typename M::frag*>(p);
-  };
-
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
-  const int n_k = (dim + kGK - 1) / kGK;
-  gload(0);
-  for (int it = 0; it < n_k; ++it) {
-    const int buf = it & 1;
-    lstore(buf);
-    __syncthreads();
-    if (it + 1 < n_k) gload((it + 1) * kGK);
-#pragma unroll
-    for (int ks = 0; ks < kGK / M::kstep; ++ks) {
-      typename M::frag fa[2], fb[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        fa[i] = frag(lds_a[buf], wr * 64 + i * 32 + (lane & 31), ks);
-        fb[i] = frag(lds_b[buf], wc * 64 + i * 32 + (lane & 31), ks);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = M::mma(fa[i], fb[j], acc[i][j]);
-    }
-  }
-  // Epilogue: acc[i][j][e] is audio row wr*64 + i*32 + 8*(e/4) + 4*(lane/32) + e%4,
-  // visual column wc*64 + j*32 + lane%32.
-  float inv[2][16];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int64_t r = tl.m0 + wr * 64 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-      float s = -INFINITY;  // rows past the clip's audio never win the max
-      if (r < n_a) {
-        const double nn = na[c.aud_off + r];
-        s = nn > 0.0 ? (float)(1.0 / sqrt(nn)) : 0.0f;
-      }
-      inv[i][e] = s;
-    }
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    float m = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float x = inv[i][e] == -INFINITY ? -INFINITY : acc[i][j][e] * inv[i][e];
-        m = fmaxf(m, x);
-      }
-    m = fmaxf(m, __shfl_xor(m, 32));
-    const int64_t col = tl.n0 + wc * 64 + j * 32 + (lane & 31);
-    if (lane < 32 && col < n_v && m > -INFINITY) atomicMax(&maxkey[c.vis_off + col], order_key(m));
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Capped largest-remainder apportionment of `total` over items [0, n) with
 // weights w[i] and caps cap[i], run by one wave: lane l owns items l, l + 64,
 // ... and alone writes their fixed, quota and alloc entries.  Water-filling
@@ -983,11 +850,13 @@ __global__ __launch_bounds__(kPlanBlk) void k_plan(ClipDev* __restrict__ clips, 
 // fp64 Gram tiles on the matrix cores (v_mfma_f64_16x16x4f64), for the
 // anchor Grams and the spatial CKA.  A wave takes a 2 x 2 block of 16 x 16
 // tiles (three tiles of a block on the diagonal) over a slice of the
-// embedding, so each row it loads and widens feeds two MFMAs: widening one
-// element to fp64 costs about as much as the half MFMA it feeds, and with
-// one tile per wave the vector ALU, not the matrix core, set the rate
-// (anchor Grams of a ragged batch 808 -> 190 us, 20 -> 86 TFLOP/s counting
-// both triangles; spatial Gram of a 60 s clip 394 -> 110 us).
+// embedding, so each row it loads and widens feeds two MFMAs, and each
+// element is widened under the 64 cycles of the MFMA before it; with single
+// tiles, all of a step widened ahead of its MFMAs and every value masked for
+// the last step, the vector ALU took longer than the matrix core.  Spatial
+// Gram of a 60 s clip 392 -> 268 us (its MFMAs alone take 154), anchor Grams
+// of a 60 s clip 46 -> 34, of a 20 s clip at dim 2048 18.5 -> 14.5, of a
+// 290 s clip 117 -> 103.
 // MFMA operands: lane l supplies A[l % 16][k = l / 16] and B[k = l / 16][l % 16];
 // accumulator element e of lane l is D[4e + l / 16][l % 16].  Each lane
 // loads 8 consecutive elements of its row and feeds them to 8 MFMAs, lane
@@ -1886,18 +1755,11 @@ apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& 
                      dp.band_a, dp.cka, frame_cka, gate_fired);
   if ((st = launch_status("k_cka")) != APACK_OK) return st;
   if (pl.gemm_tiles > 0) {
-    if constexpr (std::is_same<T, bf16_t>::value) {
-      if (pl.use256) {
-        if ((st = launch_gate_gemm256(dp.clips, dp.gemm, pl.gemm_tiles, dim, xv, xa, dp.na, dp.maxkey, s)) !=
-            APACK_OK)
-          return st;
-      }
-    }
-    if (!pl.use256) {
-      hipLaunchKernelGGL(k_gate_gemm<T>, dim3((unsigned)pl.gemm_tiles), dim3(kBlk), 0, s, dp.clips, dp.gemm, dim,
-                         xv, xa, dp.na, dp.maxkey);
-      if ((st = launch_status("k_gate_gemm")) != APACK_OK) return st;
-    }
+    constexpr bool kBf16 = std::is_same<T, bf16_t>::value;
+    st = pl.use256 ? launch_gate_gemm256(dp.clips, dp.gemm, pl.gemm_tiles, dim, (const uint16_t*)xv, (const uint16_t*)xa,
+                                         dp.na, dp.maxkey, s)
+                   : launch_gate_gemm_any(dp.clips, dp.gemm, pl.gemm_tiles, dim, kBf16, xv, xa, dp.na, dp.maxkey, s);
+    if (st != APACK_OK) return st;
   }
   hipLaunchKernelGGL(k_plan, dim3(nc), dim3(kPlanBlk), 0, s, dp.clips, prm, dp.cka, dp.band_v, dp.vq, dp.qq, dp.rv,
                      dp.maxkey, dp.plan, dp.anchors, dp.scratch, (int64_t)(pl.total_frames + nc), frame_score,

@@ -89,21 +89,12 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   pl.total_audio = aud_end;
   pl.total_kept = kept;
   pl.total_gram = gram;
-  // Gate GEMM tiles: columns (visual) in groups of eight share an XCD.
-  std::vector<GemmTileDev> tiles;
-  for (int s = 0; s < n_seq; ++s) {
-    const ClipDev& c = pl.clips[s];
-    const int64_t nv = (int64_t)c.n_frames * c.per_frame;
-    if (nv == 0) continue;
-    const int mb = (int)((c.n_audio + 127) / 128), nb = (int)((nv + 127) / 128);
-    for (int g0 = 0; g0 < nb; g0 += 8)
-      for (int m = 0; m < mb; ++m)
-        for (int n = g0; n < std::min(g0 + 8, nb); ++n) tiles.push_back({s, m * 128, n * 128, 0});
-  }
-  pl.gemm_tiles = (int64_t)tiles.size();
+  // Gate GEMM tiles of either kernel, in the order its launch expects.
+  pl.gemm = gate_gemm_any_tiles(pl.clips);
+  pl.gemm_tiles = (int64_t)pl.gemm.size();
   if (dim % kGemm256K == 0) pl.gemm256 = gate_gemm256_tiles(pl.clips);
   // The blob holds whichever list the call uses.
-  const size_t n_tiles = std::max(tiles.size(), pl.gemm256.size());
+  const size_t n_tiles = std::max(pl.gemm.size(), pl.gemm256.size());
   // Workspace layout.
   const int64_t nc = n_seq;
   Carver c(nullptr);
@@ -152,7 +143,6 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   pl.off_sqp = c.used;
   c.take<double>((size_t)((dim + kPoolSlice - 1) / kPoolSlice) * (vis_end + aud_end));
   pl.ws_bytes = std::max<size_t>(c.used, kAlign);
-  pl.gemm = std::move(tiles);
   return APACK_OK;
 }
 

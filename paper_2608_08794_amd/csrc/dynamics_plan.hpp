@@ -115,6 +115,12 @@ apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles,
                                  const uint16_t* xv, const uint16_t* xa, const double* na, uint32_t* maxkey,
                                  hipStream_t stream);
 std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips);
+// The same for fp32 inputs (split into bf16 parts) and for bf16 inputs of
+// any other dim.
+apack_status launch_gate_gemm_any(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int dim, bool bf16,
+                                  const void* xv, const void* xa, const double* na, uint32_t* maxkey,
+                                  hipStream_t stream);
+std::vector<GemmTileDev> gate_gemm_any_tiles(const std::vector<ClipDev>& clips);
 constexpr int kGemm256K = 64;   // dim must be a multiple of this for the 256-tile kernel
 constexpr int kPoolSlice = 512;  // embedding elements per coarse-pass block (8 per lane)
 

@@ -330,3 +330,34 @@ def test_gram_blocks_at_their_edges(dim, per_frame, audio, alignment):
     want = _oracle(case)
     _certify(want)
     _compare(case, _run(case), want)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dim,frames,audio", [
+    (8, 127, 255),     # one partial K step, one short tile
+    (40, 128, 256),    # a whole tile
+    (264, 129, 257),   # one row and one column past a tile
+    (1288, 300, 600),  # several tiles, a partial last K step
+])
+def test_gate_gemm_of_any_dim_and_dtype(dim, frames, audio, dtype):
+    """Largest cosines of single-token frames (the frame score is 1 - d_hat
+    with gamma 0) where the products' tiles and K steps have remainders, for
+    fp32 rows (three bf16 parts each) and for bf16 rows."""
+    import paper_2608_08794_amd as A
+    rng = np.random.default_rng(dim)
+    wide = np.exp(2.0 * rng.standard_normal((frames + audio, dim)))   # values over many binades
+    x = (rng.standard_normal((frames + audio, dim)) * wide).astype(np.float32)
+    raw = W.to_bf16_bits(x) if dtype == "bf16" else x
+    xv, xa = raw[:frames], raw[frames:]
+    clip = dict(n_frames=frames, per_frame=1, n_audio=audio, n_query=1, vis_off=0, aud_off=0, qry_off=0)
+    out = A.apack_score_dynamics(to_dev(xv, dtype), to_dev(xa, dtype), to_dev(xa[:1], dtype), [clip],
+                                 {"alignment": "av_cosine", "gamma": 0.0, "r_pre": 1.0})
+    got = out["score"].cpu().numpy().astype(np.float64)
+    d, _ = OD.direct_distance(widen(xv, dtype), widen(xa, dtype), frames, 1)
+    want = 1.0 - OD.minmax(d)
+    # Each of the 6 K / 32 partial sums (and K / 32 in bf16), the parts left
+    # out and the scaling round by at most 2^-24 of sum |x y| <= |x| |y|; the
+    # score holds three such errors over the range of d, and its own rounding.
+    n = (6 if dtype == "f32" else 1) * (dim // 32 + 1) + 4
+    tol = 4.0 * n * 2.0 ** -24 / (d.max() - d.min()) + 2.0 ** -23
+    np.testing.assert_allclose(got, want, rtol=0, atol=tol)
