@@ -83,6 +83,9 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
     }
     const int64_t nb = (nt + 1) / 2;
     pl.spatial_blocks = (int32_t)(nb * (nb + 1) / 2);
+    // Sums are kept per block; the workspace has room for them per tile, as
+    // callers who keep one across versions have sized it.
+    pl.spatial_slots = (int32_t)(nt * (nt + 1) / 2);
   }
   pl.total_frames = frames;
   pl.total_tokens = vis_end;
@@ -137,7 +140,7 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   pl.off_sim = c.used;
   c.take<double>(tokens);
   pl.off_spatial = c.used;
-  c.take<double>((size_t)frames * pl.spatial_blocks * 3);
+  c.take<double>((size_t)frames * pl.spatial_slots * 3);
   pl.off_anchors = c.used;
   c.take<int32_t>(frames);
   pl.off_sqp = c.used;

@@ -58,6 +58,7 @@ struct DynPlan {
   int64_t total_frames = 0, total_tokens = 0, total_audio = 0, total_kept = 0, total_gram = 0;
   int max_per_frame = 1;
   int64_t gemm_tiles = 0;            // gate GEMM workgroups over all clips
+  int32_t spatial_slots = 0;         // slots of three sums per frame in the workspace, at least spatial_blocks
   int32_t spatial_blocks = 0;        // spatial CKA Gram blocks (2 x 2 tiles) per frame (0 unless selected)
   std::vector<GemmTileDev> gemm;
   std::vector<GemmTileDev> gemm256;  // 256 x 256 tiles (dim a multiple of 64), XCD-ordered
