@@ -325,11 +325,25 @@ __device__ __forceinline__ void merge(float& m, float& s, float mo, float so) {
 // Pass 1: per query row, online max and sum of exp2 over one key chunk.
 // C = K Q^T: lane (l % 32) owns a query column and 16 key rows per block.
 // ---------------------------------------------------------------------------
+// Workgroup b's tile of a call with one sequence, in the order the host
+// lists them.
+__device__ __forceinline__ TileDev inline_tile(const SeqDev& sq, int b) {
+  const int per_g = sq.n_chunks * sq.n_rg;
+  TileDev t;
+  t.seq = 0;
+  t.g = b / per_g;
+  const int r = b - t.g * per_g, c0 = r / (8 * sq.n_rg) * 8, left = r - c0 * sq.n_rg;
+  const int w = min(8, sq.n_chunks - c0);
+  t.rg = left / w;
+  t.chunk = c0 + left - t.rg * w;
+  return t;
+}
+
 template <class T, int D, int NW, int S>
-__global__ __launch_bounds__(NW * kWave) void k_rowstats(const SeqDev* __restrict__ seqs,
-                                                         const TileDev* __restrict__ tiles,
-                                                         const uint8_t* __restrict__ tags,
-                                                         const T* __restrict__ q, int64_t q_hs,
+__global__ __launch_bounds__(NW * kWave) void k_rowstats(const InlineCall in, SeqDev* __restrict__ seqs,
+                                                         TileDev* __restrict__ tiles,
+                                                         FTileDev* __restrict__ ftiles, uint8_t* __restrict__ tags,
+                                                         uint32_t* __restrict__ ctr, const T* __restrict__ q, int64_t q_hs,
                                                          const T* __restrict__ k, int64_t k_hs,
                                                          int n_rep, float scale_log2,
                                                          float2* __restrict__ stats, uint32_t* __restrict__ zero,
@@ -342,8 +356,9 @@ __global__ __launch_bounds__(NW * kWave) void k_rowstats(const SeqDev* __restric
   // before the loop so that no tile waits on a load of its tags.
   __shared__ __attribute__((aligned(16))) float lmask[kMaxChunk];
 
-  const TileDev tl = tiles[blockIdx.x];
-  const SeqDev sq = seqs[tl.seq];
+  const bool inl = in.n_spans >= 0;
+  const TileDev tl = inl ? inline_tile(in.seq, blockIdx.x) : tiles[blockIdx.x];
+  const SeqDev sq = inl ? in.seq : seqs[tl.seq];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rows_g = n_rep * sq.q_len;
   const int rg_end = min(rows_g, (tl.rg + 1) * sq.rows_per_rg);
@@ -371,11 +386,30 @@ __global__ __launch_bounds__(NW * kWave) void k_rowstats(const SeqDev* __restric
   QFrags<T, D> qfr;
   auto& qf = qfr.v;
   if (active) load_q<T, D>(qfr, q, q_hs, sq, tl.g, n_rep, row0, lane);
-  const uint8_t* tg = tags + sq.tag_off;
+  uint8_t* tg = tags + sq.tag_off;
 
-  // Tags are read in batches of 8 per thread, all in flight together (the
-  // index is clamped to a valid row; rows past the chunk get -inf).
-  {
+  if (inl) {
+    // Tags from the spans, written once per chunk; then what the later
+    // kernels read, spread over the workgroups.
+    const bool write_tags = tl.g == 0 && tl.rg == 0;
+    const int n_mask = n_tiles * kKeyTile;
+    for (int i = tid; i < n_mask; i += NW * kWave) {
+      const int64_t r = key_begin + i;
+      int tag = 0;
+      for (int s = 0; s < in.n_spans; ++s)
+        if (r >= in.spans[s].begin && r < in.spans[s].end) tag = in.spans[s].tag;
+      lmask[i] = r < key_end && tag != 0 ? 0.0f : -INFINITY;
+      if (write_tags && r < key_end) tg[r] = (uint8_t)tag;
+    }
+    const int stride = (int)gridDim.x * NW * kWave, t = (int)blockIdx.x * NW * kWave + tid;
+    for (int i = t; i < in.n_ctr; i += stride) ctr[i] = 0;
+    for (int i = t; i < sq.n_ftiles; i += stride) ftiles[i] = FTileDev{0, i};
+    if (tid == 0) tiles[blockIdx.x] = tl;
+    if (blockIdx.x == 0 && tid < (int)(sizeof(SeqDev) / 4))
+      reinterpret_cast<uint32_t*>(seqs)[tid] = reinterpret_cast<const uint32_t*>(&in.seq)[tid];
+  } else {
+    // Tags are read in batches of 8 per thread, all in flight together (the
+    // index is clamped to a valid row; rows past the chunk get -inf).
     constexpr int kB = 8;
     const int n_mask = n_tiles * kKeyTile;
     for (int b0 = 0; b0 < n_mask; b0 += kB * NW * kWave) {
@@ -814,13 +848,13 @@ __global__ __launch_bounds__(NW * kWave) void k_colsum(SeqDev* __restrict__ seqs
 // Host launch sequence.
 // ---------------------------------------------------------------------------
 template <class T, int D, int NW, int S = key_stages<T, D, NW>()>
-apack_status launch_scores_t(const PrunePlan& pl, const DevPtrs& dp, const void* q, int64_t q_hs,
+apack_status launch_scores_t(const PrunePlan& pl, const DevPtrs& dp, const InlineCall& in, const void* q, int64_t q_hs,
                              const void* k, int64_t k_hs, int n_rep, int hkv, float* scores, hipStream_t stream) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   const int nt = (int)pl.tiles.size();
   if (nt > 0) {
-    hipLaunchKernelGGL((k_rowstats<T, D, NW, S>), dim3(nt), dim3(NW * kWave), 0, stream, dp.seqs, dp.tiles,
-                       dp.tags, (const T*)q, q_hs, (const T*)k, k_hs, n_rep, scale_log2, dp.stats, dp.hist,
+    hipLaunchKernelGGL((k_rowstats<T, D, NW, S>), dim3(nt), dim3(NW * kWave), 0, stream, in, dp.seqs, dp.tiles,
+                       dp.ftiles, dp.tags, dp.ctr, (const T*)q, q_hs, (const T*)k, k_hs, n_rep, scale_log2, dp.stats, dp.hist,
                        pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : (int64_t)0);
     APACK_CHECK(launch_status("k_rowstats") == APACK_OK, APACK_E_HIP, "%s", apack_last_error());
     hipLaunchKernelGGL((k_colsum<T, D, NW, S>), dim3(nt), dim3(NW * kWave), 0, stream, dp.seqs, dp.tiles, dp.tags,
@@ -832,7 +866,7 @@ apack_status launch_scores_t(const PrunePlan& pl, const DevPtrs& dp, const void*
 }
 
 template <class T, int D>
-apack_status launch_scores_d(const PrunePlan& pl, const DevPtrs& dp, const void* q, int64_t q_hs,
+apack_status launch_scores_d(const PrunePlan& pl, const DevPtrs& dp, const InlineCall& in, const void* q, int64_t q_hs,
                              const void* k, int64_t k_hs, int n_rep, int hkv, float* scores, hipStream_t stream) {
   // Up to four waves of query rows run as four-wave workgroups: with one or
   // two row waves the others only share the tile loads and the chunk's
@@ -840,25 +874,25 @@ apack_status launch_scores_d(const PrunePlan& pl, const DevPtrs& dp, const void*
   switch (pl.waves) {
     case 1:
     case 2:
-    case 4: return launch_scores_t<T, D, 4>(pl, dp, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
-    case 7: return launch_scores_t<T, D, 7>(pl, dp, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
-    default: return launch_scores_t<T, D, 8>(pl, dp, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
+    case 4: return launch_scores_t<T, D, 4>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
+    case 7: return launch_scores_t<T, D, 7>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
+    default: return launch_scores_t<T, D, 8>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
   }
 }
 
 }  // namespace
 
-apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, apack_dtype dt, int d, int hq, int hkv,
+apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCall& in, apack_dtype dt, int d, int hq, int hkv,
                           const void* q, int64_t q_hs, const void* k, int64_t k_hs, float* scores,
                           int32_t* kept, hipStream_t stream) {
   const int n_rep = hq / hkv;
   apack_status st;
   if (dt == APACK_BF16)
-    st = d == 64 ? launch_scores_d<bf16_t, 64>(pl, dp, q, q_hs, k, k_hs, n_rep, hkv, scores, stream)
-                 : launch_scores_d<bf16_t, 128>(pl, dp, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
+    st = d == 64 ? launch_scores_d<bf16_t, 64>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream)
+                 : launch_scores_d<bf16_t, 128>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
   else
-    st = d == 64 ? launch_scores_d<float, 64>(pl, dp, q, q_hs, k, k_hs, n_rep, hkv, scores, stream)
-                 : launch_scores_d<float, 128>(pl, dp, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
+    st = d == 64 ? launch_scores_d<float, 64>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream)
+                 : launch_scores_d<float, 128>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
   if (st != APACK_OK) return st;
   if (pl.total_tok == 0) return APACK_OK;
   return launch_select(pl, dp, scores, kept, stream);

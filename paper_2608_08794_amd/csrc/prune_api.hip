@@ -224,6 +224,37 @@ apack_status apack_prune_layer(int32_t n_seq, const apack_seq* seqs, apack_dtype
     for (int s = 0; s < n_seq; ++s) n_kept[s] = pl.n_kept[s];
   if (pl.total_tok == 0) return APACK_OK;
 
+  hipStream_t hs = static_cast<hipStream_t>(stream);
+  char* ws = static_cast<char*>(workspace);
+  DevPtrs dp;
+  dp.seqs = reinterpret_cast<SeqDev*>(ws);
+  dp.tiles = reinterpret_cast<TileDev*>(ws + pl.off_tiles);
+  dp.ftiles = reinterpret_cast<FTileDev*>(ws + pl.off_ftiles);
+  dp.hist = reinterpret_cast<uint32_t*>(ws + pl.off_hist);
+  dp.cnt = reinterpret_cast<uint32_t*>(ws + pl.off_cnt);
+  dp.ctr = reinterpret_cast<uint32_t*>(ws + pl.off_ctr);
+  dp.tags = reinterpret_cast<uint8_t*>(ws + pl.off_tags);
+  dp.stats = reinterpret_cast<float2*>(ws + pl.off_stats);
+  dp.colpart = reinterpret_cast<float*>(ws + pl.off_colpart);
+  // Tag = selection slot + 1: the modality, or slot 1 for every candidate of
+  // a jointly ranked sequence.
+  auto tag_of = [&](int s, const apack_span& sp) {
+    return seqs[s].flags == APACK_RANK_JOINT && sp.modality != APACK_OTHER ? 1 : sp.modality;
+  };
+  // One sequence with few spans passes its descriptors by value (its score
+  // kernels must run: they write what the select reads).
+  InlineCall in;
+  in.n_spans = -1;
+  if (n_seq == 1 && seqs[0].n_spans <= kInlineSpans && !pl.tiles.empty()) {
+    in.seq = pl.seqs[0];
+    in.n_spans = seqs[0].n_spans;
+    in.n_ctr = (int32_t)pl.total_ctr;
+    for (int i = 0; i < in.n_spans; ++i) {
+      const apack_span& sp = seqs[0].spans[i];
+      in.spans[i] = {(int32_t)sp.begin, (int32_t)(sp.begin + sp.len), tag_of(0, sp)};
+    }
+    return launch_prune(pl, dp, in, dtype, d, hq, hkv, q, q_head_stride, k, k_head_stride, scores, kept_rows, hs);
+  }
   // Host blob: sequence descriptors, tiles and per-row modality tags.
   Staging* blk;
   void* host;
@@ -235,30 +266,15 @@ apack_status apack_prune_layer(int32_t n_seq, const apack_seq* seqs, apack_dtype
     std::memcpy(h + pl.off_ftiles, pl.ftiles.data(), pl.ftiles.size() * sizeof(FTileDev));
   uint8_t* tags = reinterpret_cast<uint8_t*>(h + pl.off_tags);
   std::memset(tags, 0, pl.total_tok);
-  // Tag = selection slot + 1: the modality, or slot 1 for every candidate of
-  // a jointly ranked sequence.
   for (int s = 0; s < n_seq; ++s)
     for (int i = 0; i < seqs[s].n_spans; ++i) {
       const apack_span& sp = seqs[s].spans[i];
       if (sp.modality != APACK_OTHER)
-        std::memset(tags + pl.seqs[s].tag_off + sp.begin, seqs[s].flags == APACK_RANK_JOINT ? 1 : sp.modality,
-                    (size_t)sp.len);
+        std::memset(tags + pl.seqs[s].tag_off + sp.begin, tag_of(s, sp), (size_t)sp.len);
     }
   std::memset(h + pl.off_ctr, 0, pl.total_ctr * sizeof(uint32_t));
-  hipStream_t hs = static_cast<hipStream_t>(stream);
-  char* ws = static_cast<char*>(workspace);
   if ((st = staging_upload(blk, ws, pl.blob_bytes, hs)) != APACK_OK) return st;
-  DevPtrs dp;
-  dp.seqs = reinterpret_cast<SeqDev*>(ws);
-  dp.tiles = reinterpret_cast<TileDev*>(ws + pl.off_tiles);
-  dp.ftiles = reinterpret_cast<FTileDev*>(ws + pl.off_ftiles);
-  dp.hist = reinterpret_cast<uint32_t*>(ws + pl.off_hist);
-  dp.cnt = reinterpret_cast<uint32_t*>(ws + pl.off_cnt);
-  dp.ctr = reinterpret_cast<uint32_t*>(ws + pl.off_ctr);
-  dp.tags = reinterpret_cast<uint8_t*>(ws + pl.off_tags);
-  dp.stats = reinterpret_cast<float2*>(ws + pl.off_stats);
-  dp.colpart = reinterpret_cast<float*>(ws + pl.off_colpart);
-  const apack_status ls = launch_prune(pl, dp, dtype, d, hq, hkv, q, q_head_stride, k, k_head_stride, scores,
+  const apack_status ls = launch_prune(pl, dp, in, dtype, d, hq, hkv, q, q_head_stride, k, k_head_stride, scores,
                                        kept_rows, hs);
   const apack_status rs = staging_release(blk, hs);
   return ls != APACK_OK ? ls : rs;

@@ -58,6 +58,27 @@ struct SeqDev {
   int32_t ctr_off;      // arrival counters: [n_chunks key chunks][1 sequence]
 };
 
+// A run of rows [begin, end) of one tag (see apack_prune_layer's tags).
+struct SpanDev {
+  int32_t begin, end, tag;
+};
+
+// The descriptors of a call with one sequence of at most kInlineSpans spans,
+// passed to the first score kernel by value: it needs no upload and no loads
+// of descriptors, and writes what the later kernels read (the sequence, its
+// tiles, tags and zeroed counters) into the workspace itself.  The upload
+// kernel, its pinned block and two dependent loads had cost 3-5 us of a call
+// (9454-row layers 61.3 -> 58.1 and 69.5 -> 66.9 us, the 1312-row fp32 layer
+// 53.6 -> 49.8).  Longer span lists (each key tests every span) and batches
+// are uploaded; n_spans is then -1.
+constexpr int kInlineSpans = 16;
+struct InlineCall {
+  SeqDev seq;
+  int32_t n_spans;
+  int32_t n_ctr;        // arrival counters to clear
+  SpanDev spans[kInlineSpans];
+};
+
 struct FTileDev {
   int32_t seq, idx;     // sequence and row tile within it (rows idx*kRowTile ...)
 };
@@ -104,7 +125,7 @@ int64_t select_hist_words(int64_t n_seq);   // radix histogram words of n_seq se
 apack_status launch_select(const PrunePlan& pl, const DevPtrs& dp, float* scores, int32_t* kept,
                            hipStream_t stream);
 
-apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, apack_dtype dt, int d, int hq, int hkv,
+apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCall& in, apack_dtype dt, int d, int hq, int hkv,
                           const void* q, int64_t q_hs, const void* k, int64_t k_hs, float* scores,
                           int32_t* kept, hipStream_t stream);
 

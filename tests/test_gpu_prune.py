@@ -596,3 +596,33 @@ def test_entry_points_on_a_side_stream():
                           s.per_frame, dyn.params)
     np.testing.assert_array_equal(got["kept"].cpu().numpy().astype(np.int64), r["kept"])
     np.testing.assert_array_equal(got["budget"].cpu().numpy(), r["frame_budget"])
+
+
+@pytest.mark.parametrize("joint", [False, True])
+@pytest.mark.parametrize("pieces", [2, 15, 16, 17, 40])
+def test_descriptors_by_value_and_uploaded_agree(pieces, joint):
+    """One sequence passes its descriptors by value up to 16 spans and
+    through the upload past that: the same rows written as more spans (an
+    OTHER run, an empty one and gaps among them) give the same bits."""
+    import paper_2608_08794_amd as A
+    rng = np.random.default_rng(5)
+    n, nt, hq, hkv, d, ql = 3000, 3111, 28, 4, 128, 5
+    q, k = (to_dev(W.to_bf16_bits(rng.standard_normal(s).astype(np.float32)), "bf16")
+            for s in ((hq, ql, d), (hkv, nt, d)))
+    base = [(7, 900, W.AUDIO), (1000, n - 1000, W.VISUAL)]
+
+    def run(spans):
+        seq = W.PruneSeq(0, nt, spans, 0, ql, (0.45, 0.0) if joint else (0.45, 0.3), (0, 0), joint)
+        s, kept, nk = A.apack_prune_layer(q, k, [seq])
+        torch.cuda.synchronize()
+        return bits(s), bits(kept), nk
+
+    spans = [base[0], (907, 20, W.OTHER), (950, 0, W.AUDIO)]
+    cut = max(1, pieces - 3)
+    edges = np.linspace(1000, n, cut + 1).astype(int)
+    spans += [(int(a), int(b - a), W.VISUAL) for a, b in zip(edges[:-1], edges[1:])]
+    assert len(spans) == max(4, pieces)
+    want, got = run(base), run(spans)
+    assert want[2] == got[2]
+    np.testing.assert_array_equal(want[0], got[0])
+    np.testing.assert_array_equal(want[1], got[1])
