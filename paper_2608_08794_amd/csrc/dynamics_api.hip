@@ -95,7 +95,7 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   // Gate GEMM tiles of either kernel, in the order its launch expects.
   pl.gemm = gate_gemm_any_tiles(pl.clips);
   pl.gemm_tiles = (int64_t)pl.gemm.size();
-  if (dim % kGemm256K == 0) pl.gemm256 = gate_gemm256_tiles(pl.clips);
+  if (dim % kGemm256K == 0) pl.gemm256 = gate_gemm256_tiles(pl.clips, &pl.gemm256_bi);
   // The blob holds whichever list the call uses.
   const size_t n_tiles = std::max(pl.gemm.size(), pl.gemm256.size());
   // Workspace layout.

@@ -62,6 +62,7 @@ struct DynPlan {
   int32_t spatial_blocks = 0;        // spatial CKA Gram blocks (2 x 2 tiles) per frame (0 unless selected)
   std::vector<GemmTileDev> gemm;
   std::vector<GemmTileDev> gemm256;  // 256 x 256 tiles (dim a multiple of 64), XCD-ordered
+  int gemm256_bi = 8;                // their rows / 32
   bool use256 = false;               // set per call: bf16 inputs and gemm256 planned
   // Workspace layout (byte offsets).
   size_t off_clips = 0, off_frames = 0, off_gemm = 0, blob_bytes = 0;
@@ -112,10 +113,10 @@ struct DynPtrs {
 // The gate GEMM on 256 x 256 tiles for bf16 inputs whose dim is a multiple
 // of 64 (gate_gemm.hip); `tiles` holds one tile per workgroup, already in
 // the order the launch expects.
-apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int dim,
+apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int bi, int dim,
                                  const uint16_t* xv, const uint16_t* xa, const double* na, uint32_t* maxkey,
                                  hipStream_t stream);
-std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips);
+std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips, int* bi);
 // The same for fp32 inputs (split into bf16 parts) and for bf16 inputs of
 // any other dim.
 apack_status launch_gate_gemm_any(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int dim, bool bf16,

@@ -4,11 +4,12 @@
 // bf16 MFMA with fp32 accumulation.  This is the kernel for bf16 inputs
 // whose dim is a multiple of 64; k_gate_gemm in dynamics.hip covers the rest.
 //
-// Each workgroup owns a 256 x 256 tile (audio rows x visual columns); its
-// eight waves (two per SIMD) own 128 x 64 blocks as 8 x 4 blocks of
-// v_mfma_f32_16x16x32_bf16, so a wave reads 12 fragments from LDS per 32
-// MFMAs.  K streams through two 64-element LDS stages (2 x 64 KiB), filled
-// by 16-byte direct-to-LDS loads; the 128-byte rows are stored with their
+// Each workgroup owns a tile of 32 BI x 256 (audio rows x visual columns; BI
+// is 8 unless fewer rows fill the chip better, see gate_gemm256_tiles); its
+// eight waves (two per SIMD) own 16 BI x 64 blocks as BI x 4 blocks of
+// v_mfma_f32_16x16x32_bf16, so with BI = 8 a wave reads 12 fragments from
+// LDS per 32 MFMAs.  K streams through two 64-element LDS stages (2 x 64 KiB
+// with BI = 8), filled by 16-byte direct-to-LDS loads; the 128-byte rows are stored with their
 // 16-byte chunks XOR-swizzled by the row index, so the fragment reads of
 // consecutive rows hit distinct banks without padding.  Every output
 // element sums K in order, 32 elements per MFMA, whatever its tile.  The
@@ -25,8 +26,8 @@
 // fewer LDS reads) took 4.06 ms: one wave per SIMD leaves its waits bare.
 //
 // Workgroups are dealt to the eight XCDs round-robin by index, so the host
-// lists the tiles so that each XCD gets whole column blocks of one band of
-// at most eight row tiles, and the workgroups resident on one XCD share
+// lists the tiles so that each XCD gets a run of column blocks of one band
+// of at most eight row tiles, and the workgroups resident on one XCD share
 // both operands in that XCD's L2: a band's audio rows and a few column
 // blocks of visual rows.
 #include <algorithm>
@@ -44,20 +45,37 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 typedef __attribute__((address_space(1))) void* glb_ptr_t;
 
-constexpr int kTile = 256;                     // rows and columns per workgroup
+constexpr int kTileN = 256;                    // columns per workgroup
 constexpr int kK = kGemm256K;                  // K elements per LDS stage
 constexpr int kRowB = kK * 2;                  // bytes of one row per stage
 constexpr int kChunks = kRowB / 16;            // 16-byte chunks per row
-constexpr int kOpB = kTile * kRowB;            // one operand's stage
-constexpr int kStageB = 2 * kOpB;
 constexpr int kWaves = 8;
 constexpr int kWN = 4;                         // waves along the visual columns
-constexpr int kBI = kTile / (kWaves / kWN) / 16;  // 16-row blocks per wave
-constexpr int kBJ = kTile / kWN / 16;             // 16-column blocks per wave
-constexpr int kReads = kBI + kBJ;                 // fragments of one 32-element K slice
-constexpr int kMfmas = kBI * kBJ;                 // MFMAs of one slice
-constexpr int kLoadsPerWave = kOpB / 1024 / kWaves;  // 1 KiB loads per wave per operand
-static_assert(kK == 64 && kMfmas >= 2 * kReads && kMfmas >= 3 * 2 * kLoadsPerWave, "slots of the K-slice schedule");
+constexpr int kBJ = kTileN / kWN / 16;         // 16-column blocks per wave
+static_assert(kK == 64, "two 32-element slices per stage");
+
+// Shape of a tile of 32 BI rows.
+template <int BI>
+struct TileGeom {
+  static constexpr int kTileM = kWaves / kWN * BI * 16;
+  static constexpr int kOpA = kTileM * kRowB, kOpB = kTileN * kRowB;   // operands' bytes per stage
+  static constexpr int kStageB = kOpA + kOpB;
+  // LDS stages: a stage of few rows carries too little arithmetic to cover
+  // the latency of its loads, so they run further ahead (bi = 2: 49 us with
+  // two stages, 35 with four).
+  static constexpr int kStages = 160 * 1024 / kStageB < 4 ? 160 * 1024 / kStageB : 4;
+  static constexpr int kReads = BI + kBJ;      // fragments of one 32-element K slice
+  static constexpr int kMfmas = BI * kBJ;      // MFMAs of one slice
+  // 1 KiB loads per wave and stage.  Where the waves do not share the audio
+  // rows evenly, the last load is issued by more than one wave (the same
+  // bytes to the same place).
+  static constexpr int kLoadsA = (kOpA / 1024 + kWaves - 1) / kWaves, kLoadsB = kOpB / 1024 / kWaves;
+  static constexpr int kLoads = kLoadsA + kLoadsB;
+  // MFMAs from one fragment read, and from one load, to the next.
+  static constexpr int kReadStep = kMfmas >= 2 * kReads ? 2 : 1;
+  static constexpr int kLoadStep = kMfmas >= 3 * kLoads ? 3 : kMfmas >= 2 * kLoads ? 2 : 1;
+  static_assert(kMfmas >= kReads && kMfmas >= kLoads && kStages >= 2, "slots of the K-slice schedule");
+};
 constexpr int kXcds = 8;
 
 // Chunk c of row r sits at chunk c ^ swz(r).  A 16-byte LDS read is served
@@ -68,35 +86,19 @@ constexpr int kXcds = 8;
 constexpr int kRowsPer256 = 256 / kRowB;
 __device__ __forceinline__ int swz(int r) { return (r / kRowsPer256) & (kChunks - 1); }
 
-// One operand's stage: rows r0 .. r0+255 (clamped to the last valid row),
+// One operand's stage: rows r0, r0 + 1, ... (clamped to the last valid row),
 // elements [k0, k0 + kK).  Load j fills LDS bytes [1024 j, 1024 j + 1024);
 // lane l's 16 bytes land at row r = (1024 j + 16 l) / kRowB, chunk c, and
-// come from global chunk c ^ swz(r).  off[i] is lane l's byte offset of load
-// i from the stage's first byte (row r0, element k0), the same for every
-// stage, so a stage only moves the scalar base.
-__device__ __forceinline__ void operand_offsets(int64_t r0, int64_t n_rows, int dim, int wave, int lane,
-                                                uint32_t (&off)[kLoadsPerWave]) {
-#pragma unroll
-  for (int i = 0; i < kLoadsPerWave; ++i) {
-    const int j = wave * kLoadsPerWave + i;
-    const int byte = j * 1024 + lane * 16;
-    const int r = byte / kRowB;
-    const int c = ((byte % kRowB) >> 4) ^ swz(r);
-    const int64_t left = n_rows - 1 - r0;
-    const int rr = left < r ? (int)left : r;
-    off[i] = (uint32_t)rr * (uint32_t)dim * 2u + (uint32_t)c * 16u;
-  }
-}
-
-// Load l of a wave's share of a stage (l < kLoadsPerWave: audio, else visual).
-__device__ __forceinline__ void issue_load(char* stage, const char* base_a, const char* base_b,
-                                           const uint32_t (&off_a)[kLoadsPerWave],
-                                           const uint32_t (&off_b)[kLoadsPerWave], int wave, int l) {
-  const int i = l % kLoadsPerWave, j = wave * kLoadsPerWave + i;
-  if (l < kLoadsPerWave)
-    __builtin_amdgcn_global_load_lds((glb_ptr_t)(base_a + off_a[i]), (lds_ptr_t)(stage + j * 1024), 16, 0, 0);
-  else
-    __builtin_amdgcn_global_load_lds((glb_ptr_t)(base_b + off_b[i]), (lds_ptr_t)(stage + kOpB + j * 1024), 16, 0, 0);
+// come from global chunk c ^ swz(r).  The result is lane l's byte offset of
+// load j from the stage's first byte (row r0, element k0), the same for
+// every stage, so a stage only moves the scalar base.
+__device__ __forceinline__ uint32_t load_offset(int64_t r0, int64_t n_rows, int dim, int j, int lane) {
+  const int byte = j * 1024 + lane * 16;
+  const int r = byte / kRowB;
+  const int c = ((byte % kRowB) >> 4) ^ swz(r);
+  const int64_t left = n_rows - 1 - r0;
+  const int rr = left < r ? (int)left : r;
+  return (uint32_t)rr * (uint32_t)dim * 2u + (uint32_t)c * 16u;
 }
 
 // p as a scalar (it is the same in every lane), so that the loads that add a
@@ -152,10 +154,15 @@ __device__ __forceinline__ void column_maxima(const f32x4 (&acc)[BI][BJ], const 
   }
 }
 
+template <int BI>
 __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gate_gemm256(
     const ClipDev* __restrict__ clips, const GemmTileDev* __restrict__ tiles, int dim, const uint16_t* __restrict__ xv,
     const uint16_t* __restrict__ xa, const double* __restrict__ na, uint32_t* __restrict__ maxkey) {
-  __shared__ __attribute__((aligned(16))) char lds[2 * kStageB];
+  using G = TileGeom<BI>;
+  constexpr int kBI = BI, kStageB = G::kStageB, kOpA = G::kOpA, kReads = G::kReads, kMfmas = G::kMfmas,
+                kLoads = G::kLoads;
+  constexpr int S = G::kStages;
+  __shared__ __attribute__((aligned(16))) char lds[S * kStageB];
   const GemmTileDev tl = tiles[blockIdx.x];
   if (tl.clip < 0) return;  // padding of an XCD's share
   const ClipDev c = clips[tl.clip];
@@ -173,16 +180,26 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
     for (int j = 0; j < kBJ; ++j) acc[i][j] = f32x4{};
 
   const int n_k = dim / kK;
-  uint32_t off_a[kLoadsPerWave], off_b[kLoadsPerWave];
-  operand_offsets(tl.m0, n_a, dim, wave, lane, off_a);
-  operand_offsets(tl.n0, n_v, dim, wave, lane, off_b);
   const char* base_a = reinterpret_cast<const char*>(A + tl.m0 * dim);
   const char* base_b = reinterpret_cast<const char*>(B + tl.n0 * dim);
+  // Load l of this wave's share of a stage: audio rows first.
+  int at[kLoads];         // LDS byte of the load within the stage
+  uint32_t off[kLoads];   // this lane's offset from its base
+#pragma unroll
+  for (int l = 0; l < kLoads; ++l) {
+    const bool audio = l < G::kLoadsA;
+    const int j = audio ? min(wave + kWaves * l, kOpA / 1024 - 1) : wave + kWaves * (l - G::kLoadsA);
+    at[l] = (audio ? 0 : kOpA) + j * 1024;
+    off[l] = audio ? load_offset(tl.m0, n_a, dim, j, lane) : load_offset(tl.n0, n_v, dim, j, lane);
+  }
+  auto issue_load = [&](char* stage, const char* ga, const char* gb, int l) {
+    __builtin_amdgcn_global_load_lds((glb_ptr_t)((l < G::kLoadsA ? ga : gb) + off[l]), (lds_ptr_t)(stage + at[l]), 16, 0,
+                                     0);
+  };
   auto issue = [&](int k_stage) {
 #pragma unroll
-    for (int l = 0; l < 2 * kLoadsPerWave; ++l)
-      issue_load(lds + (k_stage & 1) * kStageB, base_a + (size_t)k_stage * kRowB, base_b + (size_t)k_stage * kRowB, off_a,
-                 off_b, wave, l);
+    for (int l = 0; l < kLoads; ++l)
+      issue_load(lds + k_stage * kStageB, base_a + (size_t)k_stage * kRowB, base_b + (size_t)k_stage * kRowB, l);
   };
   // Fragments of the slice in hand and of the next one; read r of a slice in
   // the order its MFMAs first need them: fa[0], fb[0 ..], fa[1 ..].
@@ -190,17 +207,18 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   const int row_a = wm * kBI * 16 + (lane & 15), row_b = wn * kBJ * 16 + (lane & 15);
   auto read = [&](const char* stage, int ks, int r) {
     if (r >= 1 && r <= kBJ)
-      fb[ks][r - 1] = lds_frag(stage + kOpB, row_b + 16 * (r - 1), ks, lane);
+      fb[ks][r - 1] = lds_frag(stage + kOpA, row_b + 16 * (r - 1), ks, lane);
     else
       fa[ks][r == 0 ? 0 : r - kBJ] = lds_frag(stage, row_a + 16 * (r == 0 ? 0 : r - kBJ), ks, lane);
   };
-  issue(0);
-  if (n_k > 1) {
-    issue(1);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoadsPerWave) : "memory");
-  } else {
+  // The first S stages (issue takes a stage below S); stage 0 is awaited.
+#pragma unroll
+  for (int p = 0; p < S; ++p)
+    if (p < n_k) issue(p);
+  if (n_k >= S)
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 1) * kLoads) : "memory");
+  else
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 #pragma unroll
@@ -208,24 +226,29 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   __builtin_amdgcn_sched_barrier(0);
   // One stage, its two slices' MFMAs back to back.  Slice 0's run over the
   // reads of slice 1; then every wave waits for its loads of stage it + 1
-  // (issued one stage ago) and its last reads of stage it, so that past the
-  // barrier stage it + 1 is whole and this stage's buffer is free; slice 1's
-  // MFMAs run over the first reads of stage it + 1 and the loads of stage
-  // it + 2.  The scheduling barriers hold one fragment read behind every
-  // second MFMA and one load behind every third: loads issued in a burst
+  // (issued S - 1 stages ago) and its last reads of stage it, so that past
+  // the barrier stage it + 1 is whole and this stage's buffer is free; slice
+  // 1's MFMAs run over the first reads of stage it + 1 and the loads of stage
+  // it + S.  The scheduling barriers hold one fragment read behind every
+  // second MFMA and one load behind every third (with BI = 8): loads issued in a burst
   // stop the MFMAs behind them (spaced every MFMA 169 us on the 60 s clip,
   // second 162, third 158, fourth 158; every second one is 1% faster on the
   // 290 s clip, every fourth 4% slower).
+  int buf = 0;   // it % S
   auto stage = [&](int it, auto load_tag, auto next_tag) {
     constexpr bool kLoad = decltype(load_tag)::value, kNext = decltype(next_tag)::value;
-    char* cur = lds + (it & 1) * kStageB;
-    const char* next = lds + ((it + 1) & 1) * kStageB;
-    const char* next_a = uniform_ptr(base_a + (size_t)(it + 2) * kRowB);
-    const char* next_b = uniform_ptr(base_b + (size_t)(it + 2) * kRowB);
+    char* cur = lds + buf * kStageB;
+    buf = buf + 1 == S ? 0 : buf + 1;
+    const char* next = lds + buf * kStageB;
+    const char* next_a = uniform_ptr(base_a + (size_t)(it + S) * kRowB);
+    const char* next_b = uniform_ptr(base_b + (size_t)(it + S) * kRowB);
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       if (ks == 1 && kNext) {
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        if constexpr (kLoad)   // the loads of the S - 2 stages after it + 1 stay in flight
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((S - 2) * kLoads) : "memory");
+        else
+          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
@@ -234,12 +257,12 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
       for (int g = 0; g < kMfmas; ++g) {
         const int i = g / kBJ, j = g % kBJ;
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[ks][i], fb[ks][j], acc[i][j], 0, 0, 0);
-        if (g % 2 == 0 && g / 2 < kReads && (ks == 0 || kNext)) {
-          read(ks == 0 ? cur : next, ks ^ 1, g / 2);
+        if (g % G::kReadStep == 0 && g / G::kReadStep < kReads && (ks == 0 || kNext)) {
+          read(ks == 0 ? cur : next, ks ^ 1, g / G::kReadStep);
           __builtin_amdgcn_sched_barrier(0);
         }
-        if (ks == 1 && kLoad && g % 3 == 2 && g / 3 < 2 * kLoadsPerWave) {
-          issue_load(cur, next_a, next_b, off_a, off_b, wave, g / 3);
+        if (ks == 1 && kLoad && (g + 1) % G::kLoadStep == 0 && g / G::kLoadStep < kLoads) {
+          issue_load(cur, next_a, next_b, g / G::kLoadStep);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -247,8 +270,8 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
     }
   };
   int it = 0;
-  for (; it + 2 < n_k; ++it) stage(it, std::true_type{}, std::true_type{});
-  if (it + 1 < n_k) stage(it++, std::false_type{}, std::true_type{});
+  for (; it + S < n_k; ++it) stage(it, std::true_type{}, std::true_type{});
+  for (; it + 1 < n_k; ++it) stage(it, std::false_type{}, std::true_type{});
   stage(it, std::false_type{}, std::false_type{});
 
   // Epilogue.  Inverse audio norms of the tile's rows in LDS (-inf past the
@@ -256,7 +279,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   // row 16 (kBI wm + i) + 4(l/16) + e, visual column 16 (kBJ wn + j) + l%16.
   __syncthreads();
   float* inv = reinterpret_cast<float*>(lds);
-  inverse_norms<kTile>(inv, na + c.aud_off, tl.m0, n_a, tid);
+  inverse_norms<G::kTileM>(inv, na + c.aud_off, tl.m0, n_a, tid);
   __syncthreads();
   column_maxima(acc, inv + wm * kBI * 16, lane, tl.n0 + wn * kBJ * 16, n_v, maxkey + c.vis_off);
 }
@@ -460,26 +483,33 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 
 }  // namespace
 
+constexpr int kCUs = 256;
+constexpr double kRoundCost = 5.0;
+
 // One tile per workgroup, of tile_m audio rows by tile_n visual columns.
 static std::vector<GemmTileDev> gate_gemm_tiles(const std::vector<ClipDev>& clips, int tile_m, int tile_n) {
   // A clip's row tiles are cut into bands of at most kBandRows (as even as
-  // possible); per band, column blocks (clip, n0) are dealt to the XCDs in
-  // turn, and an XCD's share lists the band's row tiles of its blocks, block
-  // after block.  A tall clip's audio then passes through each XCD's L2 once
-  // per band and column block rather than once per column block.
+  // possible); a band's tiles, column block after column block, are cut into
+  // eight runs of equal length, one per XCD.  A tall clip's audio then passes
+  // through each XCD's L2 once per band and column block rather than once per
+  // column block, and no XCD gets more tiles than its share: whole column
+  // blocks to each had given some 35 of a 45 s clip's 255 tiles to an XCD's
+  // 32 compute units, a second round (144 us; 87 now).
   constexpr int kBandRows = 8;
   std::vector<std::vector<GemmTileDev>> share(kXcds);
-  int next = 0;
+  int first = 0;   // XCD of the band's first run
   for (size_t s = 0; s < clips.size(); ++s) {
     const ClipDev& c = clips[s];
     const int64_t nv = (int64_t)c.n_frames * c.per_frame;
     if (nv == 0 || c.n_audio == 0) continue;
     const int mb = (int)((c.n_audio + tile_m - 1) / tile_m), nb = (int)((nv + tile_n - 1) / tile_n);
     const int n_band = (mb + kBandRows - 1) / kBandRows;
-    for (int b = 0; b < n_band; ++b) {
-      const int m0 = b * mb / n_band, m1 = (b + 1) * mb / n_band;
-      for (int n = 0; n < nb; ++n, next = (next + 1) % kXcds)
-        for (int m = m0; m < m1; ++m) share[next].push_back({(int32_t)s, m * tile_m, n * tile_n, 0});
+    for (int b = 0; b < n_band; ++b, first = (first + 1) % kXcds) {
+      const int m0 = (int)((int64_t)b * mb / n_band), rows = (int)((int64_t)(b + 1) * mb / n_band) - m0;
+      const int64_t n_tiles = (int64_t)rows * nb;
+      for (int64_t t = 0; t < n_tiles; ++t)
+        share[(first + t * kXcds / n_tiles) % kXcds].push_back(
+            {(int32_t)s, (m0 + (int)(t % rows)) * tile_m, (int)(t / rows) * tile_n, 0});
     }
   }
   size_t rounds = 0;
@@ -493,19 +523,47 @@ static std::vector<GemmTileDev> gate_gemm_tiles(const std::vector<ClipDev>& clip
   return out;
 }
 
-std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips) {
-  return gate_gemm_tiles(clips, kTile, kTile);
+// Rows per tile (32 bi) of a call: the tiles run in rounds of one per compute
+// unit, and a round of tiles of bi blocks costs about bi + kRoundCost (a part
+// is paid whatever the rows: the visual operand's loads and reads, filling
+// the pipeline, the epilogue), so a part-empty round is weighed against
+// smaller tiles.  Measured on 3584-d clips, us with bi = 8 and as chosen:
+// 4 s 68 and 36 (bi 2), 20 s 70 and 35 (2), 30 s 72 and 49 (4), 45 s 87 and 87
+// (8), 60 s 158 and 149 (7), 100 s 412 and 409 (8); a round takes 77 us with
+// bi 8, 73 with 7, 60 with 6, 55 with 5, 48 with 4, 40 with 3 and 33 with 2.
+std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips, int* bi_out) {
+  int best = 8;
+  double best_cost = 0.0;
+  for (int bi = 8; bi >= 2; --bi) {
+    int64_t n = 0;
+    for (const ClipDev& c : clips)
+      n += ((c.n_audio + 32 * bi - 1) / (32 * bi)) * (((int64_t)c.n_frames * c.per_frame + kTileN - 1) / kTileN);
+    const double cost = (double)((n + kCUs - 1) / kCUs) * (bi + kRoundCost);
+    if (bi == 8 || cost < best_cost) {
+      best = bi;
+      best_cost = cost;
+    }
+  }
+  *bi_out = best;
+  return gate_gemm_tiles(clips, 32 * best, kTileN);
 }
 std::vector<GemmTileDev> gate_gemm_any_tiles(const std::vector<ClipDev>& clips) {
   return gate_gemm_tiles(clips, kAnyM, kAnyN);
 }
 
-apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int dim,
+apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int bi, int dim,
                                  const uint16_t* xv, const uint16_t* xa, const double* na, uint32_t* maxkey,
                                  hipStream_t stream) {
   if (n_tiles == 0) return APACK_OK;
-  hipLaunchKernelGGL(k_gate_gemm256, dim3((unsigned)n_tiles), dim3(kWaves * 64), 0, stream, clips, tiles, dim, xv, xa,
-                     na, maxkey);
+  auto kernel = bi == 8   ? k_gate_gemm256<8>
+                : bi == 7 ? k_gate_gemm256<7>
+                : bi == 6 ? k_gate_gemm256<6>
+                : bi == 5 ? k_gate_gemm256<5>
+                : bi == 4 ? k_gate_gemm256<4>
+                : bi == 3 ? k_gate_gemm256<3>
+                          : k_gate_gemm256<2>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)n_tiles), dim3(kWaves * 64), 0, stream, clips, tiles, dim, xv, xa, na,
+                     maxkey);
   return launch_status("k_gate_gemm256");
 }
 

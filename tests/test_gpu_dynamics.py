@@ -361,3 +361,33 @@ def test_gate_gemm_of_any_dim_and_dtype(dim, frames, audio, dtype):
     n = (6 if dtype == "f32" else 1) * (dim // 32 + 1) + 4
     tol = 4.0 * n * 2.0 ** -24 / (d.max() - d.min()) + 2.0 ** -23
     np.testing.assert_allclose(got, want, rtol=0, atol=tol)
+
+
+@pytest.mark.parametrize("audio,visual,dim", [
+    (33, 200, 64),      # 64-row tiles, one K stage (of four in flight)
+    (33, 200, 320),     # five K stages
+    (470, 9000, 320),   # 96 rows
+    (700, 9000, 128),   # 128 rows
+    (470, 17281, 128),  # 160 rows
+    (1125, 9000, 128),  # 192 rows
+    (1500, 9000, 128),  # 224 rows
+    (700, 17281, 192),  # 256 rows
+])
+def test_gate_gemm_tile_heights(audio, visual, dim):
+    """Largest cosines with every height of the 256-column tiles (chosen by
+    how the tiles fill the compute units), with short last tiles and with
+    fewer, as many and more K stages than LDS holds; one token per frame, the
+    frame score is 1 - d_hat with gamma 0."""
+    import paper_2608_08794_amd as A
+    rng = np.random.default_rng(audio + visual)
+    xv, xa = (W.to_bf16_bits(rng.standard_normal((n, dim)).astype(np.float32)) for n in (visual, audio))
+    clip = dict(n_frames=visual, per_frame=1, n_audio=audio, n_query=1, vis_off=0, aud_off=0, qry_off=0)
+    out = A.apack_score_dynamics(to_dev(xv, "bf16"), to_dev(xa, "bf16"), to_dev(xa[:1], "bf16"), [clip],
+                                 {"alignment": "av_cosine", "gamma": 0.0, "r_pre": 1.0})
+    got = out["score"].cpu().numpy().astype(np.float64)
+    d, _ = OD.direct_distance(widen(xv, "bf16"), widen(xa, "bf16"), visual, 1)
+    want = 1.0 - OD.minmax(d)
+    # As above: dim / 32 partial sums and the scaling, each rounded by at most
+    # 2^-24 of |x| |y|, three times over the range of d.
+    tol = 4.0 * (dim // 32 + 4) * 2.0 ** -24 / (d.max() - d.min()) + 2.0 ** -23
+    np.testing.assert_allclose(got, want, rtol=0, atol=tol)
