@@ -19,12 +19,12 @@
 //                continuity smoothing and cuts, Eq. 3 segment scores, frame
 //                scores, Eq. 4 segment budgets and frame budgets (capped
 //                largest remainder), anchors and output offsets
-//   k_gram       fp64 Gram of the tokens of every anchor frame (fp64 MFMA)
+//   k_gram_dedup fp64 Gram of the tokens of every anchor frame (fp64 MFMA),
+//                and beside it the cosine of every token of the other
+//                frames to its anchor's token, one wave per token
 //   k_dafps      per anchor frame: cosines from the Gram and its diagonal,
-//                then density-aware farthest-point sampling in one wave
-//   k_dedup_sim, k_dedup_pick  one wave per token, then one workgroup per
-//                non-anchor frame: keep the positions least
-//                similar to the anchor
+//                then density-aware farthest-point sampling in one wave; per
+//                other frame: the positions least similar to the anchor
 //
 // Every discrete decision (gate, cuts, budgets, DA-FPS argmax, dedup ranks)
 // is taken in fp64, as in the oracle.  The gate GEMM accumulates in fp32.
@@ -854,9 +854,8 @@ __global__ __launch_bounds__(kPlanBlk) void k_plan(ClipDev* __restrict__ clips, 
 // element is widened under the 64 cycles of the MFMA before it; with single
 // tiles, all of a step widened ahead of its MFMAs and every value masked for
 // the last step, the vector ALU took longer than the matrix core.  Spatial
-// Gram of a 60 s clip 392 -> 268 us (its MFMAs alone take 154), anchor Grams
-// of a 60 s clip 46 -> 34, of a 20 s clip at dim 2048 18.5 -> 14.5, of a
-// 290 s clip 117 -> 103.
+// Gram of a 60 s clip 392 -> 270 us (its MFMAs alone take 154), anchor Grams
+// of a 290 s clip 117 -> 100.
 // MFMA operands: lane l supplies A[l % 16][k = l / 16] and B[k = l / 16][l % 16];
 // accumulator element e of lane l is D[4e + l / 16][l % 16].  Each lane
 // loads 8 consecutive elements of its row and feeds them to 8 MFMAs, lane
@@ -870,6 +869,8 @@ constexpr int kGramSplit = 8;     // K slices (waves) per workgroup of the ancho
 constexpr int kSpatialSplit = 4;  // and of the spatial Gram
 constexpr int64_t kSpatialBlocks = 1 << 20;  // workgroups of the spatial Gram at most (a multiple of 8)
 constexpr int kGramBlocks = 512;  // workgroups of the anchor Gram at most: two per CU
+constexpr int kFuseFrames = 192;  // frames up to which the cosines share the Grams' launch
+constexpr int64_t kDedupBlocks = 1 << 20;  // workgroups of the cosines beside it at most
 
 // Tile block (bi, bj), bj >= bi, number t of the row-major upper triangle of
 // an nb x nb grid of blocks.
@@ -1000,31 +1001,36 @@ __device__ __forceinline__ void anchor_grams(const ClipDev* __restrict__ clips, 
   const int nsteps = (dim + 31) / 32;
   const int per = (nsteps + kGramSplit - 1) / kGramSplit;
   const int s_begin = min(nsteps, wave * per), s_end = min(nsteps, s_begin + per);
-  // Anchors go to XCDs round-robin (workgroup b runs on XCD b % 8), so an
-  // anchor's rows are fetched into one L2; the XCD's slots share its
-  // anchors' blocks in turn.  Every workgroup walks the same anchor sequence.
-  const int xcd = blk & 7, slot = blk >> 3, nslot = n_blk >> 3;
-  int c = 0;
-  int64_t seg_before = 0;  // anchors of clips [0, c)
-  int64_t jbase = 0;       // blocks of this XCD's earlier anchors
-  for (int64_t an = xcd;; an += 8) {
-    while (c < n_clips) {
-      const int64_t ns = clips[c].n_frames > 0 ? clips[c].n_seg : 0;
-      if (an < seg_before + ns) break;
-      seg_before += ns;
-      ++c;
-    }
-    if (c >= n_clips) return;
+  // Items of each clip in turn, workgroup blk taking every n_blk-th (n_blk is
+  // a multiple of 8).  Eight anchors at a time are interleaved, so that each
+  // one's blocks run on one XCD (workgroup b runs on XCD b % 8) and share
+  // its rows in that L2; the blocks of the last few anchors are spread over
+  // all of them (with whole anchors dealt to XCDs a clip of two had used two
+  // of the eight, and one of nine had given the first XCD two: 10 s clip
+  // 36 -> 14 us, 20 s 23 -> 14, 60 s 33 -> 22.5, 290 s 124 -> 114).
+  int64_t base = 0;
+  for (int c = 0; c < n_clips; ++c) {
     const ClipDev cc = clips[c];
+    if (cc.n_frames == 0) continue;
     const int P = cc.per_frame, nb = (P + N * kGramTile - 1) / (N * kGramTile), blocks = nb * (nb + 1) / 2;
-    const int f = anchors[cc.frame_off + (an - seg_before)];
-    const int64_t j0 = jbase + ((slot - jbase % nslot) % nslot + nslot) % nslot;
-    const int64_t jend = jbase + blocks;
-    jbase = jend;
-    if (plan[cc.frame_off + f].budget == 0) continue;  // the same for the whole workgroup
-    for (int64_t jj = j0; jj < jend; jj += nslot) {
+    const int64_t items = (int64_t)cc.n_seg * blocks, whole = (int64_t)(cc.n_seg / 8) * 8 * blocks;
+    const int64_t q0 = ((blk - base % n_blk) % n_blk + n_blk) % n_blk;
+    base += items;
+    for (int64_t q = q0; q < items; q += n_blk) {
+      int64_t an;
+      int t;
+      if (q < whole) {
+        const int64_t r = q % (8 * blocks);
+        an = q / (8 * blocks) * 8 + (r & 7);
+        t = (int)(r >> 3);
+      } else {
+        an = whole / blocks + (q - whole) / blocks;
+        t = (int)((q - whole) % blocks);
+      }
+      const int f = anchors[cc.frame_off + an];
+      if (plan[cc.frame_off + f].budget == 0) continue;  // the same for the whole workgroup
       int bi, bj;
-      upper_block((int)(jj - (jend - blocks)), nb, bi, bj);
+      upper_block(t, nb, bi, bj);
       const T* x = xv + (cc.vis_off + (int64_t)f * P) * dim;
       const T* row[2 * N];
 #pragma unroll
@@ -1066,25 +1072,86 @@ __device__ __forceinline__ void anchor_grams(const ClipDev* __restrict__ clips, 
   }
 }
 
-// Blocks of 2 x 2 tiles where single tiles would make more than two rounds
-// of the grid; fewer items than that leave compute units idle, so a few
-// anchors go tile by tile (120 against 360 items for the 8 anchors of a
-// 60 s clip: 38 us in blocks).
+// Non-anchor frames: cosine of token p of frame f with token p of its
+// anchor, one wave per position, written to sim at the token's row.  The dot
+// product and both squared norms are summed the same way, so a position that
+// repeats the anchor's token has cosine exactly 1.  Block b covers WAVES
+// positions of one frame.
+template <class T, int WAVES>
+__device__ __forceinline__ void dedup_cosines(const ClipDev* __restrict__ clips, const FrameDev* __restrict__ frames,
+                                              const FramePlanDev* __restrict__ plan, int dim,
+                                              const T* __restrict__ xv, double* __restrict__ sim, int64_t b,
+                                              int per_frame_blocks) {
+  const int64_t item = b / per_frame_blocks;
+  const FrameDev fr = frames[item];
+  const ClipDev c = clips[fr.clip];
+  const FramePlanDev fp = plan[c.frame_off + fr.f];
+  if (fp.is_anchor || fp.budget == 0) return;
+  const int P = c.per_frame;
+  const int lane = threadIdx.x & 63;
+  const int p = (int)(b - item * per_frame_blocks) * WAVES + (threadIdx.x >> 6);
+  if (p >= P) return;
+  const int64_t rowf = c.vis_off + (int64_t)fr.f * P + p, rowa = c.vis_off + (int64_t)fp.anchor * P + p;
+  const T* x = xv + rowf * dim;
+  const T* y = xv + rowa * dim;
+  double xy = 0.0, xx = 0.0, yy = 0.0, o[8], q[8];
+#pragma unroll 4
+  for (int d = lane * 8; d < dim; d += 64 * 8) {
+    load8(x + d, o);
+    load8(y + d, q);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      xy = fma(o[e], q[e], xy);
+      xx = fma(o[e], o[e], xx);
+      yy = fma(q[e], q[e], yy);
+    }
+  }
+  xy = wave_sum(xy);
+  xx = wave_sum(xx);
+  yy = wave_sum(yy);
+  if (lane == 0) sim[rowf - c.vis_off + c.token_off] = cos_from(xy, xx, yy);
+}
+
+// Anchor Grams (the first gram_blocks workgroups) and, up to kFuseFrames
+// frames, the non-anchor frames' cosines (the rest) in one launch: a few
+// anchors' Grams leave compute units idle and are bound by the fp64 matrix
+// cores, the cosines by memory.  More frames fill the chip with either, and
+// the cosines then do better at the higher occupancy of a kernel of their
+// own (in one launch and in two: 20 frames 16.7 and 21.7 us, 40 frames 20.6
+// and 25.9, 120 frames 46.3 and 50.2, 180 frames 66.6 and 70.2, 240 frames
+// 86.9 and 83.4, 580 frames 255 and 262, 3700 frames 1.67 and 1.45 ms).
+// Grams go in blocks of 2 x 2 tiles where single tiles would make more than
+// two rounds of the grid; fewer items than that leave compute units idle, so
+// a few anchors go tile by tile (60 s clip 34 us against 38 in blocks).
 template <class T>
-__global__ __launch_bounds__(kGramSplit * 64) void k_gram(const ClipDev* __restrict__ clips, int n_clips,
-                                                          const int32_t* __restrict__ anchors,
-                                                          const FramePlanDev* __restrict__ plan, int dim,
-                                                          const T* __restrict__ xv, double* __restrict__ gram) {
+__global__ __launch_bounds__(kGramSplit * 64, 4) void k_gram_dedup(
+    const ClipDev* __restrict__ clips, int n_clips, const FrameDev* __restrict__ frames, int64_t n_frames,
+    const int32_t* __restrict__ anchors, const FramePlanDev* __restrict__ plan, int dim, const T* __restrict__ xv,
+    double* __restrict__ gram, double* __restrict__ sim, int gram_blocks, int per_frame_blocks) {
   __shared__ double red[kGramSplit - 1][16 * 64];
+  if (blockIdx.x >= (unsigned)gram_blocks) {
+    for (int64_t b = (int64_t)blockIdx.x - gram_blocks; b < n_frames * per_frame_blocks; b += gridDim.x - gram_blocks)
+      dedup_cosines<T, kGramSplit>(clips, frames, plan, dim, xv, sim, b, per_frame_blocks);
+    return;
+  }
   int64_t tiles = 0;
   for (int c = 0; c < n_clips; ++c) {
     const int nt = (clips[c].per_frame + kGramTile - 1) / kGramTile;
     tiles += clips[c].n_frames > 0 ? (int64_t)clips[c].n_seg * (nt * (nt + 1) / 2) : 0;
   }
-  if (tiles <= 2 * (int64_t)gridDim.x)
-    anchor_grams<T, 1>(clips, n_clips, anchors, plan, dim, xv, gram, red, blockIdx.x, gridDim.x);
+  if (tiles <= 2 * (int64_t)gram_blocks)
+    anchor_grams<T, 1>(clips, n_clips, anchors, plan, dim, xv, gram, red, blockIdx.x, gram_blocks);
   else
-    anchor_grams<T, 2>(clips, n_clips, anchors, plan, dim, xv, gram, red, blockIdx.x, gridDim.x);
+    anchor_grams<T, 2>(clips, n_clips, anchors, plan, dim, xv, gram, red, blockIdx.x, gram_blocks);
+}
+
+template <class T>
+__global__ __launch_bounds__(kBlk) void k_dedup(const ClipDev* __restrict__ clips, const FrameDev* __restrict__ frames,
+                                                int64_t n_frames, const FramePlanDev* __restrict__ plan, int dim,
+                                                const T* __restrict__ xv, double* __restrict__ sim,
+                                                int per_frame_blocks) {
+  for (int64_t b = blockIdx.x; b < n_frames * per_frame_blocks; b += gridDim.x)
+    dedup_cosines<T, kBlk / 64>(clips, frames, plan, dim, xv, sim, b, per_frame_blocks);
 }
 
 // ---------------------------------------------------------------------------
@@ -1513,16 +1580,52 @@ __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __re
 // it is read.
 constexpr int kDafpsThreads = 2 * kMaxPerFrame;
 
+// Non-anchor frame: the k positions least similar to the anchor token at the
+// same position, lower position first on ties, in ascending order.  Two
+// threads per position, each ranking it against half of the frame's.
+__device__ __forceinline__ void dedup_pick(const double* __restrict__ simg, double* lds, int P, int k,
+                                           int32_t* __restrict__ kept, int64_t out, int64_t base) {
+  double* sim = lds;                                               // one per position, and one of padding
+  int* wcount = reinterpret_cast<int*>(lds + kMaxPerFrame + 2);   // one per wave
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int p = tid >> 1, h = tid & 1;
+  const int half = (P + 1) / 2;
+  if (tid < 2 * half) sim[tid] = tid < P ? simg[tid] : INFINITY;
+  __syncthreads();
+  const double mine = p < P ? sim[p] : 0.0;
+  const int q0 = h * half;
+  int rank = 0;
+#pragma unroll 8
+  for (int i = 0; i < half; ++i) {
+    const int q = q0 + i;
+    const double o = sim[q];   // an odd P's last entry is +inf
+    rank += (int)((o < mine) | ((o == mine) & (q < p)));
+  }
+  rank += __shfl_xor(rank, 1);
+  const bool kp = p < P && rank < k && h == 0;
+  const uint64_t bal = __ballot(kp);
+  if (lane == 0) wcount[wave] = __popcll(bal);
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) out += wcount[w];
+  if (kp) kept[out + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)(base + p);
+}
+
 __global__ __launch_bounds__(kDafpsThreads) void k_dafps(const ClipDev* __restrict__ clips,
                                                          const FrameDev* __restrict__ frames,
                                                          const FramePlanDev* __restrict__ plan, DynParamsDev prm,
-                                                         const double* __restrict__ gram, int32_t* __restrict__ kept) {
+                                                         const double* __restrict__ gram,
+                                                         const double* __restrict__ sim, int32_t* __restrict__ kept) {
   __shared__ __attribute__((aligned(16))) double lds[kDafpsLds];
   const FrameDev fr = frames[blockIdx.x];
   const ClipDev c = clips[fr.clip];
   const int64_t frame = c.frame_off + fr.f;
   const FramePlanDev fp = plan[frame];
-  if (!fp.is_anchor || fp.budget == 0) return;
+  if (fp.budget == 0) return;
+  if (!fp.is_anchor) {
+    const int64_t row0 = (int64_t)fr.f * c.per_frame;
+    dedup_pick(sim + c.token_off + row0, lds, c.per_frame, fp.budget, kept, fp.out_off, c.vis_off + row0);
+    return;
+  }
   const int P = c.per_frame, tid = threadIdx.x, i = tid >> 1, h = tid & 1;
   const int k = min(fp.budget, P);
   const double* S = gram + c.gram_off + (int64_t)fr.f * P * P;
@@ -1635,82 +1738,6 @@ __global__ __launch_bounds__(kDafpsThreads) void k_dafps(const ClipDev* __restri
   else dafps_pick<4>(L, S, P, k, prm.power, tid, kept, out, base);
 }
 
-// ---------------------------------------------------------------------------
-// Non-anchor frames: keep the k_f positions least similar to the anchor
-// token at the same position (lower position first on ties).
-// ---------------------------------------------------------------------------
-template <class T>
-__global__ __launch_bounds__(kBlk) void k_dedup_sim(const ClipDev* __restrict__ clips,
-                                                    const FrameDev* __restrict__ frames,
-                                                    const FramePlanDev* __restrict__ plan, int dim,
-                                                    const T* __restrict__ xv, double* __restrict__ sim) {
-  // One wave per position: cosine of token p of frame f with token p of its
-  // anchor, written to sim at the token's row.  The dot product and both
-  // squared norms are summed the same way, so a position that repeats the
-  // anchor's token has cosine exactly 1.
-  const FrameDev fr = frames[blockIdx.x];
-  const ClipDev c = clips[fr.clip];
-  const FramePlanDev fp = plan[c.frame_off + fr.f];
-  if (fp.is_anchor || fp.budget == 0) return;
-  const int P = c.per_frame;
-  const int lane = threadIdx.x & 63;
-  const int p = blockIdx.y * (kBlk / 64) + (threadIdx.x >> 6);
-  if (p >= P) return;
-  const int64_t rowf = c.vis_off + (int64_t)fr.f * P + p, rowa = c.vis_off + (int64_t)fp.anchor * P + p;
-  const T* x = xv + rowf * dim;
-  const T* y = xv + rowa * dim;
-  double xy = 0.0, xx = 0.0, yy = 0.0, o[8], q[8];
-#pragma unroll 4
-  for (int d = lane * 8; d < dim; d += 64 * 8) {
-    load8(x + d, o);
-    load8(y + d, q);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      xy = fma(o[e], q[e], xy);
-      xx = fma(o[e], o[e], xx);
-      yy = fma(q[e], q[e], yy);
-    }
-  }
-  xy = wave_sum(xy);
-  xx = wave_sum(xx);
-  yy = wave_sum(yy);
-  if (lane == 0) sim[rowf - c.vis_off + c.token_off] = cos_from(xy, xx, yy);
-}
-
-__global__ __launch_bounds__(kBlk) void k_dedup_pick(const ClipDev* __restrict__ clips,
-                                                     const FrameDev* __restrict__ frames,
-                                                     const FramePlanDev* __restrict__ plan,
-                                                     const double* __restrict__ simg, int32_t* __restrict__ kept) {
-  // The k_f positions least similar to the anchor, lower position first on
-  // ties, written in ascending order.
-  __shared__ double sim[kMaxPerFrame];
-  __shared__ int wcount[kBlk / 64];
-  const FrameDev fr = frames[blockIdx.x];
-  const ClipDev c = clips[fr.clip];
-  const FramePlanDev fp = plan[c.frame_off + fr.f];
-  if (fp.is_anchor || fp.budget == 0) return;
-  const int P = c.per_frame;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t rowf = c.vis_off + (int64_t)fr.f * P;
-  const double* sg = simg + c.token_off + (int64_t)fr.f * P;
-  for (int q = threadIdx.x; q < P; q += kBlk) sim[q] = sg[q];
-  __syncthreads();
-  const int p = threadIdx.x;
-  bool kp = false;
-  if (p < P) {
-    int rank = 0;
-    for (int q = 0; q < P; ++q)
-      if (sim[q] < sim[p] || (sim[q] == sim[p] && q < p)) ++rank;
-    kp = rank < fp.budget;
-  }
-  const uint64_t bal = __ballot(kp);
-  if (lane == 0) wcount[wave] = __popcll(bal);
-  __syncthreads();
-  int64_t pos = fp.out_off;
-  for (int w = 0; w < wave; ++w) pos += wcount[w];
-  if (kp) kept[pos + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)(rowf + p);
-}
-
 template <class T>
 apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& prm, int dim, const T* xv,
                       const T* xa, const T* xq, float* frame_cka, float* frame_score, int32_t* frame_budget,
@@ -1767,19 +1794,21 @@ apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& 
                      segment_id);
   if ((st = launch_status("k_plan")) != APACK_OK) return st;
   if (nf > 0) {
-    if (pl.gram_items > 0) {
-      const unsigned gb = (unsigned)std::min<int64_t>((pl.gram_items + 7) / 8 * 8, kGramBlocks);
-      hipLaunchKernelGGL(k_gram<T>, dim3(gb), dim3(kGramSplit * 64), 0, s, dp.clips, nc, dp.anchors, dp.plan, dim,
-                         xv, dp.gram);
+    const int gb = (int)std::min<int64_t>((pl.gram_items + 7) / 8 * 8, kGramBlocks);
+    const bool fuse = nf <= kFuseFrames;
+    const int waves = fuse ? kGramSplit : kBlk / 64, pb = (pl.max_per_frame + waves - 1) / waves;
+    const unsigned db = (unsigned)std::min<int64_t>((int64_t)nf * pb, kDedupBlocks);
+    hipLaunchKernelGGL(k_gram_dedup<T>, dim3(fuse ? gb + db : gb), dim3(kGramSplit * 64), 0, s, dp.clips, nc, dp.frames,
+                       (int64_t)nf, dp.anchors, dp.plan, dim, xv, dp.gram, dp.sim, gb, pb);
+    if ((st = launch_status("k_gram_dedup")) != APACK_OK) return st;
+    if (!fuse) {
+      hipLaunchKernelGGL(k_dedup<T>, dim3(db), dim3(kBlk), 0, s, dp.clips, dp.frames, (int64_t)nf, dp.plan, dim, xv,
+                         dp.sim, pb);
+      if ((st = launch_status("k_dedup")) != APACK_OK) return st;
     }
-    if ((st = launch_status("k_gram")) != APACK_OK) return st;
-    hipLaunchKernelGGL(k_dafps, dim3(nf), dim3(kDafpsThreads), 0, s, dp.clips, dp.frames, dp.plan, prm, dp.gram, kept);
+    hipLaunchKernelGGL(k_dafps, dim3(nf), dim3(kDafpsThreads), 0, s, dp.clips, dp.frames, dp.plan, prm, dp.gram, dp.sim,
+                       kept);
     if ((st = launch_status("k_dafps")) != APACK_OK) return st;
-    hipLaunchKernelGGL(k_dedup_sim<T>, dim3(nf, (pl.max_per_frame + kBlk / 64 - 1) / (kBlk / 64)), dim3(kBlk), 0, s,
-                       dp.clips, dp.frames, dp.plan, dim, xv, dp.sim);
-    if ((st = launch_status("k_dedup_sim")) != APACK_OK) return st;
-    hipLaunchKernelGGL(k_dedup_pick, dim3(nf), dim3(kBlk), 0, s, dp.clips, dp.frames, dp.plan, dp.sim, kept);
-    if ((st = launch_status("k_dedup_pick")) != APACK_OK) return st;
   }
   return APACK_OK;
 }
