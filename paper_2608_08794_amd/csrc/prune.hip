@@ -19,6 +19,7 @@
 //                then a fixed-order cross-wave sum through LDS.  The last
 //                workgroup of each key chunk sums the per-group partials
 //                into I_j and counts its first radix digit.
+// Calls with few query rows run k_few_logits and k_few_colsum instead (below).
 // The remaining radix digits, the per-modality top-k and the ordered kept
 // list are formed by the kernels of select.hip.
 #include <cfloat>
@@ -339,6 +340,54 @@ __device__ __forceinline__ TileDev inline_tile(const SeqDev& sq, int b) {
   return t;
 }
 
+// What the first score kernel does for a call with descriptors by value: the
+// chunk's mask and (once per chunk) tags from the spans, and the arrays that
+// the later kernels read, spread over the workgroups.
+template <int NT>
+__device__ __forceinline__ void inline_setup(const InlineCall& in, const TileDev& tl, const SeqDev& sq, SeqDev* seqs,
+                                             TileDev* tiles, FTileDev* ftiles, uint8_t* tg, uint32_t* ctr,
+                                             int64_t key_begin, int64_t key_end, int n_mask, float* lmask) {
+  const int tid = threadIdx.x;
+  const bool write_tags = tl.g == 0 && tl.rg == 0;
+  for (int i = tid; i < n_mask; i += NT) {
+    const int64_t r = key_begin + i;
+    int tag = 0;
+    for (int s = 0; s < in.n_spans; ++s)
+      if (r >= in.spans[s].begin && r < in.spans[s].end) tag = in.spans[s].tag;
+    lmask[i] = r < key_end && tag != 0 ? 0.0f : -INFINITY;
+    if (write_tags && r < key_end) tg[r] = (uint8_t)tag;
+  }
+  const int stride = (int)gridDim.x * NT, t = (int)blockIdx.x * NT + tid;
+  for (int i = t; i < in.n_ctr; i += stride) ctr[i] = 0;
+  for (int i = t; i < sq.n_ftiles; i += stride) ftiles[i] = FTileDev{0, i};
+  if (tid == 0) tiles[blockIdx.x] = tl;
+  if (blockIdx.x == 0 && tid < (int)(sizeof(SeqDev) / 4))
+    reinterpret_cast<uint32_t*>(seqs)[tid] = reinterpret_cast<const uint32_t*>(&in.seq)[tid];
+}
+
+// The chunk's mask from uploaded tags: read in batches of 8 per thread, all
+// in flight together (the index is clamped to a valid row; rows past the
+// chunk get -inf).
+template <int NT>
+__device__ __forceinline__ void load_mask(const uint8_t* tg, int64_t key_begin, int64_t key_end, int n_mask,
+                                          float* lmask) {
+  constexpr int kB = 8;
+  const int tid = threadIdx.x;
+  for (int b0 = 0; b0 < n_mask; b0 += kB * NT) {
+    uint8_t t[kB];
+#pragma unroll
+    for (int j = 0; j < kB; ++j) {
+      const int64_t r = key_begin + b0 + tid + j * NT;
+      t[j] = tg[r < key_end ? r : key_end - 1];
+    }
+#pragma unroll
+    for (int j = 0; j < kB; ++j) {
+      const int i = b0 + tid + j * NT;
+      if (i < n_mask) lmask[i] = (key_begin + i < key_end && t[j] != 0) ? 0.0f : -INFINITY;
+    }
+  }
+}
+
 template <class T, int D, int NW, int S>
 __global__ __launch_bounds__(NW * kWave) void k_rowstats(const InlineCall in, SeqDev* __restrict__ seqs,
                                                          TileDev* __restrict__ tiles,
@@ -388,44 +437,10 @@ __global__ __launch_bounds__(NW * kWave) void k_rowstats(const InlineCall in, Se
   if (active) load_q<T, D>(qfr, q, q_hs, sq, tl.g, n_rep, row0, lane);
   uint8_t* tg = tags + sq.tag_off;
 
-  if (inl) {
-    // Tags from the spans, written once per chunk; then what the later
-    // kernels read, spread over the workgroups.
-    const bool write_tags = tl.g == 0 && tl.rg == 0;
-    const int n_mask = n_tiles * kKeyTile;
-    for (int i = tid; i < n_mask; i += NW * kWave) {
-      const int64_t r = key_begin + i;
-      int tag = 0;
-      for (int s = 0; s < in.n_spans; ++s)
-        if (r >= in.spans[s].begin && r < in.spans[s].end) tag = in.spans[s].tag;
-      lmask[i] = r < key_end && tag != 0 ? 0.0f : -INFINITY;
-      if (write_tags && r < key_end) tg[r] = (uint8_t)tag;
-    }
-    const int stride = (int)gridDim.x * NW * kWave, t = (int)blockIdx.x * NW * kWave + tid;
-    for (int i = t; i < in.n_ctr; i += stride) ctr[i] = 0;
-    for (int i = t; i < sq.n_ftiles; i += stride) ftiles[i] = FTileDev{0, i};
-    if (tid == 0) tiles[blockIdx.x] = tl;
-    if (blockIdx.x == 0 && tid < (int)(sizeof(SeqDev) / 4))
-      reinterpret_cast<uint32_t*>(seqs)[tid] = reinterpret_cast<const uint32_t*>(&in.seq)[tid];
-  } else {
-    // Tags are read in batches of 8 per thread, all in flight together (the
-    // index is clamped to a valid row; rows past the chunk get -inf).
-    constexpr int kB = 8;
-    const int n_mask = n_tiles * kKeyTile;
-    for (int b0 = 0; b0 < n_mask; b0 += kB * NW * kWave) {
-      uint8_t t[kB];
-#pragma unroll
-      for (int j = 0; j < kB; ++j) {
-        const int64_t r = key_begin + b0 + tid + j * NW * kWave;
-        t[j] = tg[r < key_end ? r : key_end - 1];
-      }
-#pragma unroll
-      for (int j = 0; j < kB; ++j) {
-        const int i = b0 + tid + j * NW * kWave;
-        if (i < n_mask) lmask[i] = (key_begin + i < key_end && t[j] != 0) ? 0.0f : -INFINITY;
-      }
-    }
-  }
+  if (inl)
+    inline_setup<NW * kWave>(in, tl, sq, seqs, tiles, ftiles, tg, ctr, key_begin, key_end, n_tiles * kKeyTile, lmask);
+  else
+    load_mask<NW * kWave>(tg, key_begin, key_end, n_tiles * kKeyTile, lmask);
   // One pass over the chunk's key tiles: with exact = false each lane sums
   // against its fixed reference (row_update_ref), with exact = true it keeps
   // the online maximum (row_update).  The first is taken; the second redoes
@@ -845,6 +860,238 @@ __global__ __launch_bounds__(NW * kWave) void k_colsum(SeqDev* __restrict__ seqs
 }
 
 // ---------------------------------------------------------------------------
+// Few query rows (bf16, at most 16 per key head: the last query token of
+// grouped heads).  The general passes carry 64 rows per wave, so with 7 real
+// rows most of their arithmetic is padding, one wave of a workgroup has rows
+// at all, and K is read twice.  Here pass 1 streams K once from global memory
+// into 16x16x32 MFMA operands (no LDS), every wave its own keys, and stores
+// the masked logits in fp32: hkv * rows * 4 bytes per key against
+// hkv * D * 2 of K (28 against 256 per head with 7 rows).  Pass 2 is a sum
+// over those.  Bound by the read of K.  Mean of 14 prunes of 94k down to 24k
+// rows (28 heads over 4, one query token): 25.7 us to 14.5 for pass 1 and
+// 28.7 to 13.6 for pass 2.  Both passes were faster in every form tried, from
+// 1280 keys of 8 heads over 2 at D = 64 (22.6 us to 16.4) to 16 rows for each
+// of 64 key heads over 21.5k keys (379 to 149), so the limit of 16 rows is
+// the MFMA tile's.
+// ---------------------------------------------------------------------------
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+constexpr int kFewWaves = 4;
+constexpr int kFewBlocks = 4;                             // 16-key blocks a wave has in flight
+constexpr int kFewKeys = kFewWaves * kFewBlocks * 16;     // keys of one step of a workgroup
+constexpr int kFewCols = 256;                             // keys per workgroup of pass 2
+static_assert(kRowTile % kFewCols == 0 && kMaxChunk % kKeyTile == 0, "pass 2 cuts row tiles evenly");
+
+template <int D>
+__global__ __launch_bounds__(kFewWaves * kWave) void k_few_logits(
+    const InlineCall in, SeqDev* __restrict__ seqs, TileDev* __restrict__ tiles, FTileDev* __restrict__ ftiles,
+    uint8_t* __restrict__ tags, uint32_t* __restrict__ ctr, const bf16_t* __restrict__ q, int64_t q_hs,
+    const bf16_t* __restrict__ k, int64_t k_hs, int n_rep, float scale_log2, float2* __restrict__ stats,
+    float* __restrict__ logits, uint32_t* __restrict__ zero, int64_t zero_n) {
+  constexpr int KS = D / 32, NT = kFewWaves * kWave;
+  __shared__ __attribute__((aligned(16))) float lmask[kMaxChunk];
+  __shared__ float2 wstat[kFewWaves][kFewRows];
+  const bool inl = in.n_spans >= 0;
+  const TileDev tl = inl ? inline_tile(in.seq, blockIdx.x) : tiles[blockIdx.x];
+  const SeqDev sq = inl ? in.seq : seqs[tl.seq];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rows = n_rep * sq.q_len;
+  const int64_t key_begin = (int64_t)tl.chunk * sq.chunk;
+  int64_t key_end = key_begin + sq.chunk;
+  if (key_end > sq.n_tokens) key_end = sq.n_tokens;
+  const int n_keys = (int)(key_end - key_begin), n_mask = (n_keys + kKeyTile - 1) / kKeyTile * kKeyTile;
+
+  // Lane l holds key (l % 16) of a block, elements 32 ks + 8 (l / 16) .. + 7
+  // of it (rows past the chunk repeat its last row; they are masked).
+  const bf16_t* kb = k + (int64_t)tl.g * k_hs + (sq.tok_off + key_begin) * D + 8 * (lane >> 4);
+  bf16x8 nxt[kFewBlocks][KS];
+  auto load = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < kFewBlocks; ++u) {
+      const bf16_t* p = kb + (int64_t)min(i0 + 16 * u + (lane & 15), n_keys - 1) * D;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) nxt[u][ks] = *reinterpret_cast<const bf16x8*>(p + 32 * ks);
+    }
+  };
+  const int first = wave * kFewBlocks * 16;
+  load(first);
+  // Query row l % 16 of the head group, the same elements; padding rows are 0.
+  bf16x8 qf[KS];
+  {
+    const int rho = lane & 15, rc = min(rho, rows - 1);
+    const bf16_t* p = q + (int64_t)(tl.g * n_rep + rc / sq.q_len) * q_hs + (sq.q_off + rc % sq.q_len) * (int64_t)D +
+                      8 * (lane >> 4);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8*>(p + 32 * ks);
+    if (rho >= rows) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) qf[ks] = bf16x8{};
+    }
+  }
+  {
+    const int64_t per = (zero_n + gridDim.x - 1) / gridDim.x;
+    const int64_t z0 = (int64_t)blockIdx.x * per, z1 = min(zero_n, z0 + per);
+    for (int64_t i = z0 + tid; i < z1; i += NT) zero[i] = 0;
+  }
+  if (inl)
+    inline_setup<NT>(in, tl, sq, seqs, tiles, ftiles, tags + sq.tag_off, ctr, key_begin, key_end, n_mask, lmask);
+  else
+    load_mask<NT>(tags + sq.tag_off, key_begin, key_end, n_mask, lmask);
+  __syncthreads();
+
+  // Stored logits of this group's row l % 16: keys 4 (l / 16) .. + 3 of each
+  // block (the row length is a multiple of 16).
+  const int64_t np = (sq.n_tokens + 15) / 16 * 16;
+  float* out = logits + sq.logits_off + ((int64_t)tl.g * rows + (lane & 15)) * np + key_begin;
+  const bool store = (lane & 15) < rows;
+  float m_run = -FLT_MAX, s_run = 0.f;
+  for (int i0 = first; i0 < n_keys; i0 += kFewKeys) {
+    f32x16 x;
+    f32x4v acc[kFewBlocks];
+#pragma unroll
+    for (int u = 0; u < kFewBlocks; ++u) {
+      acc[u] = f32x4v{};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nxt[u][ks], qf[ks], acc[u], 0, 0, 0);
+    }
+    if (i0 + kFewKeys < n_keys) load(i0 + kFewKeys);
+#pragma unroll
+    for (int u = 0; u < kFewBlocks; ++u) {
+      const int i = i0 + 16 * u + 4 * (lane >> 4);
+      const bool in_mask = i < n_mask;   // a whole block lies below the mask's end or past it
+      const f32x4v mk = in_mask ? *reinterpret_cast<const f32x4v*>(lmask + i)
+                                : f32x4v{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+      f32x4v v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = acc[u][e] + mk[e];
+        x[4 * u + e] = v[e];
+      }
+      if (store && in_mask && key_begin + i < np) *reinterpret_cast<f32x4v*>(out + i) = v;
+    }
+    row_update(x, scale_log2, m_run, s_run);
+  }
+  // The chunk's (max, sum) of each row: over the four lanes that share it,
+  // then over the waves in order.
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {
+    const float mo = __shfl_xor(m_run, off), so = __shfl_xor(s_run, off);
+    const float mm = fmaxf(m_run, mo);
+    s_run = s_run * fast_exp2(m_run - mm) + so * fast_exp2(mo - mm);
+    m_run = mm;
+  }
+  if (lane < kFewRows) wstat[wave][lane] = make_float2(m_run, s_run);
+  __syncthreads();
+  if (tid < rows) {
+    float m = wstat[0][tid].x, s = wstat[0][tid].y;
+#pragma unroll
+    for (int w = 1; w < kFewWaves; ++w) merge(m, s, wstat[w][tid].x, wstat[w][tid].y);
+    stats[sq.stats_off + ((int64_t)tl.g * sq.n_chunks + tl.chunk) * sq.rows_pad + tid] = make_float2(m, s);
+  }
+}
+
+// Pass 2 over the stored logits: a quarter row tile (256 keys) per workgroup,
+// each wave a share of the rows of all key heads, four keys per lane.  Every
+// workgroup first merges the chunks' partials of every row (a few threads per
+// row, in a fixed order).  The last workgroup of a sequence picks the first
+// radix digit's bins.
+__global__ __launch_bounds__(kFewWaves * kWave) void k_few_colsum(SeqDev* __restrict__ seqs,
+                                                                  const FTileDev* __restrict__ ftiles,
+                                                                  const uint8_t* __restrict__ tags, int n_rep, int hkv,
+                                                                  float scale_log2, const float2* __restrict__ stats,
+                                                                  const float* __restrict__ logits,
+                                                                  float* __restrict__ scores,
+                                                                  uint32_t* __restrict__ hist,
+                                                                  uint32_t* __restrict__ ctr) {
+  constexpr int NT = kFewWaves * kWave, kPer = kRowTile / kFewCols;
+  __shared__ float lb[kFewTotal];
+  __shared__ float red[kFewWaves][kFewCols];
+  __shared__ uint32_t lh[2 * kRadixBins];
+  const FTileDev ft = ftiles[blockIdx.x / kPer];
+  SeqDev* sr = &seqs[ft.seq];
+  const SeqDev sq = *sr;
+  const int64_t key0 = (int64_t)ft.idx * kRowTile + (blockIdx.x % kPer) * kFewCols;
+  if (key0 >= sq.n_tokens || sq.n_cand == 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rows_g = n_rep * sq.q_len, rows = hkv * rows_g;
+  const bool sel = sq.select[0] || sq.select[1];
+  if (sel)
+    for (int b = tid; b < 2 * kRadixBins; b += NT) lh[b] = 0;
+
+  // b_r = M_r + log2(Z_r): tpr threads of a row (a power of two) each take
+  // every tpr-th chunk, and meet by symmetric lane swaps.
+  int tpr = 1;
+  while (tpr < 64 && 2 * tpr * rows <= NT) tpr *= 2;
+  for (int r0 = 0; r0 < rows; r0 += NT / tpr) {
+    const int r = r0 + tid / tpr, rc = min(r, rows - 1), sub = tid % tpr;
+    const int g = rc / rows_g;
+    const float2* p = stats + sq.stats_off + (int64_t)g * sq.n_chunks * sq.rows_pad + (rc - g * rows_g);
+    float m = -FLT_MAX, s = 0.f;
+    constexpr int CB = 8;
+    for (int c0 = sub; c0 < sq.n_chunks; c0 += CB * tpr) {
+      float2 v[CB];
+#pragma unroll
+      for (int i = 0; i < CB; ++i) v[i] = p[(int64_t)min(c0 + i * tpr, sq.n_chunks - 1) * sq.rows_pad];
+#pragma unroll
+      for (int i = 0; i < CB; ++i)
+        if (c0 + i * tpr < sq.n_chunks) merge(m, s, v[i].x, v[i].y);
+    }
+    for (int off = 1; off < tpr; off <<= 1) {
+      const float mo = __shfl_xor(m, off), so = __shfl_xor(s, off);
+      const float mm = fmaxf(m, mo);
+      s = s * fast_exp2(m - mm) + so * fast_exp2(mo - mm);
+      m = mm;
+    }
+    if (sub == 0 && r < rows) lb[r] = s > 0.f ? m + log2f(s) : INFINITY;
+  }
+  __syncthreads();
+
+  // Sum over this wave's rows (of all groups, in order) of exp2(x - b_r).
+  const int64_t np = (sq.n_tokens + 15) / 16 * 16;
+  const int per = (rows + kFewWaves - 1) / kFewWaves, ra = min(rows, wave * per), rb = min(rows, ra + per);
+  const int64_t key = key0 + 4 * lane;
+  f32x4v sum = f32x4v{};
+  if (key < np) {
+    const float* p = logits + sq.logits_off + key;
+    constexpr int RB = 8;
+    for (int r0 = ra; r0 < rb; r0 += RB) {
+      f32x4v v[RB];
+#pragma unroll
+      for (int i = 0; i < RB; ++i) v[i] = *reinterpret_cast<const f32x4v*>(p + (int64_t)min(r0 + i, rb - 1) * np);
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+        if (r0 + i < rb) {
+          const float b = lb[r0 + i];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum[e] += fast_exp2(fmaf(v[i][e], scale_log2, -b));
+        }
+    }
+  }
+  *reinterpret_cast<f32x4v*>(&red[wave][4 * lane]) = sum;
+  __syncthreads();
+  const int64_t j = key0 + tid;
+  if (j < sq.n_tokens) {
+    float acc = red[0][tid];
+#pragma unroll
+    for (int w = 1; w < kFewWaves; ++w) acc += red[w][tid];
+    const uint8_t m = (tags + sq.tag_off)[j];
+    float v = 0.f;
+    if (m != 0) {
+      v = acc / (float)(n_rep * hkv * sq.q_len);
+      if ((m == 1 || m == 2) && (m == 1 ? sq.select[0] : sq.select[1]))
+        atomicAdd(&lh[(m - 1) * kRadixBins + (clamp_bits(v) >> 20)], 1u);
+    }
+    scores[sq.tok_off + j] = v;
+  }
+  if (!sel) return;
+  __syncthreads();
+  uint32_t* gh = hist + (int64_t)ft.seq * 2 * kRadixBins;
+  merge_hist<NT>(lh, gh);
+  if (arrive_last<NT>(ctr + sq.ctr_off + sq.n_chunks, (uint32_t)((sq.n_tokens + kFewCols - 1) / kFewCols)))
+    pick_bins<NT>(sr, gh, 0);
+}
+
+// ---------------------------------------------------------------------------
 // Host launch sequence.
 // ---------------------------------------------------------------------------
 template <class T, int D, int NW, int S = key_stages<T, D, NW>()>
@@ -880,6 +1127,23 @@ apack_status launch_scores_d(const PrunePlan& pl, const DevPtrs& dp, const Inlin
   }
 }
 
+template <int D>
+apack_status launch_few(const PrunePlan& pl, const DevPtrs& dp, const InlineCall& in, const void* q, int64_t q_hs,
+                        const void* k, int64_t k_hs, int n_rep, int hkv, float* scores, hipStream_t stream) {
+  const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
+  const unsigned nt = (unsigned)pl.tiles.size();
+  if (nt == 0) return APACK_OK;
+  hipLaunchKernelGGL(k_few_logits<D>, dim3(nt), dim3(kFewWaves * kWave), 0, stream, in, dp.seqs, dp.tiles, dp.ftiles,
+                     dp.tags, dp.ctr, (const bf16_t*)q, q_hs, (const bf16_t*)k, k_hs, n_rep, scale_log2, dp.stats,
+                     dp.logits, dp.hist, pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : (int64_t)0);
+  apack_status st = launch_status("k_few_logits");
+  if (st != APACK_OK) return st;
+  hipLaunchKernelGGL(k_few_colsum, dim3((unsigned)pl.ftiles.size() * (kRowTile / kFewCols)), dim3(kFewWaves * kWave), 0,
+                     stream, dp.seqs, dp.ftiles, dp.tags, n_rep, hkv, scale_log2, dp.stats, dp.logits, scores, dp.hist,
+                     dp.ctr);
+  return launch_status("k_few_colsum");
+}
+
 }  // namespace
 
 apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCall& in, apack_dtype dt, int d, int hq, int hkv,
@@ -887,7 +1151,10 @@ apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCa
                           int32_t* kept, hipStream_t stream) {
   const int n_rep = hq / hkv;
   apack_status st;
-  if (dt == APACK_BF16)
+  if (dt == APACK_BF16 && pl.few)
+    st = d == 64 ? launch_few<64>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream)
+                 : launch_few<128>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
+  else if (dt == APACK_BF16)
     st = d == 64 ? launch_scores_d<bf16_t, 64>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream)
                  : launch_scores_d<bf16_t, 128>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
   else

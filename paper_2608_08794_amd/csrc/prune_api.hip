@@ -113,7 +113,10 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
   // Keys per workgroup: about one score workgroup per CU over the whole
   // call (one 7- or 8-wave workgroup fills a CU), so the chip runs a single
   // round and each workgroup loads its query fragments once.
-  const int64_t target = APACK_TILE_TARGET;
+  pl.few = n_seq > 0;
+  for (const SeqDev& sd : pl.seqs)
+    pl.few &= n_rep * sd.q_len <= kFewRows && hkv * n_rep * sd.q_len <= kFewTotal;
+  const int64_t target = pl.few ? kFewTarget : APACK_TILE_TARGET;
   for (int s = 0; s < n_seq; ++s) {
     SeqDev& sd = pl.seqs[s];
     if (sd.n_cand == 0) continue;
@@ -126,6 +129,10 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
     stats += (int64_t)hkv * sd.rows_pad * sd.n_chunks;
     sd.colpart_off = colpart;
     colpart += (int64_t)hkv * sd.n_rg * sd.n_tokens;
+    if (pl.few) {
+      sd.logits_off = pl.total_logits;
+      pl.total_logits += (int64_t)hkv * n_rep * sd.q_len * ((sd.n_tokens + 15) / 16 * 16);
+    }
     sd.ctr_off = (int32_t)pl.total_ctr;
     pl.total_ctr += sd.n_chunks + 1;
     // Tiles: chunks of one (g, rg) eight apart so that both query-row
@@ -156,6 +163,8 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
   c.take<float2>(pl.total_stats);
   pl.off_colpart = c.used;
   c.take<float>(pl.total_colpart);
+  pl.off_logits = c.used;
+  c.take<float>(pl.total_logits);
   pl.off_hist = c.used;
   c.take<uint32_t>(pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : 0);
   pl.off_cnt = c.used;
@@ -236,6 +245,7 @@ apack_status apack_prune_layer(int32_t n_seq, const apack_seq* seqs, apack_dtype
   dp.tags = reinterpret_cast<uint8_t*>(ws + pl.off_tags);
   dp.stats = reinterpret_cast<float2*>(ws + pl.off_stats);
   dp.colpart = reinterpret_cast<float*>(ws + pl.off_colpart);
+  dp.logits = reinterpret_cast<float*>(ws + pl.off_logits);
   // Tag = selection slot + 1: the modality, or slot 1 for every candidate of
   // a jointly ranked sequence.
   auto tag_of = [&](int s, const apack_span& sp) {

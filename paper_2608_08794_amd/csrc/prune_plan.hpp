@@ -25,6 +25,12 @@ constexpr int kMaxWaves = 8;                   // waves per score workgroup
 #define APACK_MAX_CHUNK 4096
 #endif
 constexpr int kMaxChunk = APACK_MAX_CHUNK;    // keys per score workgroup, at most
+// A call whose sequences all have at most kFewRows query rows per key head
+// (the last query token of a grouped head, say) and kFewTotal over the heads
+// stores its logits in pass 1 rather than reading K again in pass 2.
+constexpr int kFewRows = 16;
+constexpr int kFewTotal = 1024;
+constexpr int kFewTarget = 512;   // pass-1 workgroups aimed at: two per CU
 constexpr int kRowTile = 1024;   // rows per workgroup of the select and compaction kernels
 
 // Per-sequence descriptor on the device (uploaded once per call).  The
@@ -38,6 +44,7 @@ struct SeqDev {
   int64_t tag_off;      // first byte of the sequence in the tag array
   int64_t stats_off;    // first (max, sum) partial: [g][chunk][rows_pad]
   int64_t colpart_off;  // first per-group column partial: [g*n_rg + rg][n_tokens]
+  int64_t logits_off;   // first stored logit: [g][row][n_tokens rounded up to 16] (few-row calls)
   int32_t q_len;
   int32_t n_rg;         // query-row groups per KV head
   int32_t rows_per_rg;  // rows per group (multiple of 64)
@@ -96,13 +103,15 @@ struct PrunePlan {
   int64_t max_tokens = 0;   // longest sequence
   int64_t total_stats = 0;  // (max, sum) partials
   int64_t total_colpart = 0;
+  int64_t total_logits = 0; // stored logits of a few-row call, else 0
   int64_t total_kept = 0;
   int64_t total_ctr = 0;    // arrival counters (zeroed by the upload)
   int waves = 1;
   bool any_select = false;
+  bool few = false;         // every sequence has at most kFewRows query rows per key head
   // Workspace layout (byte offsets).
   size_t off_seqs = 0, off_tiles = 0, off_ftiles = 0, off_tags = 0, off_ctr = 0, blob_bytes = 0;
-  size_t off_stats = 0, off_colpart = 0, off_hist = 0, off_cnt = 0, ws_bytes = 0;
+  size_t off_logits = 0, off_stats = 0, off_colpart = 0, off_hist = 0, off_cnt = 0, ws_bytes = 0;
 };
 
 struct DevPtrs {
@@ -112,6 +121,7 @@ struct DevPtrs {
   FTileDev* ftiles;
   float2* stats;
   float* colpart;
+  float* logits;        // stored logits of a few-row call
   uint32_t* hist;       // [n_seq][2][2048] radix histograms
   uint32_t* cnt;        // [n_ftiles][3] per-tile keep counts
   uint32_t* ctr;        // arrival counters of the score kernels

@@ -626,3 +626,50 @@ def test_descriptors_by_value_and_uploaded_agree(pieces, joint):
     assert want[2] == got[2]
     np.testing.assert_array_equal(want[0], got[0])
     np.testing.assert_array_equal(want[1], got[1])
+
+
+@pytest.mark.parametrize("hq,hkv,d,q_len", [(28, 4, 128, 1), (16, 2, 128, 2), (8, 8, 64, 16), (4, 1, 64, 3),
+                                            (64, 64, 64, 16)])
+def test_few_query_rows(hq, hkv, d, q_len):
+    """At most 16 query rows per key head (7, 16, 16, 12, and 16 over 64
+    heads): sequences whose lengths straddle the 16-key blocks, the mask's
+    128-key tiles and pass 2's 256-key and 1024-row tiles, one with no
+    candidates, one empty, spans ending inside blocks."""
+    specs = [
+        ([(0, 5, A_), (5, 4, V_)], 9, q_len, (0.5, 0.5)),
+        ([(1, 14, V_)], 16, q_len, (0.5, 0.3)),
+        ([(0, 100, A_), (110, 147, V_)], 257, q_len, (0.3, 0.6)),
+        ([], 33, q_len, (0.5, 0.5)),
+        ([(0, 0, A_)], 0, q_len, (0.5, 0.5)),
+        ([(0, 300, V_), (300, 600, A_), (901, 122, V_)], 1025, 1, (0.25, 0.7)),
+        ([(3, 2000, V_), (2010, 700, A_)], 2817, q_len, (0.4, 0.0)),   # ranked jointly
+    ]
+    _parity(_synthetic("bf16", hq, hkv, d, specs, seed=77, joint=(6,)))
+
+
+def test_few_query_rows_long_sequence():
+    """One long sequence, last query token: several steps per workgroup, many
+    chunks per row, the tiled select."""
+    specs = [([(0, 7500, A_), (7500, 32000, V_)], 39601, 1, (0.6, 0.45))]
+    _parity(_synthetic("bf16", 28, 4, 128, specs, seed=78))
+
+
+def test_few_query_rows_ties_and_one_row_more():
+    """Duplicate keys give bitwise-equal scores, and 20 rows per key head
+    (the general passes) agree with the mean of five single ones."""
+    import paper_2608_08794_amd as A
+    dup = [(10, 400), (10, 401), (200, 600)]
+    case = _synthetic("bf16", 4, 1, 128, [([(0, 700, A_)], 720, 4, (0.5, 0.5))], seed=79, lift=False, dup=dup)
+    s, _, _ = _run_prune(case)
+    assert s[10] == s[400] == s[401] and s[200] == s[600]
+    q = to_dev(case.q, "bf16")
+    k = to_dev(case.k, "bf16")
+    q5 = torch.cat([q, q[:, :1]], dim=1)     # 5 rows a head: 20 rows per key head, the general passes
+    want = []
+    for t in range(5):
+        seq = W.PruneSeq(0, 720, [(0, 700, A_)], t, 1, (0.5, 0.0))
+        want.append(A.apack_prune_layer(q5, k, [seq])[0].double())
+    got = A.apack_prune_layer(q5, k, [W.PruneSeq(0, 720, [(0, 700, A_)], 0, 5, (0.5, 0.0))])[0].double()
+    mean = torch.stack(want).mean(0)
+    # fp32 logits and sums on both sides.
+    assert float((got - mean).norm() / mean.norm()) < 4e-6
