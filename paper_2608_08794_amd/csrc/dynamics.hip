@@ -6,10 +6,10 @@
 //                the same read leaves per-slice row sums of squares
 //   k_band       band Gram v_f.v_{f+d}, a_f.a_{f+d} (d < w), v_f.q, q.q
 //   k_cka        Eq. 1 per frame from the centred w x w window Grams, the
-//                clip mean and the gate of Eq. 2
-//   k_norms      squared norms of every visual and audio token of the clips
-//                (fp64), from k_pool's per-slice sums, and 1/|x| of the
-//                visual tokens
+//                clip mean and the gate of Eq. 2; beside it (k_norms, of its
+//                own for the spatial scorer) squared norms of every visual
+//                and audio token of the clips (fp64), from k_pool's per-slice
+//                sums, and 1/|x| of the visual tokens
 //   k_gate_gemm256, k_gate_gemm_any (gate_gemm.hip)
 //                only where the gate fired: X_A . X_V^T on bf16 MFMA, scaled
 //                by 1/|a_j|, max over audio tokens in-lane, merged across
@@ -30,6 +30,7 @@
 // is taken in fp64, as in the oracle.  The gate GEMM accumulates in fp32.
 #include <algorithm>
 #include <cfloat>
+#include <climits>
 #include <cmath>
 #include <type_traits>
 
@@ -213,25 +214,32 @@ struct Raw8<float> {
 // items are every frame of every clip, then one per clip for the query.
 // The slices of an item are consecutive block indices, so the blocks that
 // read the same rows run together and each DRAM page is opened once.
-// The block's four waves take every fourth row of the frame's visual tokens,
-// of its audio bin (or of the clip's query span); their fp64 partial sums
-// meet in LDS and are added in wave order.  A wave loads eight of its rows
-// (four of the audio bin's) together as raw bits before widening any, so
-// that enough bytes are in flight for HBM.  The same pass leaves
-// each visual and audio row's sum of squares over the slice in
-// sqp[slice][row] (audio rows after the n_vis visual rows), so the token
+// The block's waves take every WAVES-th row of the frame's visual tokens, of
+// its audio bin (or of the clip's query span); their fp64 partial sums meet
+// in LDS and are added in wave order.  Four waves a block where the blocks
+// alone fill the chip, sixteen where they do not (kPoolWideBlocks), so that a
+// frame's rows take one round trip to memory instead of five.  A wave loads
+// eight (or twelve) of its rows (four of the audio bin's) together as raw
+// bits before widening any, so that enough bytes are in flight for HBM.  The
+// same pass leaves each visual and audio row's sum of squares over the slice
+// in sqp[slice][row] (audio rows after the n_vis visual rows), so the token
 // norms need no second read of X_V and X_A.
 // ---------------------------------------------------------------------------
-constexpr int kPoolWaves = kBlk / 64;      // row groups per block
-
-template <class T>
-__global__ __launch_bounds__(kBlk) void k_pool(const ClipDev* __restrict__ clips, const FrameDev* __restrict__ frames,
+// Up to one block per compute unit they have sixteen waves.  40 frames at
+// D = 2048 (164 blocks): 15.6 us with four waves, 12.7 with sixteen; 120
+// frames at D = 2048 in fp32 (484 blocks) 30.8 and 33.7, at D = 3584 (847)
+// 33.5 and 43.7.
+constexpr int64_t kPoolWideBlocks = 256;
+template <class T, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) void k_pool(const ClipDev* __restrict__ clips, const FrameDev* __restrict__ frames,
                                                int64_t total_frames, int dim, int slices, const T* __restrict__ xv,
                                                const T* __restrict__ xa, const T* __restrict__ xq,
                                                double* __restrict__ v, double* __restrict__ a,
                                                double* __restrict__ q, int64_t n_vis, int64_t sq_stride,
                                                double* __restrict__ sqp) {
-  __shared__ double part[2][kPoolWaves - 1][kPoolSlice];
+  constexpr int kPoolWaves = WAVES;
+  constexpr int kRows = WAVES > 4 && sizeof(T) == 2 ? 12 : 8;   // visual rows a wave loads together
+  __shared__ double part[2][kPoolWaves][kPoolSlice];
   const int lane = threadIdx.x & 63, rg = threadIdx.x >> 6;
   const int64_t item = blockIdx.x / slices;
   const int slice = (int)(blockIdx.x - item * slices);
@@ -266,18 +274,18 @@ __global__ __launch_bounds__(kBlk) void k_pool(const ClipDev* __restrict__ clips
     // Lanes past dim load the row's last eight elements (Raw8 clamps) and
     // widen them to zeros.
     const T* vrow = xv + row0 * dim;
-    // The wave's rows rg, rg + 4, ... eight at a time: the eight loads are
+    // The wave's rows rg, rg + WAVES, ... kRows at a time: their loads are
     // issued together as raw bits (a row past the frame re-reads its last
     // row and adds nothing), then widened and added in row order; the sums
     // of squares are reduced four rows at a time.
     const int P = c.per_frame;
-    for (int p0 = rg; p0 < P; p0 += 8 * kPoolWaves) {
-      Raw8<T> raw[8];
+    for (int p0 = rg; p0 < P; p0 += kRows * kPoolWaves) {
+      Raw8<T> raw[kRows];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) raw[j].load(vrow + (int64_t)min(p0 + j * kPoolWaves, P - 1) * dim, d0, dim);
-      double s2[8];
+      for (int j = 0; j < kRows; ++j) raw[j].load(vrow + (int64_t)min(p0 + j * kPoolWaves, P - 1) * dim, d0, dim);
+      double s2[kRows];
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
+      for (int j = 0; j < kRows; ++j) {
         s2[j] = 0.0;
         if (p0 + j * kPoolWaves < P) {
           double o8[8];
@@ -290,13 +298,13 @@ __global__ __launch_bounds__(kBlk) void k_pool(const ClipDev* __restrict__ clips
         }
       }
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < kRows / 4; ++h) {
         const double t = wave_sum4(*reinterpret_cast<const double(*)[4]>(&s2[4 * h]));
         const int p = p0 + (4 * h + lane) * kPoolWaves;
         if (lane < 4 && p < P) sq[row0 + p] = t;
       }
     }
-    // The audio bin's rows rg, rg + 4, ... four at a time, the same way.
+    // The audio bin's rows rg, rg + WAVES, ... four at a time, the same way.
     // A row shared by two bins gets the same value from both.
     const T* arow = xa + c.aud_off * dim;
     for (int64_t r0 = lo + rg; r0 < hi; r0 += 4 * kPoolWaves) {
@@ -332,30 +340,25 @@ __global__ __launch_bounds__(kBlk) void k_pool(const ClipDev* __restrict__ clips
       for (int e = 0; e < 8; ++e) av[e] += o[e];
     }
   }
-  if (rg > 0) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      part[0][rg - 1][lane * 8 + e] = av[e];
-      part[1][rg - 1][lane * 8 + e] = aa[e];
-    }
+  for (int e = 0; e < 8; ++e) {
+    part[0][rg][lane * 8 + e] = av[e];
+    part[1][rg][lane * 8 + e] = aa[e];
   }
   __syncthreads();
-  if (rg != 0 || !live) return;
-  for (int w = 0; w < kPoolWaves - 1; ++w)
+  // One element per thread and turn, its partials added in wave order.
+  for (int i = threadIdx.x; i < 2 * kPoolSlice; i += WAVES * 64) {
+    const int which = i / kPoolSlice, el = i % kPoolSlice, d = slice * kPoolSlice + el;
+    if (d >= dim || (which == 1 && !is_frame)) continue;
+    double t = part[which][0][el];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      av[e] += part[0][w][lane * 8 + e];
-      aa[e] += part[1][w][lane * 8 + e];
-    }
-  if (is_frame) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      v[frame * dim + d0 + e] = av[e] / (double)rows_v;
-      a[frame * dim + d0 + e] = hi > lo ? aa[e] / (double)(hi - lo) : 0.0;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) q[(int64_t)ci * dim + d0 + e] = av[e] / (double)rows_v;
+    for (int w = 1; w < kPoolWaves; ++w) t += part[which][w][el];
+    if (!is_frame)
+      q[(int64_t)ci * dim + d] = t / (double)rows_v;
+    else if (which == 0)
+      v[frame * dim + d] = t / (double)rows_v;
+    else
+      a[frame * dim + d] = hi > lo ? t / (double)(hi - lo) : 0.0;
   }
 }
 
@@ -425,16 +428,55 @@ __device__ __forceinline__ double band_at(const double* band, int64_t f0, int i,
 }
 
 // ---------------------------------------------------------------------------
+// Squared norms of the visual rows [0, n_vis) and audio rows [0, n_aud) of
+// the clips, from k_pool's per-slice partials added in slice order; the
+// visual max-cosine keys start at 0 (below every real key).  Rows in no
+// clip get whatever their slots held and are never read.
+// ---------------------------------------------------------------------------
+struct NormArgs {
+  int64_t n_vis, n_aud;
+  int slices;
+  const double* sqp;
+  double *nv, *rv, *na;
+  uint32_t* maxkey;
+};
+__device__ __forceinline__ void token_norms(const NormArgs& a, int64_t block) {
+  const int64_t n_vis = a.n_vis, stride = a.n_vis + a.n_aud;
+  const int64_t row = block * kBlk + threadIdx.x;
+  if (row >= stride) return;
+  double s = 0.0;
+  for (int k = 0; k < a.slices; ++k) s += a.sqp[(int64_t)k * stride + row];
+  if (row < n_vis) {
+    a.nv[row] = s;
+    a.rv[row] = s > 0.0 ? 1.0 / sqrt(s) : 0.0;   // 1/|x| for the direct distance, 0 for a zero token
+    a.maxkey[row] = 0u;
+  } else {
+    a.na[row - n_vis] = s;
+  }
+}
+
+__global__ __launch_bounds__(kBlk) void k_norms(const NormArgs a) { token_norms(a, blockIdx.x); }
+
+// ---------------------------------------------------------------------------
 // Eq. 1 per frame over its clamped window, the clip mean and the gate.
 // W >= w bounds the window, so the loops unroll and the row means stay in
 // registers; the Gram entries are read from the band where they are used.
+// One workgroup per clip; the workgroups past those form the token norms,
+// which depend on nothing here (the spatial scorer needs the norms earlier
+// and launches them itself).  120 frames, 18.8k tokens: 4.8 + 5.0 us in two
+// launches, 8.0 in one.
 // ---------------------------------------------------------------------------
 template <int W>
-__global__ __launch_bounds__(kBlk) void k_cka(ClipDev* __restrict__ clips, int w, double tau, int alignment,
+__global__ __launch_bounds__(kBlk) void k_cka(ClipDev* __restrict__ clips, int n_clips, const NormArgs norms, int w,
+                                              double tau, int alignment,
                                               const double* __restrict__ band_v, const double* __restrict__ band_a,
                                               double* __restrict__ cka, float* __restrict__ frame_cka,
                                               uint8_t* __restrict__ gate_out) {
   __shared__ double sh[kBlk / 64];
+  if (blockIdx.x >= (unsigned)n_clips) {
+    token_norms(norms, (int64_t)blockIdx.x - n_clips);
+    return;
+  }
   ClipDev* c = &clips[blockIdx.x];
   const int F = c->n_frames;
   const int64_t f0 = c->frame_off;
@@ -503,30 +545,6 @@ __global__ __launch_bounds__(kBlk) void k_cka(ClipDev* __restrict__ clips, int w
     if (alignment == APACK_ALIGN_AV_COSINE) fired = F > 0 ? 1 : 0;
     c->gate = fired;
     if (gate_out) gate_out[blockIdx.x] = (uint8_t)fired;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Squared norms of the visual rows [0, n_vis) and audio rows [0, n_aud) of
-// the clips, from k_pool's per-slice partials added in slice order; the
-// visual max-cosine keys start at 0 (below every real key).  Rows in no
-// clip get whatever their slots held and are never read.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlk) void k_norms(int64_t n_vis, int64_t n_aud, int slices,
-                                                const double* __restrict__ sqp, double* __restrict__ nv,
-                                                double* __restrict__ rv, double* __restrict__ na,
-                                                uint32_t* __restrict__ maxkey) {
-  const int64_t stride = n_vis + n_aud;
-  const int64_t row = (int64_t)blockIdx.x * kBlk + threadIdx.x;
-  if (row >= stride) return;
-  double s = 0.0;
-  for (int k = 0; k < slices; ++k) s += sqp[(int64_t)k * stride + row];
-  if (row < n_vis) {
-    nv[row] = s;
-    rv[row] = s > 0.0 ? 1.0 / sqrt(s) : 0.0;   // 1/|x| for the direct distance, 0 for a zero token
-    maxkey[row] = 0u;
-  } else {
-    na[row - n_vis] = s;
   }
 }
 
@@ -1328,6 +1346,11 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return max((uint32_t)h[0], (uint32_t)h[1]);
 }
 
+// The same for signed values.
+__device__ __forceinline__ int wave_max_i32(int v) {
+  return (int)(wave_max_u32((uint32_t)v ^ 0x80000000u) ^ 0x80000000u);
+}
+
 // Cosine of tokens i and j of an anchor frame from their Gram entry g, the
 // Gram's diagonal entries d (squared norms, summed like every entry) and
 // r = 1 / sqrt(d): exactly 1 when g equals both diagonal entries and is not
@@ -1367,21 +1390,21 @@ struct DafpsLds {
 
 // Density of token i: the mean of its dafps_k largest cosines to the other
 // tokens of the frame, times one plus the number of those cosines at or
-// above the coverage threshold.  Two lanes of a wave (2i and 2i + 1) share
-// token i, each walking its own rows [lo, hi) of column i of the Gram (S is
-// exactly symmetric: entries (i, j) and (j, i) are the same products summed
-// in the same order); each entry becomes a cosine, written back over the
+// above the coverage threshold.  LANES neighbouring lanes of a wave (two or
+// four) share token i, each walking its own rows [lo, hi) of column i of the
+// Gram (S is exactly symmetric: entries (i, j) and (j, i) are the same products
+// summed in the same order); each entry becomes a cosine, written back over the
 // Gram entry in LDS (rows below R) or into the corner block (rows and token
 // at or past R), so that the pick loop reads cosines.  Rows at or past R
 // come from the Gram in global memory, the first eight of a lane's share
 // prefetched into `pre` before the rows were staged.  Reads are issued
 // eight rows at a time; ns and ng bound, for every lane of the wave, the
-// staged and global row counts.  The two halves' lists and counts are then
-// merged across the lane pair.  KM >= min(dafps_k, P - 1): only the first
+// staged and global row counts.  The lists and counts are then merged
+// across the lanes.  KM >= min(dafps_k, P - 1): only the first
 // min(dafps_k, P - 1) entries of the merged list enter the mean.  Every
 // lane of the wave must take part (lanes of tokens past P with empty
 // ranges).
-template <int KM>
+template <int KM, int LANES>
 __device__ __forceinline__ double dafps_density(const DafpsLds& L, const double* __restrict__ S, int P, int i,
                                                 int lo, int hi, int ns, int ng, const double (&pre)[8], double di,
                                                 double ri, int k, double cover) {
@@ -1432,13 +1455,20 @@ __device__ __forceinline__ double dafps_density(const DafpsLds& L, const double*
     for (int u = 0; u < 8; ++u) g[u] = S[(int64_t)min(g_lo + jj + u, P - 1) * P + ic];
     tail(g_lo + jj, g);
   }
-  // Merge with the partner lane's list and count.
+  // Merge with the partner lanes' lists and counts (quad xor 1, then xor 2).
   double o[KM];
 #pragma unroll
   for (int q = 0; q < KM; ++q) o[q] = dpp_f64<0xB1>(top[q]);
 #pragma unroll
   for (int q = 0; q < KM; ++q) top_insert(top, o[q]);
   cov += __builtin_amdgcn_update_dpp(cov, cov, 0xB1, 0xF, 0xF, false);
+  if constexpr (LANES == 4) {
+#pragma unroll
+    for (int q = 0; q < KM; ++q) o[q] = dpp_f64<0x4E>(top[q]);
+#pragma unroll
+    for (int q = 0; q < KM; ++q) top_insert(top, o[q]);
+    cov += __builtin_amdgcn_update_dpp(cov, cov, 0x4E, 0xF, 0xF, false);
+  }
   const int nt = min(k, P - 1);
   double knn = 0.0;
 #pragma unroll
@@ -1453,20 +1483,18 @@ __device__ __forceinline__ double dafps_density(const DafpsLds& L, const double*
 // tokens count as taken).  The first pick is the densest token, each later
 // one the token farthest from the picked set, weighted by density:
 // argmax of (1 - max cosine to the picked set) rho^power.  The argmax is
-// lexicographic (value desc, token asc): the wave's largest order key, then
-// the lowest token holding it -- tokens 64u + lane ascend with u and then
-// with the lane, so the first non-empty ballot in u order names it.  Taken
-// tokens have key 0, below every value's key except a negative NaN's; should
-// no untaken token reach the maximum key (negative NaNs only), the lowest
-// untaken token is taken, so a pick is always valid.  The picked positions
+// lexicographic (value desc, token asc): the wave's largest high word, the
+// largest order key among the tokens that hold it, then the lowest such
+// token -- tokens 64u + lane ascend with u and then with the lane, so the
+// first non-empty ballot in u order names it.  A pick is always an untaken
+// token.  The picked positions
 // go to kept[out...] in ascending order, as rows base + t.
 template <int KU>
 __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __restrict__ S, int P, int k,
                                            double power, int lane, int32_t* __restrict__ kept, int64_t out,
                                            int64_t base) {
   const int R = L.R;
-  double wgt[KU], smax[KU], dt[KU], rt[KU];
-  uint64_t key[KU];
+  double wgt[KU], smax[KU], dt[KU], rt[KU], val[KU];
   // Taken tokens as wave-wide lane masks (the same in every lane), one per
   // u; tokens past P count as taken.
   uint64_t tk[KU], pad[KU];
@@ -1477,27 +1505,33 @@ __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __re
     pad[u] = tk[u] = __ballot(t >= P);
     const bool tkn = t >= P;
     tc[u] = min(t, P - 1);
-    const double rho = L.rho[tc[u]];
-    wgt[u] = tkn ? 0.0 : pow(rho, power);
-    key[u] = tkn ? 0 : order_key(rho);
+    val[u] = L.rho[tc[u]] + 0.0;   // -0 as +0
+    wgt[u] = tkn ? 0.0 : pow(val[u], power);
     smax[u] = -INFINITY;
     const double2 n = L.nrm[tc[u]];
     dt[u] = n.x;
     rt[u] = n.y;
   }
   auto pick_of = [&]() {
-    uint64_t kb = key[0];
+    // Signed integers with the order of the values' high words (no value is
+    // -0); a taken token is below every value.
+    int hk[KU];
 #pragma unroll
-    for (int u = 1; u < KU; ++u) kb = key[u] > kb ? key[u] : kb;
-    const uint32_t mh = wave_max_u32((uint32_t)(kb >> 32));
-    // Untaken tokens whose key has the maximal high word: when there is
-    // one (the usual case) it is the pick, and the low words need no
-    // reduction.
+    for (int u = 0; u < KU; ++u) {
+      const int h = (int)((uint64_t)__double_as_longlong(val[u]) >> 32);
+      hk[u] = __builtin_amdgcn_inverse_ballot_w64(tk[u]) ? INT_MIN : h ^ ((h >> 31) & 0x7FFFFFFF);
+    }
+    int hm = hk[0];
+#pragma unroll
+    for (int u = 1; u < KU; ++u) hm = max(hm, hk[u]);
+    hm = wave_max_i32(hm);
+    // Untaken tokens with the maximal high word: when there is one (the
+    // usual case) it is the pick, and the low words need no reduction.
     uint64_t hb[KU];
     int cnt = 0;
 #pragma unroll
     for (int u = 0; u < KU; ++u) {
-      hb[u] = __ballot((uint32_t)(key[u] >> 32) == mh) & ~tk[u];
+      hb[u] = __ballot(hk[u] == hm) & ~tk[u];
       cnt += __popcll(hb[u]);
     }
     int best = 0x7FFFFFFF;
@@ -1508,11 +1542,17 @@ __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __re
       return best;
     }
     if (cnt > 1) {
-      const uint32_t ml = wave_max_u32((uint32_t)(kb >> 32) == mh ? (uint32_t)kb : 0u);
-      const uint64_t mk = ((uint64_t)mh << 32) | ml;
+      // The largest whole key among them, the lowest token holding it.
+      uint32_t lo[KU], lm = 0;
 #pragma unroll
       for (int u = 0; u < KU; ++u) {
-        const uint64_t b = __ballot(key[u] == mk) & ~tk[u];
+        lo[u] = __builtin_amdgcn_inverse_ballot_w64(hb[u]) ? (uint32_t)order_key(val[u]) : 0u;
+        lm = max(lm, lo[u]);
+      }
+      lm = wave_max_u32(lm);
+#pragma unroll
+      for (int u = 0; u < KU; ++u) {
+        const uint64_t b = __ballot(lo[u] == lm) & hb[u];
         if (b && best == 0x7FFFFFFF) best = 64 * u + (int)__builtin_ctzll(b);
       }
     }
@@ -1550,8 +1590,7 @@ __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __re
     }
     if (n + 1 >= k) break;
 #pragma unroll
-    for (int u = 0; u < KU; ++u)
-      key[u] = order_key((1.0 - smax[u]) * wgt[u]) & (__builtin_amdgcn_inverse_ballot_w64(tk[u]) ? 0ull : ~0ull);
+    for (int u = 0; u < KU; ++u) val[u] = fma(1.0 - smax[u], wgt[u], 0.0);   // the product, a zero one as +0
     pick = pick_of();
   }
   // Ascending output of the picked positions.
@@ -1564,13 +1603,17 @@ __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __re
 }
 
 // ---------------------------------------------------------------------------
-// DA-FPS on an anchor frame: one workgroup, two threads per token.
+// DA-FPS on an anchor frame: one workgroup, LANES threads per token: four for
+// density lists of up to eight entries (a 144-token frame's density pass,
+// bound by the VALU of few waves, took 11.7 us with two); longer lists take
+// the registers of two.  Whole kernel, 120 frames: 52.6 us to 47; 3700 frames
+// of eight clips: 181 to 159.
 // ---------------------------------------------------------------------------
 // The frame's raw Gram rows [0, R) go to LDS by direct loads; R is the
 // largest row count for which those rows, the (P - R) x (P - R) corner block
 // and the per-token arrays fit in 160 KiB (R = P up to P = 141, 139 rows of
 // 144), else as many rows as fit without the corner.  The density pass
-// (threads 2i and 2i + 1 on token i, rows split at (P + 1) / 2) turns every
+// (each of a token's threads on its share of the rows) turns every
 // entry into a cosine (cos_gram).  The pick loop then runs in one wave,
 // which holds up to four tokens per lane and finds each pick from order
 // keys reduced by DPP (dafps_pick); a pick reads one cosine row from LDS:
@@ -1578,30 +1621,31 @@ __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __re
 // (the same values, by symmetry) and the corner block -- or, when the
 // corner did not fit, the Gram row in global memory, turned into cosines as
 // it is read.
-constexpr int kDafpsThreads = 2 * kMaxPerFrame;
 
 // Non-anchor frame: the k positions least similar to the anchor token at the
-// same position, lower position first on ties, in ascending order.  Two
-// threads per position, each ranking it against half of the frame's.
+// same position, lower position first on ties, in ascending order.  LANES
+// threads per position, each ranking it against its share of the frame's.
+template <int LANES>
 __device__ __forceinline__ void dedup_pick(const double* __restrict__ simg, double* lds, int P, int k,
                                            int32_t* __restrict__ kept, int64_t out, int64_t base) {
-  double* sim = lds;                                               // one per position, and one of padding
-  int* wcount = reinterpret_cast<int*>(lds + kMaxPerFrame + 2);   // one per wave
+  double* sim = lds;                                                        // one per position, padded
+  int* wcount = reinterpret_cast<int*>(lds + kMaxPerFrame + LANES);   // one per wave
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int p = tid >> 1, h = tid & 1;
-  const int half = (P + 1) / 2;
-  if (tid < 2 * half) sim[tid] = tid < P ? simg[tid] : INFINITY;
+  const int p = tid / LANES, h = tid % LANES;
+  const int part = (P + LANES - 1) / LANES;
+  if (tid < LANES * part) sim[tid] = tid < P ? simg[tid] : INFINITY;
   __syncthreads();
   const double mine = p < P ? sim[p] : 0.0;
-  const int q0 = h * half;
+  const int q0 = h * part;
   int rank = 0;
 #pragma unroll 8
-  for (int i = 0; i < half; ++i) {
+  for (int i = 0; i < part; ++i) {
     const int q = q0 + i;
-    const double o = sim[q];   // an odd P's last entry is +inf
+    const double o = sim[q];   // the padding is +inf
     rank += (int)((o < mine) | ((o == mine) & (q < p)));
   }
-  rank += __shfl_xor(rank, 1);
+#pragma unroll
+  for (int off = 1; off < LANES; off <<= 1) rank += __shfl_xor(rank, off);
   const bool kp = p < P && rank < k && h == 0;
   const uint64_t bal = __ballot(kp);
   if (lane == 0) wcount[wave] = __popcll(bal);
@@ -1610,7 +1654,8 @@ __device__ __forceinline__ void dedup_pick(const double* __restrict__ simg, doub
   if (kp) kept[out + __popcll(bal & ((1ull << lane) - 1ull))] = (int32_t)(base + p);
 }
 
-__global__ __launch_bounds__(kDafpsThreads) void k_dafps(const ClipDev* __restrict__ clips,
+template <int LANES>
+__global__ __launch_bounds__(LANES * kMaxPerFrame) void k_dafps(const ClipDev* __restrict__ clips,
                                                          const FrameDev* __restrict__ frames,
                                                          const FramePlanDev* __restrict__ plan, DynParamsDev prm,
                                                          const double* __restrict__ gram,
@@ -1623,10 +1668,11 @@ __global__ __launch_bounds__(kDafpsThreads) void k_dafps(const ClipDev* __restri
   if (fp.budget == 0) return;
   if (!fp.is_anchor) {
     const int64_t row0 = (int64_t)fr.f * c.per_frame;
-    dedup_pick(sim + c.token_off + row0, lds, c.per_frame, fp.budget, kept, fp.out_off, c.vis_off + row0);
+    dedup_pick<LANES>(sim + c.token_off + row0, lds, c.per_frame, fp.budget, kept, fp.out_off, c.vis_off + row0);
     return;
   }
-  const int P = c.per_frame, tid = threadIdx.x, i = tid >> 1, h = tid & 1;
+  constexpr int kDafpsThreads = LANES * kMaxPerFrame;
+  const int P = c.per_frame, tid = threadIdx.x, i = tid / LANES, h = tid % LANES;
   const int k = min(fp.budget, P);
   const double* S = gram + c.gram_off + (int64_t)fr.f * P * P;
 
@@ -1646,12 +1692,14 @@ __global__ __launch_bounds__(kDafpsThreads) void k_dafps(const ClipDev* __restri
   L.nrm = reinterpret_cast<double2*>(lds + nrm_off);
   L.rho = lds + nrm_off + 2 * P;
 
-  // Each thread's rows of column i: [0, Hs) or [Hs, P); ns and ng bound the
-  // staged and global counts of either half (the same for every wave).
-  const int Hs = (P + 1) / 2;
-  const int lo = i < P ? (h ? Hs : 0) : 0, hi = i < P ? (h ? P : Hs) : 0;
-  const int ns = max(min(Hs, R), max(min(P, R) - Hs, 0));
-  const int ng = max(Hs - min(Hs, R), P - max(Hs, R));
+  // Each thread's rows of column i: the h-th share; ns and ng bound the
+  // staged and global counts of any share (the same for every wave).
+  const int Hs = (P + LANES - 1) / LANES;
+  const int lo = i < P ? min(P, h * Hs) : 0, hi = i < P ? min(P, (h + 1) * Hs) : 0;
+  const int ns = min(Hs, R);
+  int ng = 0;
+#pragma unroll
+  for (int u = 0; u < LANES; ++u) ng = max(ng, min(P, (u + 1) * Hs) - max(min(P, u * Hs), R));
 
   // Global reads first (diagonal entry, the first eight global rows of the
   // thread's share of column i), then the staged rows; all in flight
@@ -1706,22 +1754,26 @@ __global__ __launch_bounds__(kDafpsThreads) void k_dafps(const ClipDev* __restri
   // Density of every token; the list length is the exact dafps_k up to 8.
   // Waves whose tokens all lie past P skip it (the test is the same for the
   // whole wave, so every lane of a working wave takes part).
-  if (32 * (tid >> 6) < P) {
+  if (64 / LANES * (tid >> 6) < P) {
     const int dk = prm.dafps_k;
     const double cv = prm.cover;
     double rho;
-    switch (dk) {
-      case 1: rho = dafps_density<1>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv); break;
-      case 2: rho = dafps_density<2>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv); break;
-      case 3: rho = dafps_density<3>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv); break;
-      case 4: rho = dafps_density<4>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv); break;
-      case 5: rho = dafps_density<5>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv); break;
-      case 6: rho = dafps_density<6>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv); break;
-      case 7: rho = dafps_density<7>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv); break;
-      case 8: rho = dafps_density<8>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv); break;
-      default:
-        rho = dk <= 16 ? dafps_density<16>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv)
-                       : dafps_density<32>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv);
+    auto density = [&](auto km) {
+      return dafps_density<decltype(km)::value, LANES>(L, S, P, i, lo, hi, ns, ng, pre, di, ri, dk, cv);
+    };
+    if constexpr (LANES == 2) {
+      rho = dk <= 16 ? density(std::integral_constant<int, 16>{}) : density(std::integral_constant<int, 32>{});
+    } else {
+      switch (dk) {
+        case 1: rho = density(std::integral_constant<int, 1>{}); break;
+        case 2: rho = density(std::integral_constant<int, 2>{}); break;
+        case 3: rho = density(std::integral_constant<int, 3>{}); break;
+        case 4: rho = density(std::integral_constant<int, 4>{}); break;
+        case 5: rho = density(std::integral_constant<int, 5>{}); break;
+        case 6: rho = density(std::integral_constant<int, 6>{}); break;
+        case 7: rho = density(std::integral_constant<int, 7>{}); break;
+        default: rho = density(std::integral_constant<int, 8>{});
+      }
     }
     if (i < P && h == 0) L.rho[i] = rho;
   }
@@ -1747,8 +1799,11 @@ apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& 
   const int nf = (int)pl.frames.size(), nc = (int)pl.clips.size();
   const unsigned dchunks = (unsigned)((dim + kPoolSlice - 1) / kPoolSlice);
   const int64_t n_vis = pl.total_tokens, n_aud = pl.total_audio;
-  hipLaunchKernelGGL(k_pool<T>, dim3((unsigned)((nf + nc) * dchunks)), dim3(kBlk), 0, s, dp.clips, dp.frames,
-                     (int64_t)nf, dim, (int)dchunks, xv, xa, xq, dp.v, dp.a, dp.q, n_vis, n_vis + n_aud, dp.sqp);
+  const int64_t pool_blocks = (int64_t)(nf + nc) * dchunks;
+  const bool pool_wide = pool_blocks <= kPoolWideBlocks;
+  hipLaunchKernelGGL((pool_wide ? k_pool<T, 16> : k_pool<T, 4>), dim3((unsigned)pool_blocks),
+                     dim3(pool_wide ? 1024 : 256), 0, s, dp.clips, dp.frames, (int64_t)nf, dim, (int)dchunks, xv, xa, xq,
+                     dp.v, dp.a, dp.q, n_vis, n_vis + n_aud, dp.sqp);
   if ((st = launch_status("k_pool")) != APACK_OK) return st;
   if (nf > 0) {
     // Partners per frame: max(w, 2) <= kMaxWindow (checked on the host).
@@ -1762,10 +1817,12 @@ apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& 
                        dp.a, dp.q, dp.band_v, dp.band_a, dp.vq, dp.qq);
     if ((st = launch_status("k_band")) != APACK_OK) return st;
   }
-  if (n_vis + n_aud > 0) {
-    hipLaunchKernelGGL(k_norms, dim3((unsigned)((n_vis + n_aud + kBlk - 1) / kBlk)), dim3(kBlk), 0, s, n_vis, n_aud,
-                       (int)dchunks, dp.sqp, dp.nv, dp.rv, dp.na, dp.maxkey);
+  const NormArgs norms{n_vis, n_aud, (int)dchunks, dp.sqp, dp.nv, dp.rv, dp.na, dp.maxkey};
+  unsigned norm_blocks = (unsigned)((n_vis + n_aud + kBlk - 1) / kBlk);
+  if (prm.alignment == APACK_ALIGN_SPATIAL_CKA && norm_blocks > 0) {
+    hipLaunchKernelGGL(k_norms, dim3(norm_blocks), dim3(kBlk), 0, s, norms);
     if ((st = launch_status("k_norms")) != APACK_OK) return st;
+    norm_blocks = 0;
   }
   if (prm.alignment == APACK_ALIGN_SPATIAL_CKA && nf > 0) {
     const int64_t items = ((int64_t)nf + 7) / 8 * 8 * pl.spatial_blocks;
@@ -1778,7 +1835,7 @@ apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& 
     if ((st = launch_status("k_spatial_reduce")) != APACK_OK) return st;
   }
   auto cka = prm.window <= 2 ? k_cka<2> : prm.window <= 4 ? k_cka<4> : prm.window <= 8 ? k_cka<8> : k_cka<kMaxWindow>;
-  hipLaunchKernelGGL(cka, dim3(nc), dim3(kBlk), 0, s, dp.clips, prm.window, prm.tau_gate, prm.alignment, dp.band_v,
+  hipLaunchKernelGGL(cka, dim3((unsigned)nc + norm_blocks), dim3(kBlk), 0, s, dp.clips, nc, norms, prm.window, prm.tau_gate, prm.alignment, dp.band_v,
                      dp.band_a, dp.cka, frame_cka, gate_fired);
   if ((st = launch_status("k_cka")) != APACK_OK) return st;
   if (pl.gemm_tiles > 0) {
@@ -1806,8 +1863,9 @@ apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& 
                          dp.sim, pb);
       if ((st = launch_status("k_dedup")) != APACK_OK) return st;
     }
-    hipLaunchKernelGGL(k_dafps, dim3(nf), dim3(kDafpsThreads), 0, s, dp.clips, dp.frames, dp.plan, prm, dp.gram, dp.sim,
-                       kept);
+    const bool short_lists = prm.dafps_k <= 8;
+    hipLaunchKernelGGL((short_lists ? k_dafps<4> : k_dafps<2>), dim3(nf), dim3((short_lists ? 4 : 2) * kMaxPerFrame), 0, s,
+                       dp.clips, dp.frames, dp.plan, prm, dp.gram, dp.sim, kept);
     if ((st = launch_status("k_dafps")) != APACK_OK) return st;
   }
   return APACK_OK;

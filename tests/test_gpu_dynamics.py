@@ -332,6 +332,20 @@ def test_gram_blocks_at_their_edges(dim, per_frame, audio, alignment):
     _compare(case, _run(case), want)
 
 
+@pytest.mark.parametrize("frames,per_frame", [
+    (127, 16),   # 256 pooling blocks of two slices: sixteen waves, one row each
+    (127, 3),    # more waves than rows
+    (128, 9),    # 258 blocks: four waves
+    (40, 200),   # sixteen waves, a second turn of loads for the last rows
+])
+def test_pooling_blocks_either_side_of_the_rule(frames, per_frame):
+    """Frame means and token norms where the pooling changes its wave count."""
+    case = W.dynamics_small("offset", seed=96, dim=520, frames=frames, per_frame=per_frame, audio=3 * frames)
+    want = _oracle(case)
+    _certify(want)
+    _compare(case, _run(case), want)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("dim,frames,audio", [
     (8, 127, 255),     # one partial K step, one short tile
