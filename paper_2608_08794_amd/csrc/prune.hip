@@ -624,7 +624,8 @@ __global__ __launch_bounds__(NW * kWave) void k_colsum(SeqDev* __restrict__ seqs
                                                        int n_rep, int hkv, float scale_log2,
                                                        const float2* __restrict__ stats,
                                                        float* __restrict__ colpart, float* __restrict__ scores,
-                                                       uint32_t* __restrict__ hist, uint32_t* __restrict__ ctr) {
+                                                       uint32_t* __restrict__ hist, uint32_t* __restrict__ ctr,
+                                                       ScoreTail tail) {
   using G = TileGeom<T, D>;
   using M = Mma<T>;
   constexpr int NKB = kKeyTile / 32;
@@ -790,6 +791,7 @@ __global__ __launch_bounds__(NW * kWave) void k_colsum(SeqDev* __restrict__ seqs
   if (n_tiles >= 2) col_flush<NKB, NW>(red, (n_tiles - 2) % 3, n_active, last0 - kKeyTile, key_end, out, tid);
   if (n_tiles >= 1) col_flush<NKB, NW>(red, (n_tiles - 1) % 3, n_active, last0, key_end, out, tid);
 
+  if (tail == kSumInSelect) return;
   // The last workgroup of this key chunk (over groups and row groups) forms
   // I_j = (sum of the per-group partials, fixed order) / (Hq * T), 0 for
   // non-candidates, and counts the first radix digit; the last chunk of the
@@ -798,7 +800,7 @@ __global__ __launch_bounds__(NW * kWave) void k_colsum(SeqDev* __restrict__ seqs
   SeqDev* sr = &seqs[tl.seq];
   const int planes = hkv * sr->n_rg;
   if (!arrive_last<NW * kWave>(ctr + sr->ctr_off + tl.chunk, (uint32_t)planes)) return;
-  const bool sel = sr->select[0] || sr->select[1];
+  const bool sel = tail == kTailInScores && (sr->select[0] || sr->select[1]);
   uint32_t* lh = reinterpret_cast<uint32_t*>(&lds[0][0]);  // 2 x 2048 bins; the key tiles are done
   if (sel) {
     for (int b = tid; b < 2 * kRadixBins; b += NW * kWave) lh[b] = 0;
@@ -846,7 +848,7 @@ __global__ __launch_bounds__(NW * kWave) void k_colsum(SeqDev* __restrict__ seqs
       float v = 0.f;
       if (m != 0) {
         v = acc[b] / denom;
-        if ((m == 1 || m == 2) && sel_m[m - 1]) atomicAdd(&lh[(m - 1) * kRadixBins + (clamp_bits(v) >> 20)], 1u);
+        if (sel && (m == 1 || m == 2) && sel_m[m - 1]) atomicAdd(&lh[(m - 1) * kRadixBins + (clamp_bits(v) >> 20)], 1u);
       }
       sc[j] = v;
     }
@@ -1002,7 +1004,7 @@ __global__ __launch_bounds__(kFewWaves * kWave) void k_few_colsum(SeqDev* __rest
                                                                   const float* __restrict__ logits,
                                                                   float* __restrict__ scores,
                                                                   uint32_t* __restrict__ hist,
-                                                                  uint32_t* __restrict__ ctr) {
+                                                                  uint32_t* __restrict__ ctr, ScoreTail tail) {
   constexpr int NT = kFewWaves * kWave, kPer = kRowTile / kFewCols;
   __shared__ float lb[kFewTotal];
   __shared__ float red[kFewWaves][kFewCols];
@@ -1014,7 +1016,7 @@ __global__ __launch_bounds__(kFewWaves * kWave) void k_few_colsum(SeqDev* __rest
   if (key0 >= sq.n_tokens || sq.n_cand == 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rows_g = n_rep * sq.q_len, rows = hkv * rows_g;
-  const bool sel = sq.select[0] || sq.select[1];
+  const bool sel = tail == kTailInScores && (sq.select[0] || sq.select[1]);
   if (sel)
     for (int b = tid; b < 2 * kRadixBins; b += NT) lh[b] = 0;
 
@@ -1078,7 +1080,7 @@ __global__ __launch_bounds__(kFewWaves * kWave) void k_few_colsum(SeqDev* __rest
     float v = 0.f;
     if (m != 0) {
       v = acc / (float)(n_rep * hkv * sq.q_len);
-      if ((m == 1 || m == 2) && (m == 1 ? sq.select[0] : sq.select[1]))
+      if (sel && (m == 1 || m == 2) && (m == 1 ? sq.select[0] : sq.select[1]))
         atomicAdd(&lh[(m - 1) * kRadixBins + (clamp_bits(v) >> 20)], 1u);
     }
     scores[sq.tok_off + j] = v;
@@ -1106,7 +1108,7 @@ apack_status launch_scores_t(const PrunePlan& pl, const DevPtrs& dp, const Inlin
     APACK_CHECK(launch_status("k_rowstats") == APACK_OK, APACK_E_HIP, "%s", apack_last_error());
     hipLaunchKernelGGL((k_colsum<T, D, NW, S>), dim3(nt), dim3(NW * kWave), 0, stream, dp.seqs, dp.tiles, dp.tags,
                        (const T*)q, q_hs, (const T*)k, k_hs, n_rep, hkv, scale_log2, dp.stats, dp.colpart, scores,
-                       dp.hist, dp.ctr);
+                       dp.hist, dp.ctr, score_tail(pl, false));
     APACK_CHECK(launch_status("k_colsum") == APACK_OK, APACK_E_HIP, "%s", apack_last_error());
   }
   return APACK_OK;
@@ -1140,7 +1142,7 @@ apack_status launch_few(const PrunePlan& pl, const DevPtrs& dp, const InlineCall
   if (st != APACK_OK) return st;
   hipLaunchKernelGGL(k_few_colsum, dim3((unsigned)pl.ftiles.size() * (kRowTile / kFewCols)), dim3(kFewWaves * kWave), 0,
                      stream, dp.seqs, dp.ftiles, dp.tags, n_rep, hkv, scale_log2, dp.stats, dp.logits, scores, dp.hist,
-                     dp.ctr);
+                     dp.ctr, score_tail(pl, true));
   return launch_status("k_few_colsum");
 }
 
@@ -1151,7 +1153,8 @@ apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCa
                           int32_t* kept, hipStream_t stream) {
   const int n_rep = hq / hkv;
   apack_status st;
-  if (dt == APACK_BF16 && pl.few)
+  const bool few = dt == APACK_BF16 && pl.few;
+  if (few)
     st = d == 64 ? launch_few<64>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream)
                  : launch_few<128>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
   else if (dt == APACK_BF16)
@@ -1162,7 +1165,7 @@ apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCa
                  : launch_scores_d<float, 128>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
   if (st != APACK_OK) return st;
   if (pl.total_tok == 0) return APACK_OK;
-  return launch_select(pl, dp, scores, kept, stream);
+  return launch_select(pl, dp, few, n_rep, hkv, scores, kept, stream);
 }
 
 }  // namespace apack

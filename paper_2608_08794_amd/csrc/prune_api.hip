@@ -116,6 +116,7 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
   pl.few = n_seq > 0;
   for (const SeqDev& sd : pl.seqs)
     pl.few &= n_rep * sd.q_len <= kFewRows && hkv * n_rep * sd.q_len <= kFewTotal;
+  for (const SeqDev& sd : pl.seqs) pl.max_planes = std::max<int>(pl.max_planes, hkv * sd.n_rg);
   const int64_t target = pl.few ? kFewTarget : APACK_TILE_TARGET;
   for (int s = 0; s < n_seq; ++s) {
     SeqDev& sd = pl.seqs[s];

@@ -21,6 +21,7 @@ constexpr int kKeyTile = APACK_KEY_TILE;       // keys per LDS stage of the scor
 constexpr int kRB = APACK_ROW_BLOCKS;          // 32-row query blocks held by one wave
 constexpr int kRowsPerWave = 32 * kRB;
 constexpr int kMaxWaves = 8;                   // waves per score workgroup
+constexpr int kSmallRows = 16384;              // rows of a sequence that one workgroup selects from
 #ifndef APACK_MAX_CHUNK
 #define APACK_MAX_CHUNK 4096
 #endif
@@ -108,11 +109,29 @@ struct PrunePlan {
   int64_t total_ctr = 0;    // arrival counters (zeroed by the upload)
   int waves = 1;
   bool any_select = false;
+  int max_planes = 0;       // most per-group partials of a key (general score kernels)
   bool few = false;         // every sequence has at most kFewRows query rows per key head
   // Workspace layout (byte offsets).
   size_t off_seqs = 0, off_tiles = 0, off_ftiles = 0, off_tags = 0, off_ctr = 0, blob_bytes = 0;
   size_t off_logits = 0, off_stats = 0, off_colpart = 0, off_hist = 0, off_cnt = 0, ws_bytes = 0;
 };
+
+// What the scores' last steps -- the sum over a key's per-group partials, the
+// count of the first radix digit -- are left to.  The score kernels do them in
+// their last workgroups to arrive: two round trips of atomics over the XCDs
+// (7 us of a 9390-row layer's 25).  Where one workgroup selects anyway it
+// counts the digit itself: calls at 1312 fp32 rows 41.2 us against 46.1, at
+// 9390 bf16 rows 66.0 against 66.9, with few query rows 42.9 against 45.1, at
+// 15564 rows 86.4 against 85.8 -- up to kDigitRows, or with few query rows.  It
+// sums too while the partials are few: at 9390 rows of four heads 67 us with
+// the sums there, so the line lies at kSumPartials of them.
+enum ScoreTail { kTailInScores = 0, kDigitInSelect = 1, kSumInSelect = 2 };
+constexpr int64_t kSumPartials = 16384, kDigitRows = 12288;
+// few: the call runs the few-row kernels, which store whole scores.
+inline ScoreTail score_tail(const PrunePlan& pl, bool few) {
+  if (pl.max_tokens > (few ? kSmallRows : kDigitRows)) return kTailInScores;
+  return !few && pl.max_planes * pl.max_tokens <= kSumPartials ? kSumInSelect : kDigitInSelect;
+}
 
 struct DevPtrs {
   SeqDev* seqs;
@@ -132,8 +151,8 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
 
 int64_t select_hist_words(int64_t n_seq);   // radix histogram words of n_seq sequences
 
-apack_status launch_select(const PrunePlan& pl, const DevPtrs& dp, float* scores, int32_t* kept,
-                           hipStream_t stream);
+apack_status launch_select(const PrunePlan& pl, const DevPtrs& dp, bool few, int n_rep, int hkv, float* scores,
+                           int32_t* kept, hipStream_t stream);
 
 apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCall& in, apack_dtype dt, int d, int hq, int hkv,
                           const void* q, int64_t q_hs, const void* k, int64_t k_hs, float* scores,

@@ -218,18 +218,28 @@ __global__ __launch_bounds__(kT) void k_keep_write(const SeqDev* __restrict__ se
 
 // ---------------------------------------------------------------------------
 // Short sequences (up to kSmallRows rows): one workgroup per sequence holds
-// every row's tag and score in registers and runs the last two digits with
-// LDS histograms, the threshold, and the ordered kept list, in one launch
+// every row's modality and score in LDS as one key and runs the radix digits
+// with LDS histograms, the threshold, and the ordered kept list, in one launch
 // instead of four.  Same rules as above: rows above the threshold, then the
 // first `need` rows equal to it in row order.
-// Wave w holds rows [1024 w, 1024 (w + 1)), lane l of it rows 1024 w + 64 u + l
-// (u < 16), so every load is coalesced; ranks among ties and output slots
-// come from ballots inside a wave and a scan over the 16 wave totals.
+// Wave w holds rows [64 nu w, 64 nu (w + 1)), nu = ceil(n / 1024), lane l of it
+// rows 64 (nu w + u) + l (u < nu), so every load is coalesced and every wave has
+// its share; ranks among ties and output slots come from ballots inside a wave
+// and a scan over the 16 wave totals.  Bound by latency: the loops over u are
+// loops, because the straight-line form (19.5 KB, each line of it fetched once)
+// took 11 us for 1312 rows as for 9390.  Whole calls at 1312 fp32 rows: 50.2 us
+// with it, 46.1 with loops, 41.2 with the scores' last steps here as well.
 // ---------------------------------------------------------------------------
 constexpr int kST = 1024;                 // threads
-constexpr int kSPer = 16;                 // rows per thread
+constexpr int kSPer = 16;                 // rows per thread, at most
 constexpr int kSWaves = kST / 64;
-constexpr int kSmallRows = kST * kSPer;
+static_assert(kSmallRows == kST * kSPer, "a thread holds at most kSPer rows");
+constexpr int kCopies = 4;                // copies of each bin of the first digit
+
+// Keys: the score's bits, with the top bit set for visual rows; two values
+// above every score's bits (clamp_bits) for the other rows.
+constexpr uint32_t kKeyKept = 0x7FFFFFFFu;   // not a candidate: always kept
+constexpr uint32_t kKeyNone = 0xFFFFFFFFu;   // past the sequence
 
 // Lanes below this one with their bit set in a wave-wide mask.
 __device__ __forceinline__ uint32_t below(uint64_t m) {
@@ -247,10 +257,14 @@ __device__ __forceinline__ uint32_t wave_base(const uint32_t* s, int w) {
   return b;
 }
 
+// SUM: the rows' scores are still to be summed from the per-group partials.
+template <bool SUM>
 __global__ __launch_bounds__(kST) void k_select_small(const SeqDev* __restrict__ seqs,
                                                       const uint8_t* __restrict__ tags,
-                                                      float* __restrict__ scores, int32_t* __restrict__ kept) {
-  __shared__ uint32_t lh[2 * kBins1];
+                                                      const float* __restrict__ colpart, int n_rep, int hkv, int first, float* __restrict__ scores,
+                                                      int32_t* __restrict__ kept) {
+  __shared__ __attribute__((aligned(16))) uint32_t lh[2 * kBins1 * kCopies];
+  __shared__ uint32_t keys[kSmallRows];
   __shared__ uint32_t sh[kST / 64];
   __shared__ uint32_t s_prefix[2], s_kk[2], s_thr[2], s_need[2], s_part[2];
   __shared__ uint32_t s_wave[2][kSWaves];
@@ -258,33 +272,68 @@ __global__ __launch_bounds__(kST) void k_select_small(const SeqDev* __restrict__
   const int n = (int)sq.n_tokens;
   if (n == 0) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row0 = wave * (64 * kSPer) + lane;   // row of u = 0; row(u) = row0 + 64 u
+  const int nu = (n + kST - 1) / kST;
+  const int row0 = wave * (64 * nu) + lane;   // row of u = 0; row(u) = row0 + 64 u
   const uint8_t* tg = tags + sq.tag_off;
-  uint32_t bits[kSPer];
-  uint8_t mt[kSPer];
+  float* sc = scores + sq.tok_off;
+  uint32_t* key = keys + wave * (64 * kSPer) + lane;   // key of u at key[64 u]
   // Every tag and score load is issued before the first is used: a row
   // past the sequence re-reads its last row, and a score is kept only for a
-  // candidate row, so no load waits behind another (a score load behind a
-  // test of its tag had waited for the tag first, one row at a time).
+  // candidate row, so no load waits behind another.
+  uint8_t mt[kSPer];
+  float x[kSPer];
+  const bool sum = SUM && sq.n_cand != 0;
+  const int planes = sum ? hkv * sq.n_rg : 1;
+  const float* src = sum ? colpart + sq.colpart_off : sc;
 #pragma unroll
-  for (int u = 0; u < kSPer; ++u) {
-    const int i = min(row0 + 64 * u, n - 1);
-    mt[u] = tg[i];
-    bits[u] = __float_as_uint(scores[sq.tok_off + i]);
-  }
+  for (int u0 = 0; u0 < kSPer; u0 += 4)
+    if (u0 < nu) {
 #pragma unroll
-  for (int u = 0; u < kSPer; ++u) {
-    const int i = row0 + 64 * u;
-    if (i >= n) mt[u] = 0xFF;
-    bits[u] = (mt[u] == 1 || mt[u] == 2) ? clamp_bits(__uint_as_float(bits[u])) : 0u;
-  }
-  // Scores of sequences with candidates are written by the score kernels; a
-  // sequence without any has no score workgroups.
-  if (sq.n_cand == 0) {
+      for (int u = u0; u < u0 + 4; ++u) {
+        const int i = min(row0 + 64 * u, n - 1);
+        mt[u] = tg[i];
+        x[u] = src[i];
+      }
+    }
+  // The sum of the per-group partials in their order.
+#pragma unroll 1
+  for (int p = 1; p < planes; ++p) {
+    src += n;
+    float y[kSPer];
 #pragma unroll
-    for (int u = 0; u < kSPer; ++u)
-      if (mt[u] == 0) scores[sq.tok_off + row0 + 64 * u] = 0.f;
+    for (int u0 = 0; u0 < kSPer; u0 += 4)
+      if (u0 < nu) {
+#pragma unroll
+        for (int u = u0; u < u0 + 4; ++u) y[u] = src[min(row0 + 64 * u, n - 1)];
+      }
+#pragma unroll
+    for (int u0 = 0; u0 < kSPer; u0 += 4)
+      if (u0 < nu) {
+#pragma unroll
+        for (int u = u0; u < u0 + 4; ++u) x[u] += y[u];
+      }
   }
+  // Keys, in bitwise form (no branches); the scores, where they are formed
+  // here, are I_j = sum / (Hq * T) of a candidate and 0 of another row.
+  const float denom = (float)(n_rep * hkv * sq.q_len);
+#pragma unroll
+  for (int u0 = 0; u0 < kSPer; u0 += 4)
+    if (u0 < nu) {
+#pragma unroll
+      for (int u = u0; u < u0 + 4; ++u) {
+        const uint32_t other = mt[u] == 0 ? ~0u : 0u;   // all ones for a non-candidate
+        const uint32_t past = u >= nu || row0 + 64 * u >= n ? ~0u : 0u;
+        if (SUM) {
+          x[u] = __uint_as_float(__float_as_uint(x[u] / denom) & ~other);
+          if (sum && !past) sc[row0 + 64 * u] = x[u];
+        }
+        const uint32_t b = clamp_bits(x[u]) | ((uint32_t)(mt[u] & 2) << 30);
+        key[64 * u] = ((b & ~other) | (kKeyKept & other)) | past;
+      }
+    }
+  // A sequence without candidates has no score workgroups.
+  if (sq.n_cand == 0)
+    for (int i = tid; i < n; i += kST) sc[i] = 0.f;
   if (tid < 2) {
     s_prefix[tid] = tid ? sq.prefix[1] : sq.prefix[0];
     s_kk[tid] = tid ? sq.kk[1] : sq.kk[0];
@@ -292,18 +341,30 @@ __global__ __launch_bounds__(kST) void k_select_small(const SeqDev* __restrict__
     s_need[tid] = (uint32_t)(tid ? sq.need[1] : sq.need[0]);
     s_part[tid] = 0;   // a modality that does not select keeps all or none of its rows
   }
-  __syncthreads();
   const bool act0 = sq.select[0] != 0, act1 = sq.select[1] != 0;
-  for (int pass = 1; pass <= 2 && (act0 || act1); ++pass) {
-    for (int b = tid; b < 2 * kBins1; b += kST) lh[b] = 0;
+  // The scores of a layer share few values of the first digit (sign, exponent
+  // and three bits), and atomics of a wave to one LDS word are served one
+  // after another, so its bins have four copies, a lane taking one of them.
+#pragma unroll 1
+  for (int pass = first; pass <= 2 && (act0 || act1); ++pass) {
+    const int cps = pass == 0 ? kCopies : 1, my = lane & (cps - 1);
+    for (int b = tid; b < 2 * kBins1 * cps / 4; b += kST) reinterpret_cast<uint4*>(lh)[b] = make_uint4(0, 0, 0, 0);
     __syncthreads();
-    const uint32_t pre0 = s_prefix[0], pre1 = s_prefix[1];
+    // Rows whose higher digits match their modality's prefix; those of the
+    // other rows' keys, and a prefix of all ones, match nothing.
+    const int hi = pass == 0 ? 31 : pass == 1 ? 20 : 9, lo = pass == 0 ? 20 : pass == 1 ? 9 : 0;
+    const uint32_t mask = pass == 2 ? 0x1FFu : 0x7FFu;
+    const uint32_t pre0 = act0 ? s_prefix[0] : ~0u, pre1 = act1 ? s_prefix[1] : ~0u;
+#pragma unroll 1
+    for (int u0 = 0; u0 < nu; u0 += 4) {
+      uint32_t kx[4];
 #pragma unroll
-    for (int u = 0; u < kSPer; ++u) {
-      const bool a = mt[u] == 1 && act0, v = mt[u] == 2 && act1;
-      if (!a && !v) continue;
-      uint32_t d;
-      if (digit_of(bits[u], pass, a ? pre0 : pre1, d)) atomicAdd(&lh[(a ? 0 : kBins1) + d], 1u);
+      for (int j = 0; j < 4; ++j) kx[j] = key[64 * (u0 + j)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t m = kx[j] >> 31, b = kx[j] & 0x7FFFFFFFu;
+        if (b >> hi == (m ? pre1 : pre0) && b != kKeyKept) atomicAdd(&lh[(m * kBins1 + ((b >> lo) & mask)) * cps + my], 1u);
+      }
     }
     __syncthreads();
     // Bin holding the kk-th largest value of each modality: thread t covers
@@ -314,8 +375,16 @@ __global__ __launch_bounds__(kST) void k_select_small(const SeqDev* __restrict__
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int b = nb - 1 - (tid * 2 + j);
-      c[0][j] = b >= 0 ? lh[b] : 0u;
-      c[1][j] = b >= 0 ? lh[kBins1 + b] : 0u;
+#pragma unroll
+      for (int m = 0; m < 2; ++m) {
+        const int e = m * kBins1 + max(b, 0);
+        uint32_t v = lh[e];
+        if (pass == 0) {
+          const uint4 y = reinterpret_cast<const uint4*>(lh)[e];
+          v = (y.x + y.y) + (y.z + y.w);
+        }
+        c[m][j] = b >= 0 ? v : 0u;
+      }
       sum += c[0][j] | (c[1][j] << 16);
     }
     // Ranks and prefixes are read before the scan, whose barriers keep every
@@ -323,64 +392,70 @@ __global__ __launch_bounds__(kST) void k_select_small(const SeqDev* __restrict__
     const uint32_t kk[2] = {s_kk[0], s_kk[1]}, pf[2] = {s_prefix[0], s_prefix[1]};
     uint32_t total;
     const uint32_t incl = block_scan<kST>(sum, sh, total);
+#pragma unroll
     for (int m = 0; m < 2; ++m) {
       if (!(m == 0 ? act0 : act1)) continue;
       const uint32_t in_m = (incl >> (16 * m)) & 0xFFFFu, s_m = c[m][0] + c[m][1];
       uint32_t before = in_m - s_m;
       if (before < kk[m] && in_m >= kk[m]) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          if (before < kk[m] && before + c[m][j] >= kk[m]) {
-            const uint32_t b = (uint32_t)(nb - 1 - (tid * 2 + j));
-            const uint32_t prefix = (pf[m] << (pass == 1 ? 11 : 9)) | b;
-            s_prefix[m] = prefix;
-            s_kk[m] = kk[m] - before;
-            if (pass == 2) {
-              s_thr[m] = prefix;
-              s_need[m] = kk[m] - before;
-              s_part[m] = kk[m] - before != c[m][j] ? 1u : 0u;
-            }
-          }
-          before += c[m][j];
+        const int j = before + c[m][0] >= kk[m] ? 0 : 1;
+        if (j) before += c[m][0];
+        const uint32_t cj = j ? c[m][1] : c[m][0];
+        const uint32_t prefix = (pf[m] << (pass == 2 ? 9 : 11)) | (uint32_t)(nb - 1 - (tid * 2 + j));
+        s_prefix[m] = prefix;
+        s_kk[m] = kk[m] - before;
+        if (pass == 2) {
+          s_thr[m] = prefix;
+          s_need[m] = kk[m] - before;
+          s_part[m] = kk[m] - before != cj ? 1u : 0u;
         }
       }
     }
     __syncthreads();
   }
+  __syncthreads();
   // Kept: every non-candidate row, every candidate above its modality's
   // threshold and the first `need` rows equal to it in row order.  When
   // every row equal to the threshold is kept (the usual case), no rank is
-  // formed.  The tests are bitwise (no short-circuit), so they compile to
-  // straight-line compares rather than nested branches.
+  // formed.
   const uint32_t thr0 = s_thr[0], thr1 = s_thr[1], need0 = s_need[0], need1 = s_need[1];
   uint32_t keepbits = 0, nk = 0;
   if (!(s_part[0] | s_part[1])) {
+#pragma unroll 1
+    for (int u0 = 0; u0 < nu; u0 += 4) {
+      uint32_t kx[4];
 #pragma unroll
-    for (int u = 0; u < kSPer; ++u) {
-      const bool kp = (mt[u] == 0) | ((mt[u] == 1) & (bits[u] >= thr0)) | ((mt[u] == 2) & (bits[u] >= thr1));
-      keepbits |= (uint32_t)kp << u;
-      nk += __popcll(__ballot(kp));
+      for (int j = 0; j < 4; ++j) kx[j] = key[64 * (u0 + j)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t thr = kx[j] >> 31 ? thr1 : thr0, b = kx[j] & 0x7FFFFFFFu;
+        const bool kp = (kx[j] == kKeyKept) | ((kx[j] != kKeyNone) & (b >= thr));
+        keepbits |= (uint32_t)kp << (u0 + j);
+        nk += __popcll(__ballot(kp));
+      }
     }
   } else {
     // Ranks of the rows equal to each threshold: wave totals, then within
     // the wave by u and by lane.
     uint32_t ta = 0, tv = 0;
-#pragma unroll
-    for (int u = 0; u < kSPer; ++u) {
-      ta += __popcll(__ballot((mt[u] == 1) & (bits[u] == thr0)));
-      tv += __popcll(__ballot((mt[u] == 2) & (bits[u] == thr1)));
+#pragma unroll 1
+    for (int u = 0; u < nu; ++u) {
+      const uint32_t kx = key[64 * u];
+      ta += __popcll(__ballot(kx == thr0 && kx != kKeyNone));
+      tv += __popcll(__ballot(kx == (thr1 | 0x80000000u) && kx != kKeyNone));
     }
     if (lane == 0) {
       s_wave[0][wave] = ta;
       s_wave[1][wave] = tv;
     }
     uint32_t ra = wave_base(s_wave[0], wave), rv = wave_base(s_wave[1], wave);
-#pragma unroll
-    for (int u = 0; u < kSPer; ++u) {
-      const bool ea = (mt[u] == 1) & (bits[u] == thr0), ev = (mt[u] == 2) & (bits[u] == thr1);
+#pragma unroll 1
+    for (int u = 0; u < nu; ++u) {
+      const uint32_t kx = key[64 * u], b = kx & 0x7FFFFFFFu;
+      const bool ea = kx == thr0 && kx != kKeyNone, ev = kx == (thr1 | 0x80000000u) && kx != kKeyNone;
       const uint64_t ma = __ballot(ea), mv = __ballot(ev);
-      const int kp = (int)(mt[u] == 0) | ((int)(mt[u] == 1) & (int)(bits[u] > thr0)) |
-                     ((int)(mt[u] == 2) & (int)(bits[u] > thr1)) | ((int)ea & (int)(ra + below(ma) < need0)) |
+      const bool above = (kx != kKeyNone) && (b > (kx >> 31 ? thr1 : thr0));
+      const int kp = (int)(kx == kKeyKept) | (int)above | ((int)ea & (int)(ra + below(ma) < need0)) |
                      ((int)ev & (int)(rv + below(mv) < need1));
       ra += __popcll(ma);
       rv += __popcll(mv);
@@ -392,8 +467,8 @@ __global__ __launch_bounds__(kST) void k_select_small(const SeqDev* __restrict__
   if (lane == 0) s_wave[0][wave] = nk;
   uint32_t pos = wave_base(s_wave[0], wave);
   int32_t* out = kept + sq.out_off;
-#pragma unroll
-  for (int u = 0; u < kSPer; ++u) {
+#pragma unroll 1
+  for (int u = 0; u < nu; ++u) {
     const bool kp = (keepbits >> u) & 1u;
     const uint64_t mk = __ballot(kp);
     const uint32_t at = pos + below(mk);
@@ -406,14 +481,17 @@ __global__ __launch_bounds__(kST) void k_select_small(const SeqDev* __restrict__
 
 int64_t select_hist_words(int64_t n_seq) { return n_seq * 2 * kRadixBins; }
 
-apack_status launch_select(const PrunePlan& pl, const DevPtrs& dp, float* scores, int32_t* kept,
-                           hipStream_t stream) {
+apack_status launch_select(const PrunePlan& pl, const DevPtrs& dp, bool few, int n_rep, int hkv, float* scores,
+                           int32_t* kept, hipStream_t stream) {
   const int nf = (int)pl.ftiles.size();
   if (nf == 0) return APACK_OK;
   apack_status st;
-  // The scores and the first digit come from k_colsum, earlier on this stream.
+  // The scores and the first digit come from the score kernels, earlier on
+  // this stream, or from k_select_small (ScoreTail).
   if (pl.max_tokens <= kSmallRows) {
-    hipLaunchKernelGGL(k_select_small, dim3((unsigned)pl.seqs.size()), dim3(kST), 0, stream, dp.seqs, dp.tags,
+    const ScoreTail tail = score_tail(pl, few);
+    hipLaunchKernelGGL((tail == kSumInSelect ? k_select_small<true> : k_select_small<false>), dim3((unsigned)pl.seqs.size()), dim3(kST),
+                       0, stream, dp.seqs, dp.tags, dp.colpart, n_rep, hkv, tail == kTailInScores ? 1 : 0,
                        scores, kept);
     return launch_status("k_select_small");
   }

@@ -654,6 +654,17 @@ def test_few_query_rows_long_sequence():
     _parity(_synthetic("bf16", 28, 4, 128, specs, seed=78))
 
 
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 4097, 8192, 8193, 12288, 12289, 16384])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_select_of_short_sequences_at_its_edges(dtype, n):
+    """One, two and five rows a thread and all sixteen; partials summed by the
+    selection (up to 8192 rows of two heads) or by the score kernels, the
+    first digit counted by either (up to 12288 rows)."""
+    a = max(1, n // 5)
+    spans = [(0, a, A_)] if n < 8 else [(0, a, A_), (a + 3, n - a - 5, V_)]
+    _parity(_synthetic(dtype, 8, 2, 64, [(spans, n, 8, (0.6, 0.3))], seed=80))
+
+
 def test_few_query_rows_ties_and_one_row_more():
     """Duplicate keys give bitwise-equal scores, and 20 rows per key head
     (the general passes) agree with the mean of five single ones."""
