@@ -388,6 +388,14 @@ __device__ __forceinline__ void load_mask(const uint8_t* tg, int64_t key_begin, 
   }
 }
 
+// 32-key blocks of a tile: all in bf16, where chunks are whole tiles; in fp32
+// the chunk's last tile may be short.
+template <class T>
+__device__ __forceinline__ int tile_blocks(int64_t t0, int64_t key_end) {
+  constexpr int NKB = kKeyTile / kKeyBlock;
+  return sizeof(T) == 2 ? NKB : (int)min((int64_t)NKB, (key_end - t0 + kKeyBlock - 1) / kKeyBlock);
+}
+
 template <class T, int D, int NW, int S>
 __global__ __launch_bounds__(NW * kWave) void k_rowstats(const InlineCall in, SeqDev* __restrict__ seqs,
                                                          TileDev* __restrict__ tiles,
@@ -462,13 +470,14 @@ __global__ __launch_bounds__(NW * kWave) void k_rowstats(const InlineCall in, Se
     // for a second loop body.)
     constexpr bool kUseRef = sizeof(T) == 2;
     bool ref = false;
-    auto tile_body = [&](auto exact_body_tag, const char* tile, const float* lm) {
+    auto tile_body = [&](auto exact_body_tag, const char* tile, const float* lm, int nb) {
       constexpr bool kExact = decltype(exact_body_tag)::value;
       if constexpr (!kPrefetchFrags<T>) {
         // Fragments read as they are used, and each block's logits reduced
         // right after its MFMAs (the other wave of the SIMD fills the pipes).
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
+          if (kb >= nb) break;
           f32x16 cur[kRB];
           cur[0] = mask_init(lm, kb, lane);
 #pragma unroll
@@ -547,10 +556,11 @@ __global__ __launch_bounds__(NW * kWave) void k_rowstats(const InlineCall in, Se
             }
           }
         }
+        const int nb = tile_blocks<T>(t0, key_end);
         if (ref)
-          tile_body(std::false_type{}, lds[buf], lm);
+          tile_body(std::false_type{}, lds[buf], lm, nb);
         else
-          tile_body(std::true_type{}, lds[buf], lm);
+          tile_body(std::true_type{}, lds[buf], lm, nb);
       }
     }
     if (kPrefetchFrags<T> && active) {
@@ -735,8 +745,10 @@ __global__ __launch_bounds__(NW * kWave) void k_colsum(SeqDev* __restrict__ seqs
     if (active) {
       const int slot = it % 3, prev_slot = (it + 2) % 3;
       if constexpr (!kPrefetchFrags<T>) {
+        const int nb = tile_blocks<T>(t0, key_end);
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
+          if (kb >= nb) break;
           f32x16 cur[kRB];
 #pragma unroll
           for (int rb = 0; rb < kRB; ++rb) cur[rb] = f32x16{};

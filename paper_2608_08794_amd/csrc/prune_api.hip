@@ -11,7 +11,7 @@
 namespace apack {
 
 apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, int32_t hkv, int32_t d,
-                              PrunePlan& pl) {
+                              apack_dtype dtype, PrunePlan& pl) {
   APACK_CHECK(n_seq >= 0, APACK_E_ARG, "n_seq must be >= 0 (got %d)", n_seq);
   APACK_CHECK(n_seq == 0 || seqs, APACK_E_ARG, "seqs is NULL");
   APACK_CHECK(hq > 0 && hkv > 0 && hq % hkv == 0, APACK_E_SHAPE,
@@ -117,13 +117,24 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
   for (const SeqDev& sd : pl.seqs)
     pl.few &= n_rep * sd.q_len <= kFewRows && hkv * n_rep * sd.q_len <= kFewTotal;
   for (const SeqDev& sd : pl.seqs) pl.max_planes = std::max<int>(pl.max_planes, hkv * sd.n_rg);
+  // In fp32 the matrix units bound the score kernels, so a chunk is any number
+  // of 32-key blocks and the work spreads over more compute units; in bf16,
+  // where the per-workgroup part outweighs a block, whole tiles.  fp32 calls at
+  // 1312 rows (8 heads over 2, D = 64) 41.2 us with tiles, 32.5 with blocks;
+  // 9454 rows (16 over 2) 121.8 and 110.7; 9390 rows (28 over 4) 190.5 and
+  // 148.7.  bf16 at 9454 rows: 57.0 and 59.4.  The workspace covers either.
+  int64_t fine_tiles = 0, fine_stats = 0, fine_ctr = 0;
+  const int64_t unit = dtype == APACK_F32 ? kKeyBlock : kKeyTile;
   const int64_t target = pl.few ? kFewTarget : APACK_TILE_TARGET;
   for (int s = 0; s < n_seq; ++s) {
     SeqDev& sd = pl.seqs[s];
     if (sd.n_cand == 0) continue;
-    int64_t ch = (weighted + target - 1) / target;
-    ch = (ch + kKeyTile - 1) / kKeyTile * kKeyTile;
-    ch = std::max<int64_t>(kKeyTile, std::min<int64_t>(ch, kMaxChunk));
+    const int64_t want = (weighted + target - 1) / target;
+    auto chunk_of = [&](int64_t u) { return std::max<int64_t>(u, std::min<int64_t>((want + u - 1) / u * u, kMaxChunk)); };
+    const int64_t ch = chunk_of(unit), fine = (sd.n_tokens + chunk_of(kKeyBlock) - 1) / chunk_of(kKeyBlock);
+    fine_tiles += (int64_t)hkv * sd.n_rg * fine;
+    fine_stats += (int64_t)hkv * sd.rows_pad * fine;
+    fine_ctr += fine + 1;
     sd.chunk = (int32_t)ch;
     sd.n_chunks = (int32_t)((sd.n_tokens + ch - 1) / ch);
     sd.stats_off = stats;
@@ -148,29 +159,34 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
   pl.total_stats = stats;
   pl.total_colpart = colpart;
   pl.total_kept = kept;
-  // Workspace layout.
-  Carver c(nullptr);
-  c.take<SeqDev>(pl.seqs.size());
-  pl.off_tiles = c.used;
-  c.take<TileDev>(pl.tiles.size());
-  pl.off_ftiles = c.used;
-  c.take<FTileDev>(pl.ftiles.size());
-  pl.off_tags = c.used;
-  c.take<uint8_t>(pl.total_tok);
-  pl.off_ctr = c.used;
-  c.take<uint32_t>(pl.total_ctr);
-  pl.blob_bytes = c.used;
-  pl.off_stats = c.used;
-  c.take<float2>(pl.total_stats);
-  pl.off_colpart = c.used;
-  c.take<float>(pl.total_colpart);
-  pl.off_logits = c.used;
-  c.take<float>(pl.total_logits);
-  pl.off_hist = c.used;
-  c.take<uint32_t>(pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : 0);
-  pl.off_cnt = c.used;
-  c.take<uint32_t>(3 * pl.ftiles.size());
-  pl.ws_bytes = std::max<size_t>(c.used, kAlign);
+  // Workspace layout; its size is that of the finer chunks, whatever the dtype.
+  auto layout = [&](PrunePlan& p, int64_t n_tiles, int64_t n_stats, int64_t n_ctr) {
+    Carver c(nullptr);
+    c.take<SeqDev>(pl.seqs.size());
+    p.off_tiles = c.used;
+    c.take<TileDev>(n_tiles);
+    p.off_ftiles = c.used;
+    c.take<FTileDev>(pl.ftiles.size());
+    p.off_tags = c.used;
+    c.take<uint8_t>(pl.total_tok);
+    p.off_ctr = c.used;
+    c.take<uint32_t>(n_ctr);
+    p.blob_bytes = c.used;
+    p.off_stats = c.used;
+    c.take<float2>(n_stats);
+    p.off_colpart = c.used;
+    c.take<float>(pl.total_colpart);
+    p.off_logits = c.used;
+    c.take<float>(pl.total_logits);
+    p.off_hist = c.used;
+    c.take<uint32_t>(pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : 0);
+    p.off_cnt = c.used;
+    c.take<uint32_t>(3 * pl.ftiles.size());
+    return std::max<size_t>(c.used, kAlign);
+  };
+  PrunePlan finest;
+  pl.ws_bytes = layout(finest, fine_tiles, fine_stats, fine_ctr);
+  pl.ws_bytes = std::max(pl.ws_bytes, layout(pl, (int64_t)pl.tiles.size(), pl.total_stats, pl.total_ctr));
   return APACK_OK;
 }
 
@@ -184,7 +200,7 @@ apack_status apack_prune_layer_query(int32_t n_seq, const apack_seq* seqs, int32
                                      int32_t d, int64_t* n_kept, size_t* workspace_bytes) {
   clear_error();
   PrunePlan pl;
-  apack_status st = build_prune_plan(n_seq, seqs, hq, hkv, d, pl);
+  apack_status st = build_prune_plan(n_seq, seqs, hq, hkv, d, APACK_BF16, pl);
   if (st != APACK_OK) return st;
   if (n_kept)
     for (int s = 0; s < n_seq; ++s) n_kept[s] = pl.n_kept[s];
@@ -200,7 +216,7 @@ apack_status apack_prune_layer(int32_t n_seq, const apack_seq* seqs, apack_dtype
   clear_error();
   APACK_CHECK(dtype_ok(dtype), APACK_E_DTYPE, "unknown dtype %d", (int)dtype);
   PrunePlan pl;
-  apack_status st = build_prune_plan(n_seq, seqs, hq, hkv, d, pl);
+  apack_status st = build_prune_plan(n_seq, seqs, hq, hkv, d, dtype, pl);
   if (st != APACK_OK) return st;
   const size_t es = dtype_size(dtype);
   APACK_CHECK(q_rows >= 0 && k_rows >= 0, APACK_E_SHAPE, "negative row count");

@@ -18,6 +18,7 @@ namespace apack {
 #define APACK_TILE_TARGET 256
 #endif
 constexpr int kKeyTile = APACK_KEY_TILE;       // keys per LDS stage of the score kernels
+constexpr int kKeyBlock = 32;                  // keys per MFMA block
 constexpr int kRB = APACK_ROW_BLOCKS;          // 32-row query blocks held by one wave
 constexpr int kRowsPerWave = 32 * kRB;
 constexpr int kMaxWaves = 8;                   // waves per score workgroup
@@ -50,7 +51,7 @@ struct SeqDev {
   int32_t n_rg;         // query-row groups per KV head
   int32_t rows_per_rg;  // rows per group (multiple of 64)
   int32_t rows_pad;     // n_rg * rows_per_rg
-  int32_t chunk;        // keys per score workgroup (multiple of kKeyTile)
+  int32_t chunk;        // keys per score workgroup (whole tiles; in fp32 whole blocks)
   int32_t n_chunks;
   int32_t n_cand;
   int32_t k_sel[2];     // keep count per modality (audio, visual)
@@ -147,7 +148,7 @@ struct DevPtrs {
 };
 
 apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, int32_t hkv, int32_t d,
-                              PrunePlan& plan);
+                              apack_dtype dtype, PrunePlan& plan);
 
 int64_t select_hist_words(int64_t n_seq);   // radix histogram words of n_seq sequences
 

@@ -654,6 +654,15 @@ def test_few_query_rows_long_sequence():
     _parity(_synthetic("bf16", 28, 4, 128, specs, seed=78))
 
 
+@pytest.mark.parametrize("n", [31, 32, 33, 129, 4000, 9000])
+@pytest.mark.parametrize("hq,hkv,d,q_len", [(8, 2, 64, 8), (14, 2, 128, 64), (16, 2, 128, 64), (4, 4, 128, 3)])
+def test_fp32_chunks_of_whole_blocks(hq, hkv, d, q_len, n):
+    """fp32 chunks of 32 keys up to several tiles and a short one, at four,
+    seven and eight waves and with few query rows."""
+    a = max(1, n // 4)
+    _parity(_synthetic("f32", hq, hkv, d, [([(0, a, A_), (a, n - a - 1, V_)], n, q_len, (0.6, 0.3))], seed=81))
+
+
 @pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 4097, 8192, 8193, 12288, 12289, 16384])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_select_of_short_sequences_at_its_edges(dtype, n):
