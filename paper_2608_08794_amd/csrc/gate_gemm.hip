@@ -2,7 +2,7 @@
 // pass"; the fine-pass term of Eq. 2): for every visual token i of a clip
 // whose gate fired, max_j x_A[j] . x_V[i] / |x_A[j]|, from C = X_A X_V^T on
 // bf16 MFMA with fp32 accumulation.  This is the kernel for bf16 inputs
-// whose dim is a multiple of 64; k_gate_gemm in dynamics.hip covers the rest.
+// whose dim is a multiple of 64; k_gate_gemm_any below covers the rest.
 //
 // Each workgroup owns a tile of 32 BI x 256 (audio rows x visual columns; BI
 // is 8 unless fewer rows fill the chip better, see gate_gemm256_tiles); its
