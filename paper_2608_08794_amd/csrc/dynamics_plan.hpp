@@ -51,6 +51,10 @@ struct GemmTileDev {
   int32_t clip, m0, n0, pad;  // audio row block, visual column block
 };
 
+// First element of a row, in 64 bits: a long clip passes 2^31 elements
+// (visual row 131072 at dim 16384).
+__host__ __device__ __forceinline__ int64_t row_start(int64_t row, int dim) { return row * dim; }
+
 struct DynPlan {
   std::vector<ClipDev> clips;
   std::vector<FrameDev> frames;      // one entry per frame of every clip

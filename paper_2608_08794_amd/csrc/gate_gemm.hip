@@ -180,8 +180,8 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
     for (int j = 0; j < kBJ; ++j) acc[i][j] = f32x4{};
 
   const int n_k = dim / kK;
-  const char* base_a = reinterpret_cast<const char*>(A + tl.m0 * dim);
-  const char* base_b = reinterpret_cast<const char*>(B + tl.n0 * dim);
+  const char* base_a = reinterpret_cast<const char*>(A + row_start(tl.m0, dim));
+  const char* base_b = reinterpret_cast<const char*>(B + row_start(tl.n0, dim));
   // Load l of this wave's share of a stage: audio rows first.
   int at[kLoads];         // LDS byte of the load within the stage
   uint32_t off[kLoads];   // this lane's offset from its base
@@ -389,8 +389,8 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 #pragma unroll
   for (int i = 0; i < kUnits / KS; ++i) {
     const int r = (tid >> 2) + i * (kWaves * 16);
-    row[i] = r < kAnyM ? xa + (c.aud_off + min(tl.m0 + (int64_t)r, n_a - 1)) * dim
-                       : xv + (c.vis_off + min(tl.n0 + (int64_t)(r - kAnyM), n_v - 1)) * dim;
+    row[i] = r < kAnyM ? xa + row_start(c.aud_off + min(tl.m0 + (int64_t)r, n_a - 1), dim)
+                       : xv + row_start(c.vis_off + min(tl.n0 + (int64_t)(r - kAnyM), n_v - 1), dim);
   }
   Unit<T> raw[kUnits];
   auto gload = [&](int k0) {

@@ -405,3 +405,33 @@ def test_gate_gemm_tile_heights(audio, visual, dim):
     # 2^-24 of |x| |y|, three times over the range of d.
     tol = 4.0 * (dim // 32 + 4) * 2.0 ** -24 / (d.max() - d.min()) + 2.0 ** -23
     np.testing.assert_allclose(got, want, rtol=0, atol=tol)
+
+
+def test_gate_gemm_past_2_to_the_31_elements():
+    """A clip whose last gate GEMM tiles start past 2^31 elements of the
+    visual rows (131072 rows of 16384): frame scores 1 - d_hat (gamma 0)
+    against torch, tile by tile."""
+    import paper_2608_08794_amd as A
+    dim, per_frame, frames, audio = 16384, 256, 514, 40
+    n = frames * per_frame
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    xv = torch.empty((n, dim), dtype=torch.bfloat16, device="cuda")
+    for r in range(0, n, 8192):
+        xv[r:r + 8192] = torch.randn((min(8192, n - r), dim), generator=gen, device="cuda")
+    xa = torch.randn((audio, dim), generator=gen, device="cuda").bfloat16()
+    xv[-per_frame:] = xa[0]   # the last frame repeats an audio row: the smallest distance
+    clip = dict(n_frames=frames, per_frame=per_frame, n_audio=audio, n_query=1, vis_off=0, aud_off=0, qry_off=0)
+    out = A.apack_score_dynamics(xv, xa, xa[:1].clone(), [clip], {"alignment": "av_cosine", "gamma": 0.0, "r_pre": 0.01})
+    got = out["score"].cpu().double()
+    an = xa.double()
+    an /= an.norm(dim=1, keepdim=True)
+    cos = []
+    for r in range(0, n, 4096):
+        x = xv[r:r + 4096].double()
+        cos.append((x @ an.T).amax(dim=1) / x.norm(dim=1))
+    d = 1.0 - torch.cat(cos).view(frames, per_frame).mean(dim=1).cpu()
+    want = 1.0 - (d - d.min()) / (d.max() - d.min())
+    # dim / 32 partial sums and the scaling round by at most 2^-24 of |x| |y|,
+    # three times over the range of d.
+    tol = 4.0 * (dim // 32 + 4) * 2.0 ** -24 / float(d.max() - d.min()) + 2.0 ** -23
+    np.testing.assert_allclose(got.numpy(), want.numpy(), rtol=0, atol=tol)
