@@ -1842,7 +1842,7 @@ apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& 
     constexpr bool kBf16 = std::is_same<T, bf16_t>::value;
     st = pl.use256 ? launch_gate_gemm256(dp.clips, dp.gemm, pl.gemm_tiles, pl.gemm256_bi, dim, (const uint16_t*)xv,
                                          (const uint16_t*)xa, dp.na, dp.maxkey, s)
-                   : launch_gate_gemm_any(dp.clips, dp.gemm, pl.gemm_tiles, dim, kBf16, xv, xa, dp.na, dp.maxkey, s);
+                   : launch_gate_gemm_any(dp.clips, dp.gemm, pl.gemm_tiles, dim, kBf16, xv, xa, dp.nv, dp.na, dp.maxkey, s);
     if (st != APACK_OK) return st;
   }
   hipLaunchKernelGGL(k_plan, dim3(nc), dim3(kPlanBlk), 0, s, dp.clips, prm, dp.cka, dp.band_v, dp.vq, dp.qq, dp.rv,

@@ -121,10 +121,10 @@ apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles,
                                  const uint16_t* xv, const uint16_t* xa, const double* na, uint32_t* maxkey,
                                  hipStream_t stream);
 std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips, int* bi);
-// The same for fp32 inputs (split into bf16 parts) and for bf16 inputs of
-// any other dim.
+// The same for fp32 inputs (scaled by their norms nv, na and split into bf16
+// parts) and for bf16 inputs of any other dim.
 apack_status launch_gate_gemm_any(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int dim, bool bf16,
-                                  const void* xv, const void* xa, const double* na, uint32_t* maxkey,
+                                  const void* xv, const void* xa, const double* nv, const double* na, uint32_t* maxkey,
                                   hipStream_t stream);
 std::vector<GemmTileDev> gate_gemm_any_tiles(const std::vector<ClipDev>& clips);
 constexpr int kGemm256K = 64;   // dim must be a multiple of this for the 256-tile kernel

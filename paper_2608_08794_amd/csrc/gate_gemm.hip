@@ -117,15 +117,25 @@ __device__ __forceinline__ bf16x8 lds_frag(const char* lds, int row, int ks, int
   return *reinterpret_cast<const bf16x8*>(lds + row * kRowB + c * 16);
 }
 
+// e such that 2^-e takes a row of squared norm nn to a norm in [1, 2), kept
+// where 2^e and 2^-e are normal floats (a row of smaller or larger norm comes
+// within 2^-23 and 2^8 of that); an all-zero row stays all zero.
+__device__ __forceinline__ int row_exponent(double nn) {
+  const int e = ((int)((uint64_t)__double_as_longlong(nn) >> 52 & 0x7FF) - 1023) >> 1;
+  return min(max(e, -126), 126);
+}
+__device__ __forceinline__ float exp2_int(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
+
 // Inverse norms of audio rows m0 .. m0 + M - 1 (0 for a zero row, -inf past
-// the clip's audio, so those rows never win).
-template <int M>
+// the clip's audio, so those rows never win), of the scaled rows if SCALED.
+template <int M, bool SCALED>
 __device__ __forceinline__ void inverse_norms(float* inv, const double* na, int64_t m0, int64_t n_a, int tid) {
   for (int r = tid; r < M; r += kWaves * 64) {
     float s = -INFINITY;
     if (m0 + r < n_a) {
       const double nn = na[m0 + r];
-      s = nn > 0.0 ? (float)(1.0 / sqrt(nn)) : 0.0f;
+      const double up = SCALED ? (double)exp2_int(row_exponent(nn)) : 1.0;
+      s = nn > 0.0 ? (float)(1.0 / sqrt(nn) * up) : 0.0f;
     }
     inv[r] = s;
   }
@@ -133,10 +143,12 @@ __device__ __forceinline__ void inverse_norms(float* inv, const double* na, int6
 
 // Largest scaled product of each of a wave's columns, merged into the keys:
 // acc[i][j][e] of lane l is row 16 i + 4(l/16) + e of inv and column
-// n0 + 16 j + l%16.
-template <int BI, int BJ>
+// n0 + 16 j + l%16.  SCALED: the products are of scaled rows, and nv holds the
+// columns' squared norms; a column of infinite norm (whose parts are NaN) gets
+// +inf, as its products with the unsplit values would have.
+template <bool SCALED, int BI, int BJ>
 __device__ __forceinline__ void column_maxima(const f32x4 (&acc)[BI][BJ], const float* inv, int lane, int64_t n0,
-                                              int64_t n_v, uint32_t* maxkey) {
+                                              int64_t n_v, const double* nv, uint32_t* maxkey) {
 #pragma unroll
   for (int j = 0; j < BJ; ++j) {
     float m = -INFINITY;
@@ -150,6 +162,10 @@ __device__ __forceinline__ void column_maxima(const f32x4 (&acc)[BI][BJ], const 
     m = fmaxf(m, __shfl_xor(m, 16));
     m = fmaxf(m, __shfl_xor(m, 32));
     const int64_t col = n0 + j * 16 + (lane & 15);
+    if constexpr (SCALED) {
+      const double nn = nv[min(col, n_v - 1)];
+      m = nn == (double)INFINITY ? INFINITY : m * exp2_int(row_exponent(nn));
+    }
     if (lane < 16 && col < n_v && m > -INFINITY) atomicMax(&maxkey[col], order_key(m));
   }
 }
@@ -279,9 +295,9 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   // row 16 (kBI wm + i) + 4(l/16) + e, visual column 16 (kBJ wn + j) + l%16.
   __syncthreads();
   float* inv = reinterpret_cast<float*>(lds);
-  inverse_norms<G::kTileM>(inv, na + c.aud_off, tl.m0, n_a, tid);
+  inverse_norms<G::kTileM, false>(inv, na + c.aud_off, tl.m0, n_a, tid);
   __syncthreads();
-  column_maxima(acc, inv + wm * kBI * 16, lane, tl.n0 + wn * kBJ * 16, n_v, maxkey + c.vis_off);
+  column_maxima<false>(acc, inv + wm * kBI * 16, lane, tl.n0 + wn * kBJ * 16, n_v, nullptr, maxkey + c.vis_off);
 }
 
 // ---------------------------------------------------------------------------
@@ -289,9 +305,15 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 // multiple of 8): tiles of 256 x 128, eight waves of 64 x 64, the operands
 // staged through registers into two LDS buffers.
 //
-// fp32: each value is split into three bf16 parts, x = h + m + l exactly
-// (each part the rounded remainder of the last: 8 + 8 + 8 significand bits),
-// and x y is summed as l h + h l + m m + m h + h m + h h on the bf16 matrix
+// fp32: each row is scaled by the power of two that takes its norm to [1, 2)
+// (row_exponent; undone in the epilogue), then each value is split into three
+// bf16 parts, x = h + m + l (each part the rounded remainder of the last:
+// 8 + 8 + 8 significand bits).  The split is exact for values of at least
+// 2^-102 of the row's norm, whose last parts are normal bf16; smaller ones
+// lose less than 2^-125 of the norm.  The distance is a cosine, so rows of any
+// magnitude keep the same bits (unscaled, rows near 2^-118 had lost up to 6e-3
+// of a value).  The scaling is one product per value in place of a clamp that
+// unscaled first parts need.  x y is summed as l h + h l + m m + m h + h m + h h on the bf16 matrix
 // cores, six MFMAs of 32 elements in fp32.  What is left out (m l, l m, l l)
 // is below 2^-25 of the product, and a sum of K products is rounded 6 K / 32
 // times where v_mfma_f32_32x32x2_f32 rounds it K / 2 times.  Error of the
@@ -324,7 +346,7 @@ template <class T> struct Unit;
 template <> struct Unit<uint16_t> {
   uint4 u;
   __device__ __forceinline__ void load(const uint16_t* p) { u = *reinterpret_cast<const uint4*>(p); }
-  __device__ __forceinline__ void parts(bool valid, uint4 (&out)[1]) const {
+  __device__ __forceinline__ void parts(bool valid, float, uint4 (&out)[1]) const {
     out[0] = valid ? u : make_uint4(0, 0, 0, 0);
   }
 };
@@ -335,7 +357,7 @@ template <> struct Unit<float> {
     b = reinterpret_cast<const float4*>(p)[1];
   }
   // Two bf16 (round to nearest even) packed, and what they leave of the pair.
-  static __device__ __forceinline__ uint32_t split(float x, float y, float& rx, float& ry) {
+  static __device__ __forceinline__ uint32_t split(const float x, const float y, float& rx, float& ry) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     const bf16x2 h = __builtin_convertvector(f32x2{x, y}, bf16x2);
@@ -345,20 +367,14 @@ template <> struct Unit<float> {
     ry = y - __uint_as_float(w & 0xFFFF0000u);
     return w;
   }
-  __device__ __forceinline__ void parts(bool valid, uint4 (&out)[3]) const {
+  __device__ __forceinline__ void parts(bool valid, float scale, uint4 (&out)[3]) const {
     const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
     uint32_t w[3][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      // The largest finite bf16 bounds the first part, so it never rounds to
-      // infinity.
-      constexpr float kTop = 3.3895313892515355e38f;
-      float x = valid ? v[2 * i] : 0.0f, y = valid ? v[2 * i + 1] : 0.0f, rx, ry, t0, t1;
-      w[0][i] = split(__builtin_amdgcn_fmed3f(x, -kTop, kTop), __builtin_amdgcn_fmed3f(y, -kTop, kTop), t0, t1);
-      rx = x - __uint_as_float(w[0][i] << 16);
-      ry = y - __uint_as_float(w[0][i] & 0xFFFF0000u);
-      w[1][i] = split(rx, ry, t0, t1);
-      w[2][i] = split(t0, t1, rx, ry);
+      float x = valid ? v[2 * i] * scale : 0.0f, y = valid ? v[2 * i + 1] * scale : 0.0f;
+#pragma unroll
+      for (int p = 0; p < 3; ++p) w[p][i] = split(x, y, x, y);
     }
 #pragma unroll
     for (int p = 0; p < 3; ++p) out[p] = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
@@ -368,7 +384,9 @@ template <> struct Unit<float> {
 template <class T>
 __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gate_gemm_any(
     const ClipDev* __restrict__ clips, const GemmTileDev* __restrict__ tiles, int dim, const T* __restrict__ xv,
-    const T* __restrict__ xa, const double* __restrict__ na, uint32_t* __restrict__ maxkey) {
+    const T* __restrict__ xa, const double* __restrict__ nv, const double* __restrict__ na,
+    uint32_t* __restrict__ maxkey) {
+  constexpr bool kScaled = sizeof(T) == 4;   // rows scaled before they are split
   constexpr int NP = AnyGeom<T>::planes, KS = AnyGeom<T>::slices;
   constexpr int kStep = 32 * KS, kBufB = KS * NP * kSubB;
   constexpr int kUnits = kAnyRows * 4 * KS / (kWaves * 64);   // 8-element units per thread per step
@@ -386,11 +404,14 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   // chunk tid % 4; audio rows first (clamped to the clip's last rows).
   const int chunk = tid & 3;
   const T* row[kUnits / KS];
+  float scale[kUnits / KS];
 #pragma unroll
   for (int i = 0; i < kUnits / KS; ++i) {
     const int r = (tid >> 2) + i * (kWaves * 16);
-    row[i] = r < kAnyM ? xa + row_start(c.aud_off + min(tl.m0 + (int64_t)r, n_a - 1), dim)
-                       : xv + row_start(c.vis_off + min(tl.n0 + (int64_t)(r - kAnyM), n_v - 1), dim);
+    const int64_t at = r < kAnyM ? c.aud_off + min(tl.m0 + (int64_t)r, n_a - 1)
+                                 : c.vis_off + min(tl.n0 + (int64_t)(r - kAnyM), n_v - 1);
+    row[i] = (r < kAnyM ? xa : xv) + row_start(at, dim);
+    scale[i] = kScaled ? exp2_int(-row_exponent((r < kAnyM ? na : nv)[at])) : 1.0f;
   }
   Unit<T> raw[kUnits];
   auto gload = [&](int k0) {
@@ -403,7 +424,7 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
     for (int u = 0; u < kUnits; ++u) {
       const int ks = u / (kUnits / KS), r = (tid >> 2) + (u % (kUnits / KS)) * (kWaves * 16);
       uint4 part[NP];
-      raw[u].parts(k0 + 32 * ks + chunk * 8 < dim, part);
+      raw[u].parts(k0 + 32 * ks + chunk * 8 < dim, scale[u % (kUnits / KS)], part);
 #pragma unroll
       for (int p = 0; p < NP; ++p)
         *reinterpret_cast<uint4*>(buf + (ks * NP + p) * kSubB + r * 64 + ((chunk ^ (r >> 2)) & 3) * 16) = part[p];
@@ -476,9 +497,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   // 16 (kAnyB wm + i) + 4(l/16) + e, visual column 16 (kAnyB wn + j) + l%16.
   __syncthreads();
   float* inv = reinterpret_cast<float*>(lds);
-  inverse_norms<kAnyM>(inv, na + c.aud_off, tl.m0, n_a, tid);
+  inverse_norms<kAnyM, kScaled>(inv, na + c.aud_off, tl.m0, n_a, tid);
   __syncthreads();
-  column_maxima(acc, inv + wm * kAnyB * 16, lane, tl.n0 + wn * kAnyB * 16, n_v, maxkey + c.vis_off);
+  column_maxima<kScaled>(acc, inv + wm * kAnyB * 16, lane, tl.n0 + wn * kAnyB * 16, n_v, nv + c.vis_off,
+                         maxkey + c.vis_off);
 }
 
 }  // namespace
@@ -568,16 +590,16 @@ apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles,
 }
 
 apack_status launch_gate_gemm_any(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int dim, bool bf16,
-                                  const void* xv, const void* xa, const double* na, uint32_t* maxkey,
+                                  const void* xv, const void* xa, const double* nv, const double* na, uint32_t* maxkey,
                                   hipStream_t stream) {
   if (n_tiles == 0) return APACK_OK;
   const dim3 grid((unsigned)n_tiles), block(kWaves * 64);
   if (bf16)
     hipLaunchKernelGGL(k_gate_gemm_any<uint16_t>, grid, block, 0, stream, clips, tiles, dim,
-                       static_cast<const uint16_t*>(xv), static_cast<const uint16_t*>(xa), na, maxkey);
+                       static_cast<const uint16_t*>(xv), static_cast<const uint16_t*>(xa), nv, na, maxkey);
   else
     hipLaunchKernelGGL(k_gate_gemm_any<float>, grid, block, 0, stream, clips, tiles, dim, static_cast<const float*>(xv),
-                       static_cast<const float*>(xa), na, maxkey);
+                       static_cast<const float*>(xa), nv, na, maxkey);
   return launch_status("k_gate_gemm_any");
 }
 

@@ -435,3 +435,31 @@ def test_gate_gemm_past_2_to_the_31_elements():
     # three times over the range of d.
     tol = 4.0 * (dim // 32 + 4) * 2.0 ** -24 / float(d.max() - d.min()) + 2.0 ** -23
     np.testing.assert_allclose(got.numpy(), want.numpy(), rtol=0, atol=tol)
+
+
+@pytest.mark.parametrize("up,down", [(0, 0), (0, -60), (-118, 0), (-122, -118), (60, 100), (112, -120), (125, 125)])
+def test_fp32_gate_gemm_of_rows_of_any_magnitude(up, down):
+    """The direct distance is a cosine: visual rows times 2^up and audio rows
+    times 2^down (products past fp32's range at both ends, parts of values
+    below bf16's smallest subnormal) give the same bits as unscaled ones."""
+    import paper_2608_08794_amd as A
+    rng = np.random.default_rng(17)
+    frames, audio, dim = 130, 70, 264
+    x = np.clip(rng.standard_normal((frames + audio, dim)), -4, 4)
+    # The scaled rows are rounded once (some elements are subnormal there),
+    # and the unscaled ones are their exact multiples.
+    sv = np.ldexp(x[:frames], up).astype(np.float32)
+    sa = np.ldexp(x[frames:], down).astype(np.float32)
+    ov = np.ldexp(sv.astype(np.float64), -up).astype(np.float32)
+    oa = np.ldexp(sa.astype(np.float64), -down).astype(np.float32)
+    clip = dict(n_frames=frames, per_frame=1, n_audio=audio, n_query=1, vis_off=0, aud_off=0, qry_off=0)
+    got = []
+    for xv, xa in ((ov, oa), (sv, sa)):
+        out = A.apack_score_dynamics(to_dev(xv, "f32"), to_dev(xa, "f32"), to_dev(oa[:1], "f32"), [clip],
+                                     {"alignment": "av_cosine", "gamma": 0.0, "r_pre": 1.0})
+        got.append(out["score"].cpu().numpy())
+    np.testing.assert_array_equal(got[0].view(np.uint32), got[1].view(np.uint32))
+    d, _ = OD.direct_distance(ov.astype(np.float64), oa.astype(np.float64), frames, 1)
+    # Rounding as in test_gate_gemm_of_any_dim_and_dtype.
+    tol = 4.0 * (6 * (dim // 32 + 1) + 4) * 2.0 ** -24 / (d.max() - d.min()) + 2.0 ** -23
+    np.testing.assert_allclose(got[0].astype(np.float64), 1.0 - OD.minmax(d), rtol=0, atol=tol)
