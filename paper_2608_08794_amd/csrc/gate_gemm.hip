@@ -313,17 +313,24 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 // lose less than 2^-125 of the norm.  The distance is a cosine, so rows of any
 // magnitude keep the same bits (unscaled, rows near 2^-118 had lost up to 6e-3
 // of a value).  The scaling is one product per value in place of a clamp that
-// unscaled first parts need.  x y is summed as l h + h l + m m + m h + h m + h h on the bf16 matrix
-// cores, six MFMAs of 32 elements in fp32.  What is left out (m l, l m, l l)
-// is below 2^-25 of the product, and a sum of K products is rounded 6 K / 32
-// times where v_mfma_f32_32x32x2_f32 rounds it K / 2 times.  Error of the
-// largest cosine against 64 bits, rms over random, one-signed and
-// wide-ranging rows, this and that: dim 264 1.8-2.0e-7 and 2.4-2.9e-7, 2048
-// 4.3-5.7e-7 and 6.5-7.5e-7, 3584 5.2-7.5e-7 and 8.1-9.6e-7, 16384 1.1-1.5e-6
-// and 1.8-2.0e-6.  The fp32 MFMA peaks at 157 TFLOP/s; six bf16 ones leave
-// room for twice that: 1500 x 17280 x 2048 takes 654 us against 1148, and
-// 1500 x 17280 x 1288 in bf16 129 against 141 (128 x 128 tiles on 32x32x16
-// MFMAs).
+// unscaled first parts need.  x y is summed as
+// h h, and l h + h l + m h + m m + h m in accumulators of their own, on the
+// bf16 matrix cores: six MFMAs of 32 elements in fp32.  What is left out (m l,
+// l m, l l) is below 2^-25 of the product.  The large sum is rounded K / 32
+// times where v_mfma_f32_32x32x2_f32 rounds it K / 2 times, the small one at
+// 2^-8 of its size.  (With all six in one accumulator every product of every
+// step was rounded to the large sum: on one-signed rows up to twice the error
+// of the fp32 unit.)  Error of 1 - distance against 64 bits, rms over four
+// sets of random / one-signed / wide-ranging rows, here and on
+// v_mfma_f32_32x32x2_f32, in 1e-8: dim 264 1.8 / 12 / 3.9 and 5.2 / 25 / 8.5,
+// 2048 1.4 / 21 / 2.8 and 4.6 / 89 / 25, 3584 1.5 / 35 / 3.2 and 4.5 / 80 / 26,
+// 16384 1.5 / 55 / 3.3 and 4.6 / 183 / 58.  The fp32 MFMA peaks at 157 TFLOP/s;
+// six bf16 ones leave room for twice that: 1500 x 17280 x 2048 takes 638 us
+// against 1148 (644 with one accumulator), and 1500 x 17280 x 1288 in bf16 129
+// against 141 (128 x 128 tiles on 32x32x16 MFMAs).  The second accumulators
+// fit because the second parts are read into the third ones' registers; sums
+// of a step added to one set of accumulators by the vector ALU were as exact
+// and 5-8% slower.
 // Parts are kept as planes of 64-byte LDS rows (32 elements), so a fragment
 // read once serves two or three products.
 // ---------------------------------------------------------------------------
@@ -436,20 +443,13 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
     return *reinterpret_cast<const bf16x8*>(sub + r * 64 + (((lane >> 4) ^ (r >> 2)) & 3) * 16);
   };
 
-  f32x4 acc[kAnyB][kAnyB];
+  f32x4 acc[kAnyB][kAnyB], low[kAnyB][kAnyB];   // low: the sum of the small products (fp32 inputs)
 #pragma unroll
   for (int i = 0; i < kAnyB; ++i)
 #pragma unroll
-    for (int j = 0; j < kAnyB; ++j) acc[i][j] = f32x4{};
+    for (int j = 0; j < kAnyB; ++j) acc[i][j] = low[i][j] = f32x4{};
   const int n_k = (dim + kStep - 1) / kStep;
   const int row_a = wm * kAnyB * 16 + (lane & 15), row_b = kAnyM + wn * kAnyB * 16 + (lane & 15);
-  auto products = [&](const bf16x8 (&fa)[kAnyB], const bf16x8 (&fb)[kAnyB]) {
-#pragma unroll
-    for (int i = 0; i < kAnyB; ++i)
-#pragma unroll
-      for (int j = 0; j < kAnyB; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-  };
   gload(0);
   lstore(0, lds);
   gload(kStep);
@@ -461,34 +461,57 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
     asm volatile("" ::: "memory");
     const char* buf = lds + (it & 1) * kBufB;
     bf16x8 fa[KS * NP][kAnyB], fb[KS * NP][kAnyB];
+    auto read_a = [&](int p) {
 #pragma unroll
-    for (int p = KS * NP - 1; p >= 0; --p)
+      for (int i = 0; i < kAnyB; ++i) fa[p][i] = frag(buf + p * kSubB, row_a + 16 * i);
+    };
+    auto read_b = [&](int p) {
 #pragma unroll
-      for (int i = 0; i < kAnyB; ++i) {
-        fa[p][i] = frag(buf + p * kSubB, row_a + 16 * i);
-        fb[p][i] = frag(buf + p * kSubB, row_b + 16 * i);
+      for (int i = 0; i < kAnyB; ++i) fb[p][i] = frag(buf + p * kSubB, row_b + 16 * i);
+    };
+    auto product = [&](int pa, int pb, f32x4 (&sum)[kAnyB][kAnyB]) {
+#pragma unroll
+      for (int i = 0; i < kAnyB; ++i)
+#pragma unroll
+        for (int j = 0; j < kAnyB; ++j)
+          sum[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[pa][i], fb[pb][j], sum[i][j], 0, 0, 0);
+    };
+    if constexpr (NP == 3) {
+      read_a(2);
+      read_b(0);
+      read_a(0);
+      read_b(2);
+    } else {
+#pragma unroll
+      for (int p = KS - 1; p >= 0; --p) {
+        read_a(p);
+        read_b(p);
       }
+    }
     __builtin_amdgcn_sched_barrier(0);
     // The next step is split and stored under this step's products.
     lstore((it + 1) * kStep, lds + ((it + 1) & 1) * kBufB);
     gload((it + 2) * kStep);
     if constexpr (NP == 3) {
-      products(fa[2], fb[0]);
-      products(fa[0], fb[2]);
-      products(fa[1], fb[1]);
-      products(fa[1], fb[0]);
-      products(fa[0], fb[1]);
-      products(fa[0], fb[0]);
-    } else {
-#pragma unroll
-      for (int p = 0; p < KS; ++p) products(fa[p], fb[p]);
-    }
-    if constexpr (NP == 3) {
+      // The second parts are read as the third ones' registers come free.
+      product(2, 0, low);
+      read_a(1);
+      product(0, 2, low);
+      read_b(1);
+      product(1, 0, low);
+      product(1, 1, low);
+      product(0, 1, low);
+      product(0, 0, acc);
 #pragma unroll
       for (int g = 0; g < 6 * kAnyB * kAnyB; ++g) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
         __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);   // two VALU instructions
+        if (g >= 15 && g < 15 + kAnyB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+        if (g >= 31 && g < 31 + kAnyB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
+    } else {
+#pragma unroll
+      for (int p = 0; p < KS; ++p) product(p, p, acc);
     }
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -497,6 +520,12 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
   // 16 (kAnyB wm + i) + 4(l/16) + e, visual column 16 (kAnyB wn + j) + l%16.
   __syncthreads();
   float* inv = reinterpret_cast<float*>(lds);
+  if constexpr (NP == 3) {
+#pragma unroll
+    for (int i = 0; i < kAnyB; ++i)
+#pragma unroll
+      for (int j = 0; j < kAnyB; ++j) acc[i][j] += low[i][j];
+  }
   inverse_norms<kAnyM, kScaled>(inv, na + c.aud_off, tl.m0, n_a, tid);
   __syncthreads();
   column_maxima<kScaled>(acc, inv + wm * kAnyB * 16, lane, tl.n0 + wn * kAnyB * 16, n_v, nv + c.vis_off,

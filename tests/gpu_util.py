@@ -39,3 +39,7 @@ def raw_bits(x, dtype):
 
 def score_tol(dtype):
     return 2e-3 if dtype == "bf16" else 1e-5
+
+
+def rms(got, want):
+    return float(np.sqrt(np.mean((np.asarray(got, np.float64) - want) ** 2)))

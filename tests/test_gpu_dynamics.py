@@ -14,7 +14,7 @@ import pytest
 
 import workloads as W
 from oracle import dynamics as OD, widen
-from tests.gpu_util import log, to_dev
+from tests.gpu_util import log, rms, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -463,3 +463,32 @@ def test_fp32_gate_gemm_of_rows_of_any_magnitude(up, down):
     # Rounding as in test_gate_gemm_of_any_dim_and_dtype.
     tol = 4.0 * (6 * (dim // 32 + 1) + 4) * 2.0 ** -24 / (d.max() - d.min()) + 2.0 ** -23
     np.testing.assert_allclose(got[0].astype(np.float64), 1.0 - OD.minmax(d), rtol=0, atol=tol)
+
+
+# rms errors that a kernel of v_mfma_f32_32x32x2_f32 measured on the rows below.
+@pytest.mark.parametrize("dim,kind,fp32_unit", [
+    (264, "normal", 4.09e-8), (264, "one_signed", 2.59e-7), (264, "wide", 8.69e-8),
+    (2048, "normal", 3.73e-8), (2048, "one_signed", 4.46e-7), (2048, "wide", 2.49e-7),
+    (3584, "normal", 4.63e-8), (3584, "one_signed", 6.17e-7), (3584, "wide", 2.38e-7),
+])
+def test_fp32_gate_gemm_error_is_no_larger_than_the_fp32_matrix_units(dim, kind, fp32_unit):
+    """rms error of 1 - distance over random rows (d_hat divides by the
+    distance's range, which is taken out again)."""
+    import paper_2608_08794_amd as A
+    rng = np.random.default_rng(dim)
+    frames, audio = 200, 60
+    x = rng.standard_normal((frames + audio, dim))
+    if kind == "one_signed":
+        x = np.abs(x)
+    if kind == "wide":
+        x *= np.exp(2.0 * rng.standard_normal(x.shape))
+    x = x.astype(np.float32)
+    x[0], x[1] = x[frames], -x[frames]   # cosines of 1 and about -1 or 0: a wide range of d
+    xv, xa = x[:frames], x[frames:]
+    clip = dict(n_frames=frames, per_frame=1, n_audio=audio, n_query=1, vis_off=0, aud_off=0, qry_off=0)
+    out = A.apack_score_dynamics(to_dev(xv, "f32"), to_dev(xa, "f32"), to_dev(xa[:1], "f32"), [clip],
+                                 {"alignment": "av_cosine", "gamma": 0.0, "r_pre": 1.0})
+    d, _ = OD.direct_distance(xv.astype(np.float64), xa.astype(np.float64), frames, 1)
+    err = rms(out["score"].cpu().numpy(), 1.0 - OD.minmax(d)) * (d.max() - d.min())
+    print(f"[gate error] dim {dim} {kind}: rms {err:.2e}", flush=True)
+    assert err <= fp32_unit
