@@ -14,7 +14,7 @@ import pytest
 
 import workloads as W
 from oracle import dynamics as OD, widen
-from tests.gpu_util import log, rms, to_dev
+from tests.gpu_util import THREE_PART_RMS, log, rms, three_part_rows, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -492,3 +492,18 @@ def test_fp32_gate_gemm_error_is_no_larger_than_the_fp32_matrix_units(dim, kind,
     err = rms(out["score"].cpu().numpy(), 1.0 - OD.minmax(d)) * (d.max() - d.min())
     print(f"[gate error] dim {dim} {kind}: rms {err:.2e}", flush=True)
     assert err <= fp32_unit
+
+
+@pytest.mark.parametrize("dim,frames,audio", [(8, 127, 255), (40, 128, 256), (264, 129, 257), (1288, 300, 600),
+                                              (3584, 260, 513)])
+def test_fp32_gate_gemm_sums_all_six_products(dim, frames, audio):
+    """Rows whose second and third bf16 parts count: a part or a product that
+    is lost or stale in any K step or tile exceeds the bound (an emulation on
+    the CPU checks that it does)."""
+    import paper_2608_08794_amd as A
+    xv, xa = three_part_rows(np.random.default_rng(dim), frames, audio, dim)
+    clip = dict(n_frames=frames, per_frame=1, n_audio=audio, n_query=1, vis_off=0, aud_off=0, qry_off=0)
+    out = A.apack_score_dynamics(to_dev(xv, "f32"), to_dev(xa, "f32"), to_dev(xa[:1], "f32"), [clip],
+                                 {"alignment": "av_cosine", "gamma": 0.0, "r_pre": 1.0})
+    d, _ = OD.direct_distance(xv.astype(np.float64), xa.astype(np.float64), frames, 1)
+    assert rms(out["score"].cpu().numpy(), 1.0 - OD.minmax(d)) < THREE_PART_RMS
