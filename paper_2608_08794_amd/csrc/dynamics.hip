@@ -36,6 +36,7 @@
 
 #include "common.hpp"
 #include "dynamics_plan.hpp"
+#include "pick_key.hpp"
 
 namespace apack {
 namespace {
@@ -1323,16 +1324,6 @@ __device__ __forceinline__ double min_f64(double a, double b) {
   return r;
 }
 
-// Unsigned key with the numeric order of doubles: positive values (sign bit
-// clear) get the sign bit set, negative ones are negated as 64-bit integers,
-// so the larger magnitude gives the smaller key and -0 gets the key of +0.
-// Equal values have equal keys; every key is above 0 except those of
-// negative NaNs.
-__device__ __forceinline__ uint64_t order_key(double v) {
-  const uint64_t b = (uint64_t)__double_as_longlong(v);
-  return (b >> 63) ? (uint64_t)0 - b : (b | 0x8000000000000000ull);
-}
-
 // Maximum of a 32-bit value over the 64 lanes, in every lane: DPP within
 // 16-lane rows, then the row-pair and half swaps.  All lanes active.
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
@@ -1483,8 +1474,8 @@ __device__ __forceinline__ double dafps_density(const DafpsLds& L, const double*
 // tokens count as taken).  The first pick is the densest token, each later
 // one the token farthest from the picked set, weighted by density:
 // argmax of (1 - max cosine to the picked set) rho^power.  The argmax is
-// lexicographic (value desc, token asc): the wave's largest high word, the
-// largest order key among the tokens that hold it, then the lowest such
+// lexicographic (value desc, token asc): the wave's largest high word of the
+// order keys, the largest low word among the tokens that hold it, then the lowest such
 // token -- tokens 64u + lane ascend with u and then with the lane, so the
 // first non-empty ballot in u order names it.  A pick is always an untaken
 // token.  The picked positions
@@ -1513,14 +1504,11 @@ __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __re
     rt[u] = n.y;
   }
   auto pick_of = [&]() {
-    // Signed integers with the order of the values' high words (no value is
-    // -0); a taken token is below every value.
+    // A taken token is below every value.
     int hk[KU];
 #pragma unroll
-    for (int u = 0; u < KU; ++u) {
-      const int h = (int)((uint64_t)__double_as_longlong(val[u]) >> 32);
-      hk[u] = __builtin_amdgcn_inverse_ballot_w64(tk[u]) ? INT_MIN : h ^ ((h >> 31) & 0x7FFFFFFF);
-    }
+    for (int u = 0; u < KU; ++u)
+      hk[u] = __builtin_amdgcn_inverse_ballot_w64(tk[u]) ? INT_MIN : pick_key_high(val[u]);
     int hm = hk[0];
 #pragma unroll
     for (int u = 1; u < KU; ++u) hm = max(hm, hk[u]);
@@ -1542,11 +1530,11 @@ __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __re
       return best;
     }
     if (cnt > 1) {
-      // The largest whole key among them, the lowest token holding it.
+      // The largest low word among them, the lowest token holding it.
       uint32_t lo[KU], lm = 0;
 #pragma unroll
       for (int u = 0; u < KU; ++u) {
-        lo[u] = __builtin_amdgcn_inverse_ballot_w64(hb[u]) ? (uint32_t)order_key(val[u]) : 0u;
+        lo[u] = __builtin_amdgcn_inverse_ballot_w64(hb[u]) ? pick_key_low(val[u]) : 0u;
         lm = max(lm, lo[u]);
       }
       lm = wave_max_u32(lm);
@@ -1590,7 +1578,7 @@ __device__ __forceinline__ void dafps_pick(const DafpsLds& L, const double* __re
     }
     if (n + 1 >= k) break;
 #pragma unroll
-    for (int u = 0; u < KU; ++u) val[u] = fma(1.0 - smax[u], wgt[u], 0.0);   // the product, a zero one as +0
+    for (int u = 0; u < KU; ++u) val[u] = pick_value(1.0 - smax[u], wgt[u]);
     pick = pick_of();
   }
   // Ascending output of the picked positions.

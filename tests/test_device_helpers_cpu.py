@@ -41,3 +41,42 @@ int main() {{
 """)
     want = [[r * d] * 2 for r, d in cases]
     assert [[int(v) for v in line.split()] for line in out.splitlines()] == want
+
+
+def test_pick_keys_have_the_order_of_doubles(tmp_path):
+    """DA-FPS picks by the high words of the values and, among equal ones, by
+    the low words: together they must order as the doubles do, negative values
+    (every cosine above 1 by rounding) among them, and a value that underflows
+    is a zero."""
+    _run(tmp_path, "pick_key", r"""
+#include <cmath>
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "pick_key.hpp"
+using namespace apack;
+int main() {
+  const double eps = 0x1p-52;
+  std::vector<double> v = {0.0, 5e-324, eps, 1.0, 1.0 + eps, 2.0, 12.0, INFINITY};
+  // Neighbours whose magnitudes share a high word, and across a carry of the
+  // low word.
+  for (double w : {12.0, 0.75, 1.0, 4294967295.0, 3.0e300, 1.0e-300, 5.0})
+    for (double x = w, i = 0; i < 3; ++i, x = std::nextafter(x, INFINITY)) v.push_back(pick_value(-eps, x));
+  std::srand(1);
+  for (int i = 0; i < 400; ++i) {
+    const double x = std::ldexp(1.0 + std::rand() / (double)RAND_MAX, std::rand() % 40 - 20);
+    for (double y : {x, std::nextafter(x, 0.0), x + std::ldexp(x, -31), -x}) v.push_back(y);
+  }
+  const size_t n = v.size();
+  for (size_t i = 0; i < n; ++i) v.push_back(-v[i] == 0.0 ? 0.0 : -v[i]);
+  for (double a : v)
+    for (double b : v) {
+      const int ha = pick_key_high(a), hb = pick_key_high(b);
+      const bool less = ha != hb ? ha < hb : pick_key_low(a) < pick_key_low(b);
+      if (less != (a < b)) return printf("%.17g %.17g\n", a, b), 1;
+    }
+  for (double z : {pick_value(-0.0, 1.0), pick_value(-eps, 0.0), pick_value(-eps, 5e-324)})
+    if (z != 0.0 || std::signbit(z)) return printf("zero %g\n", z), 1;
+  return 0;
+}
+""")
