@@ -129,7 +129,15 @@ typedef struct apack_seq {
 
 /* Validates `seqs` for a prune step and reports the kept-row count of every
  * sequence (n_kept, HOST [n_seq], may be NULL) and the workspace size that
- * apack_prune_layer needs (workspace_bytes, may be NULL). */
+ * serves apack_prune_layer best in either dtype (workspace_bytes, may be
+ * NULL).  For calls with at most 16 query rows per key head, and 1024 in all,
+ * that includes 4 bytes per query row and key, for bf16 logits that are then
+ * formed once; for the rest, finer partials of fp32 calls.  A workspace
+ * without that room is accepted too (down to 8 bytes per query row and 128 to
+ * 4096 keys, 4 bytes per key, key head and 512 query rows, and descriptors):
+ * the call then takes its more general passes, whose scores agree to fp32
+ * rounding, so that one workspace sized for a call serves the same rows with
+ * fewer query rows. */
 apack_status apack_prune_layer_query(int32_t n_seq, const apack_seq* seqs,
                                      int32_t hq, int32_t hkv, int32_t d,
                                      int64_t* n_kept, size_t* workspace_bytes);

@@ -955,7 +955,7 @@ __global__ __launch_bounds__(kFewWaves * kWave) void k_few_logits(
   // Stored logits of this group's row l % 16: keys 4 (l / 16) .. + 3 of each
   // block (the row length is a multiple of 16).
   const int64_t np = (sq.n_tokens + 15) / 16 * 16;
-  float* out = logits + sq.logits_off + ((int64_t)tl.g * rows + (lane & 15)) * np + key_begin;
+  float* out = logits + sq.colpart_off + ((int64_t)tl.g * rows + (lane & 15)) * np + key_begin;
   const bool store = (lane & 15) < rows;
   float m_run = -FLT_MAX, s_run = 0.f;
   for (int i0 = first; i0 < n_keys; i0 += kFewKeys) {
@@ -1066,7 +1066,7 @@ __global__ __launch_bounds__(kFewWaves * kWave) void k_few_colsum(SeqDev* __rest
   const int64_t key = key0 + 4 * lane;
   f32x4v sum = f32x4v{};
   if (key < np) {
-    const float* p = logits + sq.logits_off + key;
+    const float* p = logits + sq.colpart_off + key;
     constexpr int RB = 8;
     for (int r0 = ra; r0 < rb; r0 += RB) {
       f32x4v v[RB];
@@ -1120,7 +1120,7 @@ apack_status launch_scores_t(const PrunePlan& pl, const DevPtrs& dp, const Inlin
     APACK_CHECK(launch_status("k_rowstats") == APACK_OK, APACK_E_HIP, "%s", apack_last_error());
     hipLaunchKernelGGL((k_colsum<T, D, NW, S>), dim3(nt), dim3(NW * kWave), 0, stream, dp.seqs, dp.tiles, dp.tags,
                        (const T*)q, q_hs, (const T*)k, k_hs, n_rep, hkv, scale_log2, dp.stats, dp.colpart, scores,
-                       dp.hist, dp.ctr, score_tail(pl, false));
+                       dp.hist, dp.ctr, score_tail(pl));
     APACK_CHECK(launch_status("k_colsum") == APACK_OK, APACK_E_HIP, "%s", apack_last_error());
   }
   return APACK_OK;
@@ -1149,12 +1149,12 @@ apack_status launch_few(const PrunePlan& pl, const DevPtrs& dp, const InlineCall
   if (nt == 0) return APACK_OK;
   hipLaunchKernelGGL(k_few_logits<D>, dim3(nt), dim3(kFewWaves * kWave), 0, stream, in, dp.seqs, dp.tiles, dp.ftiles,
                      dp.tags, dp.ctr, (const bf16_t*)q, q_hs, (const bf16_t*)k, k_hs, n_rep, scale_log2, dp.stats,
-                     dp.logits, dp.hist, pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : (int64_t)0);
+                     dp.colpart, dp.hist, pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : (int64_t)0);
   apack_status st = launch_status("k_few_logits");
   if (st != APACK_OK) return st;
   hipLaunchKernelGGL(k_few_colsum, dim3((unsigned)pl.ftiles.size() * (kRowTile / kFewCols)), dim3(kFewWaves * kWave), 0,
-                     stream, dp.seqs, dp.ftiles, dp.tags, n_rep, hkv, scale_log2, dp.stats, dp.logits, scores, dp.hist,
-                     dp.ctr, score_tail(pl, true));
+                     stream, dp.seqs, dp.ftiles, dp.tags, n_rep, hkv, scale_log2, dp.stats, dp.colpart, scores, dp.hist,
+                     dp.ctr, score_tail(pl));
   return launch_status("k_few_colsum");
 }
 
@@ -1165,8 +1165,7 @@ apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCa
                           int32_t* kept, hipStream_t stream) {
   const int n_rep = hq / hkv;
   apack_status st;
-  const bool few = dt == APACK_BF16 && pl.few;
-  if (few)
+  if (pl.form == ScoreForm::kFewRows)
     st = d == 64 ? launch_few<64>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream)
                  : launch_few<128>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
   else if (dt == APACK_BF16)
@@ -1177,7 +1176,7 @@ apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCa
                  : launch_scores_d<float, 128>(pl, dp, in, q, q_hs, k, k_hs, n_rep, hkv, scores, stream);
   if (st != APACK_OK) return st;
   if (pl.total_tok == 0) return APACK_OK;
-  return launch_select(pl, dp, few, n_rep, hkv, scores, kept, stream);
+  return launch_select(pl, dp, n_rep, hkv, scores, kept, stream);
 }
 
 }  // namespace apack

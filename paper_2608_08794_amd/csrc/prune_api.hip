@@ -11,7 +11,7 @@
 namespace apack {
 
 apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, int32_t hkv, int32_t d,
-                              apack_dtype dtype, PrunePlan& pl) {
+                              PrunePlan& pl) {
   APACK_CHECK(n_seq >= 0, APACK_E_ARG, "n_seq must be >= 0 (got %d)", n_seq);
   APACK_CHECK(n_seq == 0 || seqs, APACK_E_ARG, "seqs is NULL");
   APACK_CHECK(hq > 0 && hkv > 0 && hq % hkv == 0, APACK_E_SHAPE,
@@ -21,10 +21,9 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
   pl = PrunePlan();
   pl.seqs.resize(n_seq);
   pl.n_kept.resize(n_seq);
-  int64_t tag = 0, stats = 0, colpart = 0, kept = 0;
+  int64_t tag = 0, kept = 0;
   int waves = 1;
-  // Total work units so the chunk length can target a few workgroups per CU.
-  int64_t weighted = 0;
+  pl.few_rows = n_seq > 0;
   for (int s = 0; s < n_seq; ++s) {
     const apack_seq& a = seqs[s];
     APACK_CHECK(a.n_tokens >= 0 && a.tok_off >= 0, APACK_E_SHAPE, "seq %d: negative offset or length", s);
@@ -99,7 +98,10 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
     sd.rows_per_rg = (int32_t)((per + kRowsPerWave - 1) / kRowsPerWave * kRowsPerWave);
     sd.rows_pad = sd.n_rg * sd.rows_per_rg;
     waves = std::max<int>(waves, sd.rows_per_rg / kRowsPerWave);
-    if (sd.n_cand > 0) weighted += a.n_tokens * (int64_t)hkv * sd.n_rg;
+    pl.few_rows &= rows_g <= kFewRows && hkv * rows_g <= kFewTotal;
+    pl.max_planes = std::max<int>(pl.max_planes, hkv * sd.n_rg);
+    // Total work units so the chunk length can target a few workgroups per CU.
+    if (sd.n_cand > 0) pl.weighted += a.n_tokens * (int64_t)hkv * sd.n_rg;
   }
   // Sequences may not overlap in K (their scores would collide).
   {
@@ -110,41 +112,40 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
     for (size_t i = 1; i < r.size(); ++i)
       APACK_CHECK(r[i].first >= r[i - 1].second, APACK_E_SHAPE, "sequences overlap in k");
   }
+  pl.waves = waves <= 1 ? 1 : waves <= 2 ? 2 : waves <= 4 ? 4 : waves == 7 ? 7 : 8;
+  pl.total_tok = tag;
+  pl.total_kept = kept;
+  return APACK_OK;
+}
+
+void lay_out_prune(PrunePlan& pl, ScoreForm form, int n_rep, int hkv) {
+  pl.form = form;
+  pl.tiles.clear();
+  pl.total_stats = pl.total_colpart = pl.total_ctr = 0;
   // Keys per workgroup: about one score workgroup per CU over the whole
   // call (one 7- or 8-wave workgroup fills a CU), so the chip runs a single
   // round and each workgroup loads its query fragments once.
-  pl.few = n_seq > 0;
-  for (const SeqDev& sd : pl.seqs)
-    pl.few &= n_rep * sd.q_len <= kFewRows && hkv * n_rep * sd.q_len <= kFewTotal;
-  for (const SeqDev& sd : pl.seqs) pl.max_planes = std::max<int>(pl.max_planes, hkv * sd.n_rg);
   // In fp32 the matrix units bound the score kernels, so a chunk is any number
   // of 32-key blocks and the work spreads over more compute units; in bf16,
   // where the per-workgroup part outweighs a block, whole tiles.  fp32 calls at
   // 1312 rows (8 heads over 2, D = 64) 41.2 us with tiles, 32.5 with blocks;
   // 9454 rows (16 over 2) 121.8 and 110.7; 9390 rows (28 over 4) 190.5 and
-  // 148.7.  bf16 at 9454 rows: 57.0 and 59.4.  The workspace covers either.
-  int64_t fine_tiles = 0, fine_stats = 0, fine_ctr = 0;
-  const int64_t unit = dtype == APACK_F32 ? kKeyBlock : kKeyTile;
-  const int64_t target = pl.few ? kFewTarget : APACK_TILE_TARGET;
-  for (int s = 0; s < n_seq; ++s) {
+  // 148.7.  bf16 at 9454 rows: 57.0 and 59.4.
+  const int64_t unit = form == ScoreForm::kFineChunks ? kKeyBlock : kKeyTile;
+  const int64_t target = pl.few_rows && form != ScoreForm::kGeneral ? kFewTarget : APACK_TILE_TARGET;
+  const int64_t want = (pl.weighted + target - 1) / target;
+  const int64_t ch = std::max<int64_t>(unit, std::min<int64_t>((want + unit - 1) / unit * unit, kMaxChunk));
+  for (int s = 0; s < (int)pl.seqs.size(); ++s) {
     SeqDev& sd = pl.seqs[s];
     if (sd.n_cand == 0) continue;
-    const int64_t want = (weighted + target - 1) / target;
-    auto chunk_of = [&](int64_t u) { return std::max<int64_t>(u, std::min<int64_t>((want + u - 1) / u * u, kMaxChunk)); };
-    const int64_t ch = chunk_of(unit), fine = (sd.n_tokens + chunk_of(kKeyBlock) - 1) / chunk_of(kKeyBlock);
-    fine_tiles += (int64_t)hkv * sd.n_rg * fine;
-    fine_stats += (int64_t)hkv * sd.rows_pad * fine;
-    fine_ctr += fine + 1;
     sd.chunk = (int32_t)ch;
     sd.n_chunks = (int32_t)((sd.n_tokens + ch - 1) / ch);
-    sd.stats_off = stats;
-    stats += (int64_t)hkv * sd.rows_pad * sd.n_chunks;
-    sd.colpart_off = colpart;
-    colpart += (int64_t)hkv * sd.n_rg * sd.n_tokens;
-    if (pl.few) {
-      sd.logits_off = pl.total_logits;
-      pl.total_logits += (int64_t)hkv * n_rep * sd.q_len * ((sd.n_tokens + 15) / 16 * 16);
-    }
+    sd.stats_off = pl.total_stats;
+    pl.total_stats += (int64_t)hkv * sd.rows_pad * sd.n_chunks;
+    sd.colpart_off = pl.total_colpart;
+    pl.total_colpart += form == ScoreForm::kFewRows
+                            ? (int64_t)hkv * n_rep * sd.q_len * ((sd.n_tokens + 15) / 16 * 16)
+                            : (int64_t)hkv * sd.n_rg * sd.n_tokens;
     sd.ctr_off = (int32_t)pl.total_ctr;
     pl.total_ctr += sd.n_chunks + 1;
     // Tiles: chunks of one (g, rg) eight apart so that both query-row
@@ -154,40 +155,27 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
         for (int rg = 0; rg < sd.n_rg; ++rg)
           for (int c = c0; c < std::min(c0 + 8, sd.n_chunks); ++c) pl.tiles.push_back({s, g, rg, c});
   }
-  pl.waves = waves <= 1 ? 1 : waves <= 2 ? 2 : waves <= 4 ? 4 : waves == 7 ? 7 : 8;
-  pl.total_tok = tag;
-  pl.total_stats = stats;
-  pl.total_colpart = colpart;
-  pl.total_kept = kept;
-  // Workspace layout; its size is that of the finer chunks, whatever the dtype.
-  auto layout = [&](PrunePlan& p, int64_t n_tiles, int64_t n_stats, int64_t n_ctr) {
-    Carver c(nullptr);
-    c.take<SeqDev>(pl.seqs.size());
-    p.off_tiles = c.used;
-    c.take<TileDev>(n_tiles);
-    p.off_ftiles = c.used;
-    c.take<FTileDev>(pl.ftiles.size());
-    p.off_tags = c.used;
-    c.take<uint8_t>(pl.total_tok);
-    p.off_ctr = c.used;
-    c.take<uint32_t>(n_ctr);
-    p.blob_bytes = c.used;
-    p.off_stats = c.used;
-    c.take<float2>(n_stats);
-    p.off_colpart = c.used;
-    c.take<float>(pl.total_colpart);
-    p.off_logits = c.used;
-    c.take<float>(pl.total_logits);
-    p.off_hist = c.used;
-    c.take<uint32_t>(pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : 0);
-    p.off_cnt = c.used;
-    c.take<uint32_t>(3 * pl.ftiles.size());
-    return std::max<size_t>(c.used, kAlign);
-  };
-  PrunePlan finest;
-  pl.ws_bytes = layout(finest, fine_tiles, fine_stats, fine_ctr);
-  pl.ws_bytes = std::max(pl.ws_bytes, layout(pl, (int64_t)pl.tiles.size(), pl.total_stats, pl.total_ctr));
-  return APACK_OK;
+  // Workspace layout.
+  Carver c(nullptr);
+  c.take<SeqDev>(pl.seqs.size());
+  pl.off_tiles = c.used;
+  c.take<TileDev>(pl.tiles.size());
+  pl.off_ftiles = c.used;
+  c.take<FTileDev>(pl.ftiles.size());
+  pl.off_tags = c.used;
+  c.take<uint8_t>(pl.total_tok);
+  pl.off_ctr = c.used;
+  c.take<uint32_t>(pl.total_ctr);
+  pl.blob_bytes = c.used;
+  pl.off_stats = c.used;
+  c.take<float2>(pl.total_stats);
+  pl.off_colpart = c.used;
+  c.take<float>(pl.total_colpart);
+  pl.off_hist = c.used;
+  c.take<uint32_t>(pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : 0);
+  pl.off_cnt = c.used;
+  c.take<uint32_t>(3 * pl.ftiles.size());
+  pl.ws_bytes = std::max<size_t>(c.used, kAlign);
 }
 
 }  // namespace apack
@@ -200,11 +188,18 @@ apack_status apack_prune_layer_query(int32_t n_seq, const apack_seq* seqs, int32
                                      int32_t d, int64_t* n_kept, size_t* workspace_bytes) {
   clear_error();
   PrunePlan pl;
-  apack_status st = build_prune_plan(n_seq, seqs, hq, hkv, d, APACK_BF16, pl);
+  apack_status st = build_prune_plan(n_seq, seqs, hq, hkv, d, pl);
   if (st != APACK_OK) return st;
   if (n_kept)
     for (int s = 0; s < n_seq; ++s) n_kept[s] = pl.n_kept[s];
-  if (workspace_bytes) *workspace_bytes = pl.ws_bytes;
+  if (workspace_bytes) {   // room for the form of either dtype
+    *workspace_bytes = 0;
+    for (ScoreForm form : {ScoreForm::kGeneral, ScoreForm::kFineChunks, ScoreForm::kFewRows}) {
+      if (form == ScoreForm::kFewRows && !pl.few_rows) continue;
+      lay_out_prune(pl, form, hq / hkv, hkv);
+      *workspace_bytes = std::max(*workspace_bytes, pl.ws_bytes);
+    }
+  }
   return APACK_OK;
 }
 
@@ -216,8 +211,14 @@ apack_status apack_prune_layer(int32_t n_seq, const apack_seq* seqs, apack_dtype
   clear_error();
   APACK_CHECK(dtype_ok(dtype), APACK_E_DTYPE, "unknown dtype %d", (int)dtype);
   PrunePlan pl;
-  apack_status st = build_prune_plan(n_seq, seqs, hq, hkv, d, dtype, pl);
+  apack_status st = build_prune_plan(n_seq, seqs, hq, hkv, d, pl);
   if (st != APACK_OK) return st;
+  const ScoreForm form = dtype == APACK_F32 ? ScoreForm::kFineChunks
+                         : pl.few_rows      ? ScoreForm::kFewRows
+                                            : ScoreForm::kGeneral;
+  lay_out_prune(pl, form, hq / hkv, hkv);
+  if (workspace_bytes < pl.ws_bytes && form != ScoreForm::kGeneral)
+    lay_out_prune(pl, ScoreForm::kGeneral, hq / hkv, hkv);
   const size_t es = dtype_size(dtype);
   APACK_CHECK(q_rows >= 0 && k_rows >= 0, APACK_E_SHAPE, "negative row count");
   APACK_CHECK(q_head_stride >= q_rows * d && k_head_stride >= k_rows * d, APACK_E_SHAPE,
@@ -262,7 +263,6 @@ apack_status apack_prune_layer(int32_t n_seq, const apack_seq* seqs, apack_dtype
   dp.tags = reinterpret_cast<uint8_t*>(ws + pl.off_tags);
   dp.stats = reinterpret_cast<float2*>(ws + pl.off_stats);
   dp.colpart = reinterpret_cast<float*>(ws + pl.off_colpart);
-  dp.logits = reinterpret_cast<float*>(ws + pl.off_logits);
   // Tag = selection slot + 1: the modality, or slot 1 for every candidate of
   // a jointly ranked sequence.
   auto tag_of = [&](int s, const apack_span& sp) {

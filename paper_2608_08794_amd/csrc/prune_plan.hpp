@@ -45,8 +45,8 @@ struct SeqDev {
   int64_t n_kept;       // kept rows of the sequence (bound on the scan's writes)
   int64_t tag_off;      // first byte of the sequence in the tag array
   int64_t stats_off;    // first (max, sum) partial: [g][chunk][rows_pad]
-  int64_t colpart_off;  // first per-group column partial: [g*n_rg + rg][n_tokens]
-  int64_t logits_off;   // first stored logit: [g][row][n_tokens rounded up to 16] (few-row calls)
+  int64_t colpart_off;  // first per-group column partial: [g*n_rg + rg][n_tokens]; of a few-row
+                        // call the first stored logit: [g][row][n_tokens rounded up to 16]
   int32_t q_len;
   int32_t n_rg;         // query-row groups per KV head
   int32_t rows_per_rg;  // rows per group (multiple of 64)
@@ -96,6 +96,15 @@ struct TileDev {
   int32_t seq, g, rg, chunk;
 };
 
+// How the score passes cut a call; the forms' results agree to fp32 rounding.
+//   kGeneral    chunks of 128-key tiles.  Every call can take it, and its
+//               workspace is the smallest.
+//   kFineChunks chunks of 32-key blocks (fp32), with more partials per row.
+//   kFewRows    the few-row kernels (bf16), with room for the logits.
+// A call takes the form of its dtype and rows if the workspace holds it, and
+// kGeneral otherwise, so that a workspace sized for a wider call serves it.
+enum class ScoreForm { kGeneral, kFineChunks, kFewRows };
+
 struct PrunePlan {
   std::vector<SeqDev> seqs;
   std::vector<TileDev> tiles;
@@ -104,17 +113,18 @@ struct PrunePlan {
   int64_t total_tok = 0;    // sum of n_tokens (tag bytes)
   int64_t max_tokens = 0;   // longest sequence
   int64_t total_stats = 0;  // (max, sum) partials
-  int64_t total_colpart = 0;
-  int64_t total_logits = 0; // stored logits of a few-row call, else 0
+  int64_t total_colpart = 0;  // column partials, or the logits of a few-row call
   int64_t total_kept = 0;
   int64_t total_ctr = 0;    // arrival counters (zeroed by the upload)
+  int64_t weighted = 0;     // keys times row groups over the call, the score passes' work
   int waves = 1;
   bool any_select = false;
   int max_planes = 0;       // most per-group partials of a key (general score kernels)
-  bool few = false;         // every sequence has at most kFewRows query rows per key head
+  bool few_rows = false;    // every sequence has at most kFewRows query rows per key head
+  ScoreForm form = ScoreForm::kGeneral;
   // Workspace layout (byte offsets).
   size_t off_seqs = 0, off_tiles = 0, off_ftiles = 0, off_tags = 0, off_ctr = 0, blob_bytes = 0;
-  size_t off_logits = 0, off_stats = 0, off_colpart = 0, off_hist = 0, off_cnt = 0, ws_bytes = 0;
+  size_t off_stats = 0, off_colpart = 0, off_hist = 0, off_cnt = 0, ws_bytes = 0;
 };
 
 // What the scores' last steps -- the sum over a key's per-group partials, the
@@ -128,8 +138,8 @@ struct PrunePlan {
 // the sums there, so the line lies at kSumPartials of them.
 enum ScoreTail { kTailInScores = 0, kDigitInSelect = 1, kSumInSelect = 2 };
 constexpr int64_t kSumPartials = 16384, kDigitRows = 12288;
-// few: the call runs the few-row kernels, which store whole scores.
-inline ScoreTail score_tail(const PrunePlan& pl, bool few) {
+inline ScoreTail score_tail(const PrunePlan& pl) {
+  const bool few = pl.form == ScoreForm::kFewRows;   // its kernels store whole scores
   if (pl.max_tokens > (few ? kSmallRows : kDigitRows)) return kTailInScores;
   return !few && pl.max_planes * pl.max_tokens <= kSumPartials ? kSumInSelect : kDigitInSelect;
 }
@@ -141,19 +151,21 @@ struct DevPtrs {
   FTileDev* ftiles;
   float2* stats;
   float* colpart;
-  float* logits;        // stored logits of a few-row call
   uint32_t* hist;       // [n_seq][2][2048] radix histograms
   uint32_t* cnt;        // [n_ftiles][3] per-tile keep counts
   uint32_t* ctr;        // arrival counters of the score kernels
 };
 
+// Validates the call and fills what no form changes.
 apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, int32_t hkv, int32_t d,
-                              apack_dtype dtype, PrunePlan& plan);
+                              PrunePlan& plan);
+// Chunks, tiles and workspace layout of the plan in one form.
+void lay_out_prune(PrunePlan& plan, ScoreForm form, int n_rep, int hkv);
 
 int64_t select_hist_words(int64_t n_seq);   // radix histogram words of n_seq sequences
 
-apack_status launch_select(const PrunePlan& pl, const DevPtrs& dp, bool few, int n_rep, int hkv, float* scores,
-                           int32_t* kept, hipStream_t stream);
+apack_status launch_select(const PrunePlan& pl, const DevPtrs& dp, int n_rep, int hkv, float* scores, int32_t* kept,
+                           hipStream_t stream);
 
 apack_status launch_prune(const PrunePlan& pl, const DevPtrs& dp, const InlineCall& in, apack_dtype dt, int d, int hq, int hkv,
                           const void* q, int64_t q_hs, const void* k, int64_t k_hs, float* scores,

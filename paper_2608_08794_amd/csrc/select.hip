@@ -481,15 +481,15 @@ __global__ __launch_bounds__(kST) void k_select_small(const SeqDev* __restrict__
 
 int64_t select_hist_words(int64_t n_seq) { return n_seq * 2 * kRadixBins; }
 
-apack_status launch_select(const PrunePlan& pl, const DevPtrs& dp, bool few, int n_rep, int hkv, float* scores,
-                           int32_t* kept, hipStream_t stream) {
+apack_status launch_select(const PrunePlan& pl, const DevPtrs& dp, int n_rep, int hkv, float* scores, int32_t* kept,
+                           hipStream_t stream) {
   const int nf = (int)pl.ftiles.size();
   if (nf == 0) return APACK_OK;
   apack_status st;
   // The scores and the first digit come from the score kernels, earlier on
   // this stream, or from k_select_small (ScoreTail).
   if (pl.max_tokens <= kSmallRows) {
-    const ScoreTail tail = score_tail(pl, few);
+    const ScoreTail tail = score_tail(pl);
     hipLaunchKernelGGL((tail == kSumInSelect ? k_select_small<true> : k_select_small<false>), dim3((unsigned)pl.seqs.size()), dim3(kST),
                        0, stream, dp.seqs, dp.tags, dp.colpart, n_rep, hkv, tail == kTailInScores ? 1 : 0,
                        scores, kept);

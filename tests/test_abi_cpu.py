@@ -110,6 +110,37 @@ def test_prune_query_reports_counts_and_workspace():
     assert ws.value > 0 and ws.value % 256 == 0
 
 
+def _prune_workspaces(n, q_len, hq, hkv, n_seq=1, dtype=0):
+    """(bytes that the query reports, least that the call accepts)."""
+    made = [_seq([(0, n // 4, 1), (n // 4, n - n // 4 - 1, 2)], n, q_len, tok_off=i * n, q_off=i * q_len)
+            for i in range(n_seq)]
+    seqs = [s for s, _ in made]
+    ws = ctypes.c_size_t(0)
+    assert A.library().apack_prune_layer_query(n_seq, (L.Seq * n_seq)(*seqs), hq, hkv, 128, None,
+                                               ctypes.byref(ws)) == 0
+    st, msg = _prune(seqs, hq=hq, hkv=hkv, d=128, dtype=dtype, cap=1 << 30, ws_bytes=0, q_rows=n_seq * q_len,
+                     k_rows=n_seq * n, kept=FAKE + (5 << 34))
+    assert st == 4, msg
+    return ws.value, int(re.search(r"< (\d+) needed", msg).group(1))
+
+
+# n, query rows, heads, key heads, sequences; the workspace of the passes that
+# every call can take.
+@pytest.mark.parametrize("n,q_len,hq,hkv,n_seq,least", [
+    (94028, 1, 28, 4, 1, 1748736), (94028, 2, 28, 4, 1, 1748736), (94028, 128, 28, 4, 1, 4043776),
+    (94028, 16, 32, 32, 1, 12537344), (9390, 1, 28, 4, 1, 255488), (9390, 64, 28, 4, 1, 710144),
+    (1312, 64, 28, 4, 1, 198400), (700, 4, 28, 4, 3, 124672),
+])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_prune_accepts_the_workspace_of_its_general_passes(n, q_len, hq, hkv, n_seq, least, dtype):
+    """The few-row and fp32 forms want more room; a call without it is not
+    refused, so a workspace sized for a wider call serves a narrower one."""
+    query, needed = _prune_workspaces(n, q_len, hq, hkv, n_seq, dtype)
+    assert needed == least <= query
+    wider, _ = _prune_workspaces(n, max(q_len, 512 * hkv // hq), hq, hkv, n_seq, dtype)
+    assert needed <= wider
+
+
 @pytest.mark.parametrize("case,status", [
     ("hq_not_multiple", 2), ("bad_d", 7), ("bad_dtype", 3), ("span_outside", 2), ("span_unsorted", 2),
     ("bad_modality", 1), ("keep_range", 1), ("k_exceeds", 1), ("q_len0", 2), ("q_rows", 2),

@@ -693,3 +693,39 @@ def test_few_query_rows_ties_and_one_row_more():
     mean = torch.stack(want).mean(0)
     # fp32 logits and sums on both sides.
     assert float((got - mean).norm() / mean.norm()) < 4e-6
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,q_len,n", [
+    ("bf16", 28, 4, 128, 1, 9390), ("bf16", 8, 8, 64, 16, 1025), ("bf16", 28, 4, 128, 1, 40013),
+    ("f32", 28, 4, 128, 1, 3000), ("f32", 16, 2, 128, 64, 4000),
+])
+def test_least_workspace(dtype, hq, hkv, d, q_len, n):
+    """A workspace without room for the few-row logits or the finer fp32
+    partials: the general passes run (with few rows, several threads of pass 2
+    merge each row's partials), within the bytes given, and agree with the
+    oracle and with the call of a full workspace."""
+    import re
+    import paper_2608_08794_amd as A
+    specs = [([(0, n // 4, A_), (n // 4, n // 2, V_)], n, q_len, (0.5, 0.3)),
+             ([(3, 200, A_), (210, 333, V_)], 560, q_len, (0.35, 0.8)), ([], 17, q_len, (0.5, 0.5))]
+    for specs in (specs[:1], specs):   # descriptors by value, and uploaded
+        case = _synthetic(dtype, hq, hkv, d, specs, seed=83)
+        w_scores, w_kept, w_n, margins = _oracle(case)
+        assert min(margins) >= 1e-2, margins
+        q, k = to_dev(case.q, dtype), to_dev(case.k, dtype)
+        with pytest.raises(A.ApackError) as e:
+            A.apack_prune_layer(q, k, case.seqs, workspace=torch.empty(256, dtype=torch.uint8, device="cuda"))
+        least = int(re.search(r"< (\d+) needed", str(e.value)).group(1))
+        full = A.apack_prune_layer_query(case.seqs, hq, hkv, d)[1]
+        log(f"[workspace] {dtype} {hq}/{hkv} rows {n}: least {least} of {full}")
+        assert least < full
+        buf = torch.full((least + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+        scores, kept, n_kept = A.apack_prune_layer(q, k, case.seqs, workspace=buf[:least])
+        torch.cuda.synchronize()
+        assert n_kept == w_n
+        np.testing.assert_array_equal(kept.cpu().numpy().astype(np.int64), w_kept)
+        _check_scores(scores.cpu().numpy(), w_scores, case.seqs, dtype)
+        assert bool((buf[least:] == 0xA5).all())
+        wide = A.apack_prune_layer(q, k, case.seqs)[0]
+        # fp32 logits, exponentials and sums on both sides.
+        assert float((scores - wide).double().norm() / wide.double().norm()) < 4e-6
