@@ -340,13 +340,43 @@ __device__ __forceinline__ TileDev inline_tile(const SeqDev& sq, int b) {
   return t;
 }
 
+// Where the first score kernel has its descriptors from: by value (and the
+// arrays in the workspace that it fills for the later kernels), or uploaded.
+// Each instantiation sees one source: with both behind a test at run time, and
+// the uploaded arrays written in the same kernel, the compiler held both in
+// vector registers (k_rowstats<bf16, 128, 7>: 256 VGPRs and 28 bytes of
+// scratch a lane; 240 uploaded and 244 by value now, and no scratch: 9390 rows
+// 17.2 -> 15.6 us, three prunes of a 94028-row clip 245.7 -> 241.2).
+template <bool BY_VALUE>
+struct Descriptors;
+template <>
+struct Descriptors<true> {
+  InlineCall in;
+  SeqDev* seqs;
+  TileDev* tiles;
+  FTileDev* ftiles;
+  uint8_t* tags;
+  uint32_t* ctr;
+  __device__ __forceinline__ TileDev tile() const { return inline_tile(in.seq, blockIdx.x); }
+  __device__ __forceinline__ const SeqDev& seq(const TileDev&) const { return in.seq; }
+};
+template <>
+struct Descriptors<false> {
+  const SeqDev* seqs;
+  const TileDev* tiles;
+  const uint8_t* tags;
+  __device__ __forceinline__ TileDev tile() const { return tiles[blockIdx.x]; }
+  __device__ __forceinline__ const SeqDev& seq(const TileDev& tl) const { return seqs[tl.seq]; }
+};
+
 // What the first score kernel does for a call with descriptors by value: the
 // chunk's mask and (once per chunk) tags from the spans, and the arrays that
 // the later kernels read, spread over the workgroups.
 template <int NT>
-__device__ __forceinline__ void inline_setup(const InlineCall& in, const TileDev& tl, const SeqDev& sq, SeqDev* seqs,
-                                             TileDev* tiles, FTileDev* ftiles, uint8_t* tg, uint32_t* ctr,
-                                             int64_t key_begin, int64_t key_end, int n_mask, float* lmask) {
+__device__ __forceinline__ void chunk_mask(const Descriptors<true>& de, const TileDev& tl, const SeqDev& sq,
+                                           int64_t key_begin, int64_t key_end, int n_mask, float* lmask) {
+  const InlineCall& in = de.in;
+  uint8_t* tg = de.tags + sq.tag_off;
   const int tid = threadIdx.x;
   const bool write_tags = tl.g == 0 && tl.rg == 0;
   for (int i = tid; i < n_mask; i += NT) {
@@ -358,20 +388,21 @@ __device__ __forceinline__ void inline_setup(const InlineCall& in, const TileDev
     if (write_tags && r < key_end) tg[r] = (uint8_t)tag;
   }
   const int stride = (int)gridDim.x * NT, t = (int)blockIdx.x * NT + tid;
-  for (int i = t; i < in.n_ctr; i += stride) ctr[i] = 0;
-  for (int i = t; i < sq.n_ftiles; i += stride) ftiles[i] = FTileDev{0, i};
-  if (tid == 0) tiles[blockIdx.x] = tl;
+  for (int i = t; i < in.n_ctr; i += stride) de.ctr[i] = 0;
+  for (int i = t; i < sq.n_ftiles; i += stride) de.ftiles[i] = FTileDev{0, i};
+  if (tid == 0) de.tiles[blockIdx.x] = tl;
   if (blockIdx.x == 0 && tid < (int)(sizeof(SeqDev) / 4))
-    reinterpret_cast<uint32_t*>(seqs)[tid] = reinterpret_cast<const uint32_t*>(&in.seq)[tid];
+    reinterpret_cast<uint32_t*>(de.seqs)[tid] = reinterpret_cast<const uint32_t*>(&in.seq)[tid];
 }
 
 // The chunk's mask from uploaded tags: read in batches of 8 per thread, all
 // in flight together (the index is clamped to a valid row; rows past the
 // chunk get -inf).
 template <int NT>
-__device__ __forceinline__ void load_mask(const uint8_t* tg, int64_t key_begin, int64_t key_end, int n_mask,
-                                          float* lmask) {
+__device__ __forceinline__ void chunk_mask(const Descriptors<false>& de, const TileDev&, const SeqDev& sq,
+                                           int64_t key_begin, int64_t key_end, int n_mask, float* lmask) {
   constexpr int kB = 8;
+  const uint8_t* tg = de.tags + sq.tag_off;
   const int tid = threadIdx.x;
   for (int b0 = 0; b0 < n_mask; b0 += kB * NT) {
     uint8_t t[kB];
@@ -396,11 +427,9 @@ __device__ __forceinline__ int tile_blocks(int64_t t0, int64_t key_end) {
   return sizeof(T) == 2 ? NKB : (int)min((int64_t)NKB, (key_end - t0 + kKeyBlock - 1) / kKeyBlock);
 }
 
-template <class T, int D, int NW, int S>
-__global__ __launch_bounds__(NW * kWave) void k_rowstats(const InlineCall in, SeqDev* __restrict__ seqs,
-                                                         TileDev* __restrict__ tiles,
-                                                         FTileDev* __restrict__ ftiles, uint8_t* __restrict__ tags,
-                                                         uint32_t* __restrict__ ctr, const T* __restrict__ q, int64_t q_hs,
+template <class T, int D, int NW, int S, bool BY_VALUE>
+__global__ __launch_bounds__(NW * kWave) void k_rowstats(const Descriptors<BY_VALUE> de, const T* __restrict__ q,
+                                                         int64_t q_hs,
                                                          const T* __restrict__ k, int64_t k_hs,
                                                          int n_rep, float scale_log2,
                                                          float2* __restrict__ stats, uint32_t* __restrict__ zero,
@@ -413,9 +442,8 @@ __global__ __launch_bounds__(NW * kWave) void k_rowstats(const InlineCall in, Se
   // before the loop so that no tile waits on a load of its tags.
   __shared__ __attribute__((aligned(16))) float lmask[kMaxChunk];
 
-  const bool inl = in.n_spans >= 0;
-  const TileDev tl = inl ? inline_tile(in.seq, blockIdx.x) : tiles[blockIdx.x];
-  const SeqDev sq = inl ? in.seq : seqs[tl.seq];
+  const TileDev tl = de.tile();
+  const SeqDev sq = de.seq(tl);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rows_g = n_rep * sq.q_len;
   const int rg_end = min(rows_g, (tl.rg + 1) * sq.rows_per_rg);
@@ -443,12 +471,7 @@ __global__ __launch_bounds__(NW * kWave) void k_rowstats(const InlineCall in, Se
   QFrags<T, D> qfr;
   auto& qf = qfr.v;
   if (active) load_q<T, D>(qfr, q, q_hs, sq, tl.g, n_rep, row0, lane);
-  uint8_t* tg = tags + sq.tag_off;
-
-  if (inl)
-    inline_setup<NW * kWave>(in, tl, sq, seqs, tiles, ftiles, tg, ctr, key_begin, key_end, n_tiles * kKeyTile, lmask);
-  else
-    load_mask<NW * kWave>(tg, key_begin, key_end, n_tiles * kKeyTile, lmask);
+  chunk_mask<NW * kWave>(de, tl, sq, key_begin, key_end, n_tiles * kKeyTile, lmask);
   // One pass over the chunk's key tiles: with exact = false each lane sums
   // against its fixed reference (row_update_ref), with exact = true it keeps
   // the online maximum (row_update).  The first is taken; the second redoes
@@ -895,18 +918,16 @@ constexpr int kFewKeys = kFewWaves * kFewBlocks * 16;     // keys of one step of
 constexpr int kFewCols = 256;                             // keys per workgroup of pass 2
 static_assert(kRowTile % kFewCols == 0 && kMaxChunk % kKeyTile == 0, "pass 2 cuts row tiles evenly");
 
-template <int D>
+template <int D, bool BY_VALUE>
 __global__ __launch_bounds__(kFewWaves * kWave) void k_few_logits(
-    const InlineCall in, SeqDev* __restrict__ seqs, TileDev* __restrict__ tiles, FTileDev* __restrict__ ftiles,
-    uint8_t* __restrict__ tags, uint32_t* __restrict__ ctr, const bf16_t* __restrict__ q, int64_t q_hs,
-    const bf16_t* __restrict__ k, int64_t k_hs, int n_rep, float scale_log2, float2* __restrict__ stats,
-    float* __restrict__ logits, uint32_t* __restrict__ zero, int64_t zero_n) {
+    const Descriptors<BY_VALUE> de, const bf16_t* __restrict__ q, int64_t q_hs, const bf16_t* __restrict__ k,
+    int64_t k_hs, int n_rep, float scale_log2, float2* __restrict__ stats, float* __restrict__ logits,
+    uint32_t* __restrict__ zero, int64_t zero_n) {
   constexpr int KS = D / 32, NT = kFewWaves * kWave;
   __shared__ __attribute__((aligned(16))) float lmask[kMaxChunk];
   __shared__ float2 wstat[kFewWaves][kFewRows];
-  const bool inl = in.n_spans >= 0;
-  const TileDev tl = inl ? inline_tile(in.seq, blockIdx.x) : tiles[blockIdx.x];
-  const SeqDev sq = inl ? in.seq : seqs[tl.seq];
+  const TileDev tl = de.tile();
+  const SeqDev sq = de.seq(tl);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rows = n_rep * sq.q_len;
   const int64_t key_begin = (int64_t)tl.chunk * sq.chunk;
@@ -946,10 +967,7 @@ __global__ __launch_bounds__(kFewWaves * kWave) void k_few_logits(
     const int64_t z0 = (int64_t)blockIdx.x * per, z1 = min(zero_n, z0 + per);
     for (int64_t i = z0 + tid; i < z1; i += NT) zero[i] = 0;
   }
-  if (inl)
-    inline_setup<NT>(in, tl, sq, seqs, tiles, ftiles, tags + sq.tag_off, ctr, key_begin, key_end, n_mask, lmask);
-  else
-    load_mask<NT>(tags + sq.tag_off, key_begin, key_end, n_mask, lmask);
+  chunk_mask<NT>(de, tl, sq, key_begin, key_end, n_mask, lmask);
   __syncthreads();
 
   // Stored logits of this group's row l % 16: keys 4 (l / 16) .. + 3 of each
@@ -1108,15 +1126,26 @@ __global__ __launch_bounds__(kFewWaves * kWave) void k_few_colsum(SeqDev* __rest
 // ---------------------------------------------------------------------------
 // Host launch sequence.
 // ---------------------------------------------------------------------------
+// f(descriptors) with the call's source of them.
+template <class F>
+void with_descriptors(const DevPtrs& dp, const InlineCall& in, F f) {
+  if (in.n_spans >= 0)
+    f(Descriptors<true>{in, dp.seqs, dp.tiles, dp.ftiles, dp.tags, dp.ctr}, std::true_type{});
+  else
+    f(Descriptors<false>{dp.seqs, dp.tiles, dp.tags}, std::false_type{});
+}
+
 template <class T, int D, int NW, int S = key_stages<T, D, NW>()>
 apack_status launch_scores_t(const PrunePlan& pl, const DevPtrs& dp, const InlineCall& in, const void* q, int64_t q_hs,
                              const void* k, int64_t k_hs, int n_rep, int hkv, float* scores, hipStream_t stream) {
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   const int nt = (int)pl.tiles.size();
   if (nt > 0) {
-    hipLaunchKernelGGL((k_rowstats<T, D, NW, S>), dim3(nt), dim3(NW * kWave), 0, stream, in, dp.seqs, dp.tiles,
-                       dp.ftiles, dp.tags, dp.ctr, (const T*)q, q_hs, (const T*)k, k_hs, n_rep, scale_log2, dp.stats, dp.hist,
-                       pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : (int64_t)0);
+    with_descriptors(dp, in, [&](const auto& de, auto by_value) {
+      hipLaunchKernelGGL((k_rowstats<T, D, NW, S, decltype(by_value)::value>), dim3(nt), dim3(NW * kWave), 0, stream,
+                         de, (const T*)q, q_hs, (const T*)k, k_hs, n_rep, scale_log2, dp.stats, dp.hist,
+                         pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : (int64_t)0);
+    });
     APACK_CHECK(launch_status("k_rowstats") == APACK_OK, APACK_E_HIP, "%s", apack_last_error());
     hipLaunchKernelGGL((k_colsum<T, D, NW, S>), dim3(nt), dim3(NW * kWave), 0, stream, dp.seqs, dp.tiles, dp.tags,
                        (const T*)q, q_hs, (const T*)k, k_hs, n_rep, hkv, scale_log2, dp.stats, dp.colpart, scores,
@@ -1147,9 +1176,11 @@ apack_status launch_few(const PrunePlan& pl, const DevPtrs& dp, const InlineCall
   const float scale_log2 = (float)(1.4426950408889634 / std::sqrt((double)D));
   const unsigned nt = (unsigned)pl.tiles.size();
   if (nt == 0) return APACK_OK;
-  hipLaunchKernelGGL(k_few_logits<D>, dim3(nt), dim3(kFewWaves * kWave), 0, stream, in, dp.seqs, dp.tiles, dp.ftiles,
-                     dp.tags, dp.ctr, (const bf16_t*)q, q_hs, (const bf16_t*)k, k_hs, n_rep, scale_log2, dp.stats,
-                     dp.colpart, dp.hist, pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : (int64_t)0);
+  with_descriptors(dp, in, [&](const auto& de, auto by_value) {
+    hipLaunchKernelGGL((k_few_logits<D, decltype(by_value)::value>), dim3(nt), dim3(kFewWaves * kWave), 0, stream, de,
+                       (const bf16_t*)q, q_hs, (const bf16_t*)k, k_hs, n_rep, scale_log2, dp.stats, dp.colpart, dp.hist,
+                       pl.any_select ? select_hist_words((int64_t)pl.seqs.size()) : (int64_t)0);
+  });
   apack_status st = launch_status("k_few_logits");
   if (st != APACK_OK) return st;
   hipLaunchKernelGGL(k_few_colsum, dim3((unsigned)pl.ftiles.size() * (kRowTile / kFewCols)), dim3(kFewWaves * kWave), 0,
