@@ -74,18 +74,21 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   // of a frame's co-timed audio rows and visual rows, each padded to whole
   // tiles, sized for the largest frame.
   if (p->alignment == APACK_ALIGN_SPATIAL_CKA) {
-    int64_t nt = 0;
+    int64_t nt = 0, stacked = 0;
     for (int s = 0; s < n_seq; ++s) {
       const apack_av_seq& a = seqs[s];
       if (a.n_frames == 0) continue;
       const int64_t bin = (a.n_audio + a.n_frames - 1) / a.n_frames + 1;
       nt = std::max<int64_t>(nt, (bin + 15) / 16 + (a.tokens_per_frame + 15) / 16);
+      stacked = std::max<int64_t>(stacked, (bin + a.tokens_per_frame + 15) / 16);
     }
     const int64_t nb = (nt + 1) / 2;
     pl.spatial_blocks = (int32_t)(nb * (nb + 1) / 2);
-    // Sums are kept per block; the workspace has room for them per tile, as
-    // callers who keep one across versions have sized it.
-    pl.spatial_slots = (int32_t)(nt * (nt + 1) / 2);
+    // The workspace has a slot per tile of the stacked rows, the size it had
+    // when sums were kept per tile, so that one of that size stays enough.
+    // That covers the blocks: padding the parts apart adds at most one tile a
+    // side, and nb is half of that.
+    pl.spatial_slots = (int32_t)(stacked * (stacked + 1) / 2);
   }
   pl.total_frames = frames;
   pl.total_tokens = vis_end;

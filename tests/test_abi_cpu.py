@@ -484,3 +484,26 @@ def test_spatial_alignment_sizes_its_tile_sums():
     assert sizes["gated_cka"] == sizes["cka"] == sizes["av_cosine"]
     # 13 or 14 audio rows + 144 visual rows -> 10 tiles a side, 55 tiles, 3 sums each, per frame.
     assert sizes["spatial_cka"] - sizes["gated_cka"] >= 30 * 55 * 3 * 8
+
+
+@pytest.mark.parametrize("n_frames,per_frame,n_audio", [
+    (40, 98, 520), (30, 144, 375), (1, 1, 1), (270, 1, 64), (3, 17, 40), (10, 256, 8000), (7, 16, 105), (5, 100, 55),
+])
+def test_spatial_workspace_is_one_slot_per_tile_of_the_stacked_rows(n_frames, per_frame, n_audio):
+    # Audio and visual rows are padded to whole tiles apart, which adds a tile
+    # a side for many shapes (98 + 14 rows: 8 against 7), but the workspace
+    # stays that of the rows stacked, which covers the 2 x 2 blocks of either.
+    arr = (L.AVSeq * 1)(_av(n_frames=n_frames, per_frame=per_frame, n_audio=n_audio))
+    sizes = []
+    for name in ("gated_cka", "spatial_cka"):
+        p = A.apack_dyn_params_default()
+        p.alignment = L.ALIGNMENTS[name]
+        ws = ctypes.c_size_t(0)
+        assert A.library().apack_score_dynamics_query(1, arr, 64, ctypes.byref(p), None, ctypes.byref(ws)) == 0
+        sizes.append(ws.value)
+    bin_rows = -(-n_audio // n_frames) + 1
+    stacked = -(-(bin_rows + per_frame) // 16)
+    blocks = -(-(-(-bin_rows // 16) + -(-per_frame // 16)) // 2)
+    slots = stacked * (stacked + 1) // 2
+    assert sizes[1] - sizes[0] == -(-n_frames * slots * 24 // 256) * 256
+    assert blocks * (blocks + 1) // 2 <= slots
