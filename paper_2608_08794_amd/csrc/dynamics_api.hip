@@ -92,17 +92,22 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   }
   pl.total_frames = frames;
   pl.total_tokens = vis_end;
+  pl.clip_tokens = tokens;
   pl.total_audio = aud_end;
   pl.total_kept = kept;
   pl.total_gram = gram;
-  // Gate GEMM tiles of either kernel, in the order its launch expects.
-  pl.gemm = gate_gemm_any_tiles(pl.clips);
+  return APACK_OK;
+}
+
+void plan_gate_tiles(DynPlan& pl, bool use256) {
+  pl.use256 = use256;
+  pl.gemm = use256 ? gate_gemm256_tiles(pl.clips, &pl.gemm256_bi) : gate_gemm_any_tiles(pl.clips);
   pl.gemm_tiles = (int64_t)pl.gemm.size();
-  if (dim % kGemm256K == 0) pl.gemm256 = gate_gemm256_tiles(pl.clips, &pl.gemm256_bi);
-  // The blob holds whichever list the call uses.
-  const size_t n_tiles = std::max(pl.gemm.size(), pl.gemm256.size());
-  // Workspace layout.
-  const int64_t nc = n_seq;
+}
+
+void lay_out_dyn(DynPlan& pl, int32_t dim, size_t n_tiles) {
+  const int64_t nc = (int64_t)pl.clips.size(), frames = pl.total_frames, vis_end = pl.total_tokens,
+                aud_end = pl.total_audio;
   Carver c(nullptr);
   c.take<ClipDev>(nc);
   pl.off_frames = c.used;
@@ -137,11 +142,11 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   pl.off_plan = c.used;
   c.take<FramePlanDev>(frames);
   pl.off_gram = c.used;
-  c.take<double>(gram);
+  c.take<double>(pl.total_gram);
   pl.off_scratch = c.used;
   c.take<double>(16 * (frames + nc + 1));
   pl.off_sim = c.used;
-  c.take<double>(tokens);
+  c.take<double>(pl.clip_tokens);
   pl.off_spatial = c.used;
   c.take<double>((size_t)frames * pl.spatial_slots * 3);
   pl.off_anchors = c.used;
@@ -149,7 +154,6 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   pl.off_sqp = c.used;
   c.take<double>((size_t)((dim + kPoolSlice - 1) / kPoolSlice) * (vis_end + aud_end));
   pl.ws_bytes = std::max<size_t>(c.used, kAlign);
-  return APACK_OK;
 }
 
 }  // namespace apack
@@ -167,7 +171,16 @@ apack_status apack_score_dynamics_query(int32_t n_seq, const apack_av_seq* seqs,
   if (st != APACK_OK) return st;
   if (n_kept_visual)
     for (int s = 0; s < n_seq; ++s) n_kept_visual[s] = pl.budgets[s];
-  if (workspace_bytes) *workspace_bytes = pl.ws_bytes;
+  if (workspace_bytes) {   // room for the tile list of either dtype
+    size_t n_tiles = 0;
+    for (bool use256 : {false, true}) {
+      if (use256 && dim % kGemm256K != 0) continue;
+      plan_gate_tiles(pl, use256);
+      n_tiles = std::max(n_tiles, pl.gemm.size());
+    }
+    lay_out_dyn(pl, dim, n_tiles);
+    *workspace_bytes = pl.ws_bytes;
+  }
   return APACK_OK;
 }
 
@@ -183,6 +196,9 @@ apack_status apack_score_dynamics(int32_t n_seq, const apack_av_seq* seqs, apack
   DynPlan pl;
   apack_status st = build_dyn_plan(n_seq, seqs, dim, p, pl);
   if (st != APACK_OK) return st;
+  // bf16 inputs with dim a multiple of 64 take the 256-column gate GEMM.
+  plan_gate_tiles(pl, dtype == APACK_BF16 && dim % kGemm256K == 0);
+  lay_out_dyn(pl, dim, pl.gemm.size());
   const size_t es = dtype_size(dtype);
   APACK_CHECK(visual_rows >= 0 && audio_rows >= 0 && query_rows >= 0, APACK_E_SHAPE, "negative row count");
   for (int s = 0; s < n_seq; ++s) {
@@ -222,12 +238,6 @@ apack_status apack_score_dynamics(int32_t n_seq, const apack_av_seq* seqs, apack
   APACK_CHECK(workspace_bytes >= pl.ws_bytes, APACK_E_WORKSPACE, "workspace of %zu bytes < %zu needed",
               workspace_bytes, pl.ws_bytes);
 
-  // bf16 inputs with dim a multiple of 64 take the 256 x 256 gate GEMM.
-  if (dtype == APACK_BF16 && !pl.gemm256.empty()) {
-    pl.use256 = true;
-    pl.gemm = pl.gemm256;
-    pl.gemm_tiles = (int64_t)pl.gemm.size();
-  }
   Staging* blk;
   void* host;
   if ((st = staging_acquire(pl.blob_bytes, &blk, &host)) != APACK_OK) return st;

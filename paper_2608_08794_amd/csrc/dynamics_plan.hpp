@@ -60,14 +60,14 @@ struct DynPlan {
   std::vector<FrameDev> frames;      // one entry per frame of every clip
   std::vector<int64_t> budgets;
   int64_t total_frames = 0, total_tokens = 0, total_audio = 0, total_kept = 0, total_gram = 0;
+  int64_t clip_tokens = 0;           // visual tokens of the clips (total_tokens also counts rows between them)
   int max_per_frame = 1;
   int64_t gemm_tiles = 0;            // gate GEMM workgroups over all clips
   int32_t spatial_slots = 0;         // slots of three sums per frame in the workspace, at least spatial_blocks
   int32_t spatial_blocks = 0;        // spatial CKA Gram blocks (2 x 2 tiles) per frame (0 unless selected)
-  std::vector<GemmTileDev> gemm;
-  std::vector<GemmTileDev> gemm256;  // 256 x 256 tiles (dim a multiple of 64), XCD-ordered
-  int gemm256_bi = 8;                // their rows / 32
-  bool use256 = false;               // set per call: bf16 inputs and gemm256 planned
+  std::vector<GemmTileDev> gemm;     // their tiles, in the order the launch expects
+  bool use256 = false;               // of k_gate_gemm256, else of k_gate_gemm_any
+  int gemm256_bi = 8;                // rows / 32 of the former's tiles
   // Workspace layout (byte offsets).
   size_t off_clips = 0, off_frames = 0, off_gemm = 0, blob_bytes = 0;
   size_t off_v = 0, off_a = 0, off_q = 0, off_band_v = 0, off_band_a = 0, off_vq = 0, off_qq = 0;
@@ -100,8 +100,13 @@ struct FramePlanDev {
 };
 
 
+// Validates the call and fills what its dtype does not change.
 apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim, const apack_dyn_params* p,
                             DynPlan& plan);
+// The gate GEMM's tile list of one of its kernels.
+void plan_gate_tiles(DynPlan& plan, bool use256);
+// Workspace layout of the plan with room for n_tiles of them.
+void lay_out_dyn(DynPlan& plan, int32_t dim, size_t n_tiles);
 
 struct DynPtrs {
   ClipDev* clips;
@@ -114,8 +119,8 @@ struct DynPtrs {
   int32_t* anchors;  // first frame of each segment, clip c's at frame_off + m
 };
 
-// The gate GEMM on 256 x 256 tiles for bf16 inputs whose dim is a multiple
-// of 64 (gate_gemm.hip); `tiles` holds one tile per workgroup, already in
+// The gate GEMM on tiles of 32 bi x 256 for bf16 inputs whose dim is a
+// multiple of 64 (gate_gemm.hip); `tiles` holds one tile per workgroup, already in
 // the order the launch expects.
 apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int bi, int dim,
                                  const uint16_t* xv, const uint16_t* xa, const double* na, uint32_t* maxkey,
@@ -127,7 +132,7 @@ apack_status launch_gate_gemm_any(const ClipDev* clips, const GemmTileDev* tiles
                                   const void* xv, const void* xa, const double* nv, const double* na, uint32_t* maxkey,
                                   hipStream_t stream);
 std::vector<GemmTileDev> gate_gemm_any_tiles(const std::vector<ClipDev>& clips);
-constexpr int kGemm256K = 64;   // dim must be a multiple of this for the 256-tile kernel
+constexpr int kGemm256K = 64;   // dim must be a multiple of this for k_gate_gemm256
 constexpr int kPoolSlice = 512;  // embedding elements per coarse-pass block (8 per lane)
 
 apack_status launch_dynamics(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& prm, apack_dtype dt,
