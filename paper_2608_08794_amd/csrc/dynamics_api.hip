@@ -2,6 +2,7 @@
 // validation, planning, descriptor upload and the launch sequence.
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 
 #include "common.hpp"
@@ -63,6 +64,7 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
     tokens += nv;
     kept += c.budget;
     gram += nv * a.tokens_per_frame;
+    pl.least_tiles += (a.n_audio + 127) / 128 * ((nv + 127) / 128);
     const int64_t nb = (a.tokens_per_frame + 31) / 32;
     pl.gram_items += (int64_t)a.n_frames * (nb * (nb + 1) / 2);
     vis_end = std::max(vis_end, a.vis_off + nv);
@@ -99,9 +101,10 @@ apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim
   return APACK_OK;
 }
 
-void plan_gate_tiles(DynPlan& pl, bool use256) {
+void plan_gate_tiles(DynPlan& pl, bool use256, bool short_list) {
+  const int64_t most = short_list ? pl.least_tiles : INT64_MAX;
   pl.use256 = use256;
-  pl.gemm = use256 ? gate_gemm256_tiles(pl.clips, &pl.gemm256_bi) : gate_gemm_any_tiles(pl.clips);
+  pl.gemm = use256 ? gate_gemm256_tiles(pl.clips, most, &pl.gemm256_bi) : gate_gemm_any_tiles(pl.clips, most);
   pl.gemm_tiles = (int64_t)pl.gemm.size();
 }
 
@@ -175,7 +178,7 @@ apack_status apack_score_dynamics_query(int32_t n_seq, const apack_av_seq* seqs,
     size_t n_tiles = 0;
     for (bool use256 : {false, true}) {
       if (use256 && dim % kGemm256K != 0) continue;
-      plan_gate_tiles(pl, use256);
+      plan_gate_tiles(pl, use256, false);
       n_tiles = std::max(n_tiles, pl.gemm.size());
     }
     lay_out_dyn(pl, dim, n_tiles);
@@ -197,8 +200,13 @@ apack_status apack_score_dynamics(int32_t n_seq, const apack_av_seq* seqs, apack
   apack_status st = build_dyn_plan(n_seq, seqs, dim, p, pl);
   if (st != APACK_OK) return st;
   // bf16 inputs with dim a multiple of 64 take the 256-column gate GEMM.
-  plan_gate_tiles(pl, dtype == APACK_BF16 && dim % kGemm256K == 0);
+  const bool use256 = dtype == APACK_BF16 && dim % kGemm256K == 0;
+  plan_gate_tiles(pl, use256, false);
   lay_out_dyn(pl, dim, pl.gemm.size());
+  if (workspace_bytes < pl.ws_bytes && pl.gemm_tiles > pl.least_tiles) {
+    plan_gate_tiles(pl, use256, true);
+    lay_out_dyn(pl, dim, pl.gemm.size());
+  }
   const size_t es = dtype_size(dtype);
   APACK_CHECK(visual_rows >= 0 && audio_rows >= 0 && query_rows >= 0, APACK_E_SHAPE, "negative row count");
   for (int s = 0; s < n_seq; ++s) {

@@ -63,6 +63,7 @@ struct DynPlan {
   int64_t clip_tokens = 0;           // visual tokens of the clips (total_tokens also counts rows between them)
   int max_per_frame = 1;
   int64_t gemm_tiles = 0;            // gate GEMM workgroups over all clips
+  int64_t least_tiles = 0;           // 128 x 128 tiles over all clips: the list length that any workspace holds
   int32_t spatial_slots = 0;         // slots of three sums per frame in the workspace, at least spatial_blocks
   int32_t spatial_blocks = 0;        // spatial CKA Gram blocks (2 x 2 tiles) per frame (0 unless selected)
   std::vector<GemmTileDev> gemm;     // their tiles, in the order the launch expects
@@ -103,8 +104,9 @@ struct FramePlanDev {
 // Validates the call and fills what its dtype does not change.
 apack_status build_dyn_plan(int32_t n_seq, const apack_av_seq* seqs, int32_t dim, const apack_dyn_params* p,
                             DynPlan& plan);
-// The gate GEMM's tile list of one of its kernels.
-void plan_gate_tiles(DynPlan& plan, bool use256);
+// The gate GEMM's tile list of one of its kernels; short_list: at most
+// least_tiles long, for a workspace that does not hold the usual one.
+void plan_gate_tiles(DynPlan& plan, bool use256, bool short_list);
 // Workspace layout of the plan with room for n_tiles of them.
 void lay_out_dyn(DynPlan& plan, int32_t dim, size_t n_tiles);
 
@@ -125,13 +127,14 @@ struct DynPtrs {
 apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int bi, int dim,
                                  const uint16_t* xv, const uint16_t* xa, const double* na, uint32_t* maxkey,
                                  hipStream_t stream);
-std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips, int* bi);
+// Their tiles, in a list of at most `most` (least_tiles or more).
+std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips, int64_t most, int* bi);
 // The same for fp32 inputs (scaled by their norms nv, na and split into bf16
 // parts) and for bf16 inputs of any other dim.
 apack_status launch_gate_gemm_any(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int dim, bool bf16,
                                   const void* xv, const void* xa, const double* nv, const double* na, uint32_t* maxkey,
                                   hipStream_t stream);
-std::vector<GemmTileDev> gate_gemm_any_tiles(const std::vector<ClipDev>& clips);
+std::vector<GemmTileDev> gate_gemm_any_tiles(const std::vector<ClipDev>& clips, int64_t most);
 constexpr int kGemm256K = 64;   // dim must be a multiple of this for k_gate_gemm256
 constexpr int kPoolSlice = 512;  // embedding elements per coarse-pass block (8 per lane)
 

@@ -537,8 +537,10 @@ __global__ __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 
 constexpr int kCUs = 256;
 constexpr double kRoundCost = 5.0;
 
-// One tile per workgroup, of tile_m audio rows by tile_n visual columns.
-static std::vector<GemmTileDev> gate_gemm_tiles(const std::vector<ClipDev>& clips, int tile_m, int tile_n) {
+// One tile per workgroup, of tile_m audio rows by tile_n visual columns; a
+// list that its padding takes past `most` goes without.
+static std::vector<GemmTileDev> gate_gemm_tiles(const std::vector<ClipDev>& clips, int tile_m, int tile_n,
+                                                int64_t most) {
   // A clip's row tiles are cut into bands of at most kBandRows (as even as
   // possible); a band's tiles, column block after column block, are cut into
   // eight runs of equal length, one per XCD.  A tall clip's audio then passes
@@ -571,6 +573,8 @@ static std::vector<GemmTileDev> gate_gemm_tiles(const std::vector<ClipDev>& clip
     for (int x = 0; x < kXcds; ++x) out.push_back(r < share[x].size() ? share[x][r] : GemmTileDev{-1, 0, 0, 0});
   // Trailing padding only costs empty workgroups; drop it.
   while (!out.empty() && out.back().clip < 0) out.pop_back();
+  if ((int64_t)out.size() > most)
+    out.erase(std::remove_if(out.begin(), out.end(), [](const GemmTileDev& t) { return t.clip < 0; }), out.end());
   return out;
 }
 
@@ -582,7 +586,7 @@ static std::vector<GemmTileDev> gate_gemm_tiles(const std::vector<ClipDev>& clip
 // 4 s 68 and 36 (bi 2), 20 s 70 and 35 (2), 30 s 72 and 49 (4), 45 s 87 and 87
 // (8), 60 s 158 and 149 (7), 100 s 412 and 409 (8); a round takes 77 us with
 // bi 8, 73 with 7, 60 with 6, 55 with 5, 48 with 4, 40 with 3 and 33 with 2.
-std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips, int* bi_out) {
+std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips, int64_t most, int* bi_out) {
   int best = 8;
   double best_cost = 0.0;
   for (int bi = 8; bi >= 2; --bi) {
@@ -590,16 +594,16 @@ std::vector<GemmTileDev> gate_gemm256_tiles(const std::vector<ClipDev>& clips, i
     for (const ClipDev& c : clips)
       n += ((c.n_audio + 32 * bi - 1) / (32 * bi)) * (((int64_t)c.n_frames * c.per_frame + kTileN - 1) / kTileN);
     const double cost = (double)((n + kCUs - 1) / kCUs) * (bi + kRoundCost);
-    if (bi == 8 || cost < best_cost) {
+    if (bi == 8 || (n <= most && cost < best_cost)) {   // tiles of 256 x 256 are never more than `most`
       best = bi;
       best_cost = cost;
     }
   }
   *bi_out = best;
-  return gate_gemm_tiles(clips, 32 * best, kTileN);
+  return gate_gemm_tiles(clips, 32 * best, kTileN, most);
 }
-std::vector<GemmTileDev> gate_gemm_any_tiles(const std::vector<ClipDev>& clips) {
-  return gate_gemm_tiles(clips, kAnyM, kAnyN);
+std::vector<GemmTileDev> gate_gemm_any_tiles(const std::vector<ClipDev>& clips, int64_t most) {
+  return gate_gemm_tiles(clips, kAnyM, kAnyN, most);
 }
 
 apack_status launch_gate_gemm256(const ClipDev* clips, const GemmTileDev* tiles, int64_t n_tiles, int bi, int dim,

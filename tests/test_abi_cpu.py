@@ -507,3 +507,21 @@ def test_spatial_workspace_is_one_slot_per_tile_of_the_stacked_rows(n_frames, pe
     slots = stacked * (stacked + 1) // 2
     assert sizes[1] - sizes[0] == -(-n_frames * slots * 24 // 256) * 256
     assert blocks * (blocks + 1) // 2 <= slots
+
+
+@pytest.mark.parametrize("n_frames,per_frame,n_audio,dim,least", [
+    (20, 1, 7612, 64, 155904), (2, 17, 6150, 512, 130048), (1, 98, 7974, 64, 214784), (120, 144, 1500, 3584, None),
+])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_score_accepts_the_workspace_of_128_row_gate_tiles(n_frames, per_frame, n_audio, dim, least, dtype):
+    """The gate GEMM's lower tiles and the padding of its list may want more
+    room than a list of 128 x 128 tiles; a call without it is not refused."""
+    seqs = [_av(n_frames=n_frames, per_frame=per_frame, n_audio=n_audio)]
+    p = A.apack_dyn_params_default()
+    ws = ctypes.c_size_t(0)
+    assert A.library().apack_score_dynamics_query(1, (L.AVSeq * 1)(*seqs), dim, ctypes.byref(p), None,
+                                                  ctypes.byref(ws)) == 0
+    st, msg, _ = _score(seqs, dim=dim, dtype=dtype, vrows=n_frames * per_frame, arows=n_audio, ws_bytes=0)
+    assert st == 4, msg
+    needed = int(re.search(r"< (\d+) needed", msg).group(1))
+    assert needed <= (ws.value if least is None else min(least, ws.value))

@@ -407,6 +407,29 @@ def test_gate_gemm_tile_heights(audio, visual, dim):
     np.testing.assert_allclose(got, want, rtol=0, atol=tol)
 
 
+@pytest.mark.parametrize("audio,visual,dim", [(7612, 20, 64), (6150, 34, 512)])
+def test_gate_gemm_in_the_least_workspace(audio, visual, dim):
+    """A workspace without room for the list of low tiles takes higher ones:
+    the same bits, within the bytes given."""
+    import re
+    import paper_2608_08794_amd as A
+    rng = np.random.default_rng(audio)
+    xv, xa = (to_dev(W.to_bf16_bits(rng.standard_normal((n, dim)).astype(np.float32)), "bf16")
+              for n in (visual, audio))
+    clip = dict(n_frames=visual, per_frame=1, n_audio=audio, n_query=1, vis_off=0, aud_off=0, qry_off=0)
+    args = (xv, xa, xa[:1].contiguous(), [clip], {"alignment": "av_cosine", "gamma": 0.0, "r_pre": 1.0})
+    with pytest.raises(A.ApackError) as e:
+        A.apack_score_dynamics(*args, workspace=torch.empty(256, dtype=torch.uint8, device="cuda"))
+    least = int(re.search(r"< (\d+) needed", str(e.value)).group(1))
+    assert least < A.apack_score_dynamics_query([clip], dim, args[4])[1]
+    buf = torch.full((least + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    got, want = A.apack_score_dynamics(*args, workspace=buf[:least]), A.apack_score_dynamics(*args)
+    torch.cuda.synchronize()
+    assert bool((buf[least:] == 0xA5).all())
+    for k in ("cka", "score", "budget", "segment", "gate", "kept"):
+        assert torch.equal(got[k].cpu(), want[k].cpu()), k
+
+
 def test_gate_gemm_past_2_to_the_31_elements():
     """A clip whose last gate GEMM tiles start past 2^31 elements of the
     visual rows (131072 rows of 16384): frame scores 1 - d_hat (gamma 0)
