@@ -132,7 +132,12 @@ void lay_out_prune(PrunePlan& pl, ScoreForm form, int n_rep, int hkv) {
   // 9454 rows (16 over 2) 121.8 and 110.7; 9390 rows (28 over 4) 190.5 and
   // 148.7.  bf16 at 9454 rows: 57.0 and 59.4.
   const int64_t unit = form == ScoreForm::kFineChunks ? kKeyBlock : kKeyTile;
-  const int64_t target = pl.few_rows && form != ScoreForm::kGeneral ? kFewTarget : APACK_TILE_TARGET;
+  // Two workgroups per CU only for the few-row kernels, which hold that many;
+  // the fp32 kernels with few query rows run a second round: 9390 keys, one
+  // query token, 51.4 us at 256 and 71.4 at 512 (16 heads over 2), 67.3 and
+  // 84.2 (28 over 4), 344 and 356 (32 over 32); 1312 keys of 28 over 4 29.9
+  // and 30.0.
+  const int64_t target = form == ScoreForm::kFewRows ? kFewTarget : APACK_TILE_TARGET;
   const int64_t want = (pl.weighted + target - 1) / target;
   const int64_t ch = std::max<int64_t>(unit, std::min<int64_t>((want + unit - 1) / unit * unit, kMaxChunk));
   for (int s = 0; s < (int)pl.seqs.size(); ++s) {

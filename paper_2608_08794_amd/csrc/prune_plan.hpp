@@ -32,7 +32,7 @@ constexpr int kMaxChunk = APACK_MAX_CHUNK;    // keys per score workgroup, at mo
 // stores its logits in pass 1 rather than reading K again in pass 2.
 constexpr int kFewRows = 16;
 constexpr int kFewTotal = 1024;
-constexpr int kFewTarget = 512;   // pass-1 workgroups aimed at: two per CU
+constexpr int kFewTarget = 512;   // workgroups that the few-row pass 1 aims at: two per CU
 constexpr int kRowTile = 1024;   // rows per workgroup of the select and compaction kernels
 
 // Per-sequence descriptor on the device (uploaded once per call).  The
