@@ -133,15 +133,23 @@ struct PrunePlan {
 // (7 us of a 9390-row layer's 25).  Where one workgroup selects anyway it
 // counts the digit itself: calls at 1312 fp32 rows 41.2 us against 46.1, at
 // 9390 bf16 rows 66.0 against 66.9, with few query rows 42.9 against 45.1, at
-// 15564 rows 86.4 against 85.8 -- up to kDigitRows, or with few query rows.  It
-// sums too while the partials are few: at 9390 rows of four heads 67 us with
-// the sums there, so the line lies at kSumPartials of them.
+// 15564 rows 86.4 against 85.8 -- up to kDigitRows, or with few query rows.
+// It sums too where there are one or two partials per key and few of them: it
+// takes them one after another, a round trip to memory each, where the score
+// kernels read eight together in many workgroups.  64 query rows, bf16, head
+// dim 128, us with the sums in the score kernels and in the selection: one
+// partial, 1312 keys 32.4 and 31.1, 9000 44.5 and 43.9, 15000 52.8 and 53.1;
+// two, 1312 keys 33.0 and 32.1, 5400 39.2 and 39.2 (fp32 74.7 and 75.7);
+// three, 1312 and 5400 keys 26.7 and 26.7, 33.0 and 33.8; four, 1312 keys 32.0
+// and 32.1; eight, 2048 keys 28.4 and 30.3; 32, 512 keys 27.4 and 36.9; 64,
+// 256 keys 30.7 and 50.8.
 enum ScoreTail { kTailInScores = 0, kDigitInSelect = 1, kSumInSelect = 2 };
-constexpr int64_t kSumPartials = 16384, kDigitRows = 12288;
+constexpr int64_t kSumPlanes = 2, kSumPartials = 8192, kDigitRows = 12288;
 inline ScoreTail score_tail(const PrunePlan& pl) {
   const bool few = pl.form == ScoreForm::kFewRows;   // its kernels store whole scores
   if (pl.max_tokens > (few ? kSmallRows : kDigitRows)) return kTailInScores;
-  return !few && pl.max_planes * pl.max_tokens <= kSumPartials ? kSumInSelect : kDigitInSelect;
+  return !few && pl.max_planes <= kSumPlanes && pl.max_planes * pl.max_tokens <= kSumPartials ? kSumInSelect
+                                                                                             : kDigitInSelect;
 }
 
 struct DevPtrs {

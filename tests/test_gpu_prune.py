@@ -667,11 +667,21 @@ def test_fp32_chunks_of_whole_blocks(hq, hkv, d, q_len, n):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_select_of_short_sequences_at_its_edges(dtype, n):
     """One, two and five rows a thread and all sixteen; partials summed by the
-    selection (up to 8192 rows of two heads) or by the score kernels, the
+    selection (up to 4096 rows of two heads) or by the score kernels, the
     first digit counted by either (up to 12288 rows)."""
     a = max(1, n // 5)
     spans = [(0, a, A_)] if n < 8 else [(0, a, A_), (a + 3, n - a - 5, V_)]
     _parity(_synthetic(dtype, 8, 2, 64, [(spans, n, 8, (0.6, 0.3))], seed=80))
+
+
+@pytest.mark.parametrize("hq,hkv,n", [(8, 1, 8192), (8, 1, 8193), (8, 2, 4096), (12, 3, 1312), (32, 32, 512)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_partials_summed_on_either_side_of_the_rule(dtype, hq, hkv, n):
+    """One or two partials per key are summed by the selection up to 8192 of
+    them, more by the score kernels."""
+    q_len = 8 if hkv < 32 else 20
+    _parity(_synthetic(dtype, hq, hkv, 64, [([(0, n // 5, A_), (n // 5 + 3, n - n // 5 - 5, V_)], n, q_len,
+                                             (0.6, 0.3))], seed=84))
 
 
 def test_few_query_rows_ties_and_one_row_more():
