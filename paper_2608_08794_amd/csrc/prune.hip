@@ -977,29 +977,30 @@ __global__ __launch_bounds__(kFewWaves * kWave) void k_few_logits(
   const bool store = (lane & 15) < rows;
   float m_run = -FLT_MAX, s_run = 0.f;
   for (int i0 = first; i0 < n_keys; i0 += kFewKeys) {
+    // The accumulators start at the mask (a masked key's logit then stays -inf
+    // where its products sum past the largest float; added at the end, inf -
+    // inf had made the row's sum NaN).  A whole block lies below the mask's end
+    // or past it.
     f32x16 x;
     f32x4v acc[kFewBlocks];
 #pragma unroll
     for (int u = 0; u < kFewBlocks; ++u) {
-      acc[u] = f32x4v{};
+      const int i = i0 + 16 * u + 4 * (lane >> 4);
+      acc[u] = i < n_mask ? *reinterpret_cast<const f32x4v*>(lmask + i)
+                          : f32x4v{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+    }
+#pragma unroll
+    for (int u = 0; u < kFewBlocks; ++u)
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
         acc[u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nxt[u][ks], qf[ks], acc[u], 0, 0, 0);
-    }
     if (i0 + kFewKeys < n_keys) load(i0 + kFewKeys);
 #pragma unroll
     for (int u = 0; u < kFewBlocks; ++u) {
       const int i = i0 + 16 * u + 4 * (lane >> 4);
-      const bool in_mask = i < n_mask;   // a whole block lies below the mask's end or past it
-      const f32x4v mk = in_mask ? *reinterpret_cast<const f32x4v*>(lmask + i)
-                                : f32x4v{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-      f32x4v v;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] = acc[u][e] + mk[e];
-        x[4 * u + e] = v[e];
-      }
-      if (store && in_mask && key_begin + i < np) *reinterpret_cast<f32x4v*>(out + i) = v;
+      for (int e = 0; e < 4; ++e) x[4 * u + e] = acc[u][e];
+      if (store && i < n_mask && key_begin + i < np) *reinterpret_cast<f32x4v*>(out + i) = acc[u];
     }
     row_update(x, scale_log2, m_run, s_run);
   }

@@ -674,6 +674,56 @@ def test_select_of_short_sequences_at_its_edges(dtype, n):
     _parity(_synthetic(dtype, 8, 2, 64, [(spans, n, 8, (0.6, 0.3))], seed=80))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_few_query_rows_beside_masked_logits_past_the_largest_float(d, sign):
+    """Keys that are no candidates do not count, also where their logits
+    overflow: the scores are those with these keys zeroed, to the bit."""
+    import paper_2608_08794_amd as A
+    rng = np.random.default_rng(d)
+    n, hq, hkv = 600, 8, 2
+    q = torch.ones((hq, 1, d), dtype=torch.bfloat16, device="cuda")
+    k = to_dev(W.to_bf16_bits(rng.standard_normal((hkv, n, d)).astype(np.float32)), "bf16")
+    seq = W.PruneSeq(0, n, [(20, 300, A_), (333, 200, V_)], 0, 1, (0.5, 0.3))
+    got = []
+    for other in (0.0, sign * 640.0 / d * 1e36):   # 32 products of it sum to a float, d of them do not
+        for lo, hi in ((0, 20), (320, 333), (533, n)):
+            k[:, lo:hi] = other
+        s, kept, _ = A.apack_prune_layer(q, k, [seq])
+        got.append((bits(s), bits(kept)))
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("row", [5, 100, 599])   # no candidate, a candidate, the last row (no candidate)
+def test_few_query_rows_with_a_key_that_is_not_finite(value, row):
+    """As in the general passes (which a smaller workspace takes)."""
+    import re
+    import paper_2608_08794_amd as A
+    rng = np.random.default_rng(row)
+    n, hq, hkv, d = 600, 8, 2, 128
+    q, k = (to_dev(W.to_bf16_bits(rng.standard_normal(s).astype(np.float32)), "bf16")
+            for s in ((hq, 1, d), (hkv, n, d)))
+    q = q.abs() / 8                # a row of infinities gives an infinite logit
+    k[1, row] = value
+    seq = W.PruneSeq(0, n, [(20, 300, A_), (333, 200, V_)], 0, 1, (0.5, 0.3))
+    with pytest.raises(A.ApackError) as e:
+        A.apack_prune_layer(q, k, [seq], workspace=torch.empty(256, dtype=torch.uint8, device="cuda"))
+    least = int(re.search(r"< (\d+) needed", str(e.value)).group(1))
+    few = A.apack_prune_layer(q, k, [seq])
+    general = A.apack_prune_layer(q, k, [seq], workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    # Values differ by fp32 rounding; NaN and zeros are in the same places, but
+    # for a candidate whose logits are -inf: it adds nothing to any row, and the
+    # general passes' padding rows (0 times an infinity) make its score NaN.
+    got, want = few[0].clone(), general[0].clone()
+    if value == -float("inf") and 20 <= row < 533:
+        assert bool(got[row].isfinite())
+        got[row] = want[row] = 0.0
+    torch.testing.assert_close(got, want, rtol=1e-5, atol=0, equal_nan=True)
+    assert few[2] == general[2]
+
+
 @pytest.mark.parametrize("hq,hkv,n", [(8, 1, 8192), (8, 1, 8193), (8, 2, 4096), (12, 3, 1312), (32, 32, 512)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_partials_summed_on_either_side_of_the_rule(dtype, hq, hkv, n):
