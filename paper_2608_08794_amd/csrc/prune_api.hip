@@ -3,12 +3,15 @@
 // rejected call has no device-side effect.
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 
 #include "common.hpp"
 #include "prune_plan.hpp"
 
 namespace apack {
+
+constexpr int kScoreCUs = 256, kXcds = 8;
 
 apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, int32_t hkv, int32_t d,
                               PrunePlan& pl) {
@@ -118,6 +121,57 @@ apack_status build_prune_plan(int32_t n_seq, const apack_seq* seqs, int32_t hq, 
   return APACK_OK;
 }
 
+// Workgroups of a score pass in chunks of `chunk` keys, and the keys they take
+// with 64 more each (see rounds_time).
+struct ScoreTiles {
+  int64_t n = 0, keys = 0;
+};
+static ScoreTiles score_tiles(const PrunePlan& pl, int64_t chunk, int hkv) {
+  ScoreTiles t;
+  for (const SeqDev& sd : pl.seqs) {
+    if (sd.n_cand == 0) continue;
+    const int64_t n = (sd.n_tokens + chunk - 1) / chunk, planes = (int64_t)hkv * sd.n_rg;
+    t.n += n * planes;
+    t.keys += (sd.n_tokens + 64 * n) * planes;
+  }
+  return t;
+}
+
+// Time of a score pass of at least one round in such chunks, up to a constant
+// factor, by dealing its workgroups as the hardware does: to the XCDs in turn,
+// and there to the first CU that is free.  A workgroup takes its keys and
+// about 64 more (query fragments, first tile), twice as long where two waves
+// share a SIMD's matrix unit, and a call of several rounds about a tenth more
+// than this gives.
+static int64_t rounds_time(const PrunePlan& pl, int64_t chunk, int n_rep, int hkv) {
+  constexpr int kPerXcd = kScoreCUs / kXcds;
+  int64_t free_at[kXcds][kPerXcd] = {}, last = 0, i = 0;   // each XCD's CUs as a heap, the first free one on top
+  for (const SeqDev& sd : pl.seqs) {
+    if (sd.n_cand == 0) continue;
+    const int64_t n_chunks = (sd.n_tokens + chunk - 1) / chunk;
+    for (int g = 0; g < hkv; ++g)
+      for (int64_t c0 = 0; c0 < n_chunks; c0 += 8)
+        for (int rg = 0; rg < sd.n_rg; ++rg) {
+          const int rows = std::min(n_rep * sd.q_len, (rg + 1) * sd.rows_per_rg) - rg * sd.rows_per_rg;
+          for (int64_t c = c0; c < std::min(c0 + 8, n_chunks); ++c, ++i) {
+            const int64_t keys = std::min(chunk, sd.n_tokens - c * chunk) + 64;
+            int64_t* q = free_at[i % kXcds];
+            const int64_t t = q[0] + (rows > 4 * kRowsPerWave ? 2 * keys : keys);
+            int k = 0;
+            for (int w = 1; w < kPerXcd; w = 2 * k + 1) {
+              if (w + 1 < kPerXcd && q[w + 1] < q[w]) ++w;
+              if (q[w] >= t) break;
+              q[k] = q[w];
+              k = w;
+            }
+            q[k] = t;
+            last = std::max(last, t);
+          }
+        }
+  }
+  return i <= kScoreCUs ? last : last * 11 / 10;
+}
+
 void lay_out_prune(PrunePlan& pl, ScoreForm form, int n_rep, int hkv) {
   pl.form = form;
   pl.tiles.clear();
@@ -139,7 +193,42 @@ void lay_out_prune(PrunePlan& pl, ScoreForm form, int n_rep, int hkv) {
   // and 30.0.
   const int64_t target = form == ScoreForm::kFewRows ? kFewTarget : APACK_TILE_TARGET;
   const int64_t want = (pl.weighted + target - 1) / target;
-  const int64_t ch = std::max<int64_t>(unit, std::min<int64_t>((want + unit - 1) / unit * unit, kMaxChunk));
+  auto whole = [&](int64_t keys) {
+    return std::max<int64_t>(unit, std::min<int64_t>((want + keys - 1) / keys * keys, kMaxChunk));
+  };
+  int64_t ch = whole(unit);
+  // Every sequence and key head has a short last chunk, so that these chunks
+  // may need a second round of workgroups, in fp32, where they are short, often
+  // where whole tiles take one: then the best of ten sizes or so from half of
+  // that to a quarter above whole tiles.  Calls of more than three rounds keep
+  // the shortest (their last round weighs little, and the search, some 20 us of
+  // host time here, would take longer).  With the shortest always and with the
+  // search, us: 1785 and 4359 rows of 12 heads over 12, D = 128, 184 and 113;
+  // 5484 and 865 of 32 over 32 428 and 267; 49890 of 12 over 12, D = 64, 722
+  // and 412; 16 sequences of 11806 rows, 12 over 12, D = 128, 329 and 234; 64
+  // of 38807, 16 over 2, D = 64, 179 and 197, the worst of 180 drawn.  In 217
+  // drawn batches the sizes chosen were 0.2% slower than the best of those
+  // tried on average; the shortest 9%, whole tiles 23%.
+  const int64_t n_tiles = form == ScoreForm::kFineChunks ? score_tiles(pl, ch, hkv).n : 0;
+  if (n_tiles > kScoreCUs && n_tiles <= 3 * kScoreCUs) {
+    const int64_t first = ch, least = std::max<int64_t>(unit, want / 2 / unit * unit);
+    const int64_t most = std::min<int64_t>(whole(kKeyTile) * 5 / 4, kMaxChunk);
+    const int64_t step = std::max<int64_t>(unit, (most - least) / 9 / unit * unit);
+    int64_t best = rounds_time(pl, ch, n_rep, hkv);
+    // False once longer chunks gain nothing: these take one round.
+    auto consider = [&](int64_t c) {
+      const ScoreTiles t = score_tiles(pl, c, hkv);
+      if (t.n > kScoreCUs && t.keys / kScoreCUs * 11 / 10 >= best) return true;   // nor if dealt evenly
+      const int64_t time = rounds_time(pl, c, n_rep, hkv);
+      if (time < best) {
+        best = time;
+        ch = c;
+      }
+      return t.n > kScoreCUs;
+    };
+    for (int64_t c = first + step; c <= most && consider(c);) c += step;
+    for (int64_t c = first - step; c >= least; c -= step) consider(c);
+  }
   for (int s = 0; s < (int)pl.seqs.size(); ++s) {
     SeqDev& sd = pl.seqs[s];
     if (sd.n_cand == 0) continue;

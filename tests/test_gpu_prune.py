@@ -663,6 +663,17 @@ def test_fp32_chunks_of_whole_blocks(hq, hkv, d, q_len, n):
     _parity(_synthetic("f32", hq, hkv, d, [([(0, a, A_), (a, n - a - 1, V_)], n, q_len, (0.6, 0.3))], seed=81))
 
 
+@pytest.mark.parametrize("hq,hkv,d,lens,q_lens", [
+    (12, 12, 128, (1020, 2256), (16, 3)),              # longer chunks than the shortest, one round
+    (12, 12, 64, (60, 16211), (16, 7)),                # longer than whole tiles
+    (32, 8, 128, (1850, 4000, 2362, 397), (64, 1, 128, 3)),   # two row groups' worth of rows beside few
+    (8, 8, 64, (300,) * 16, (33,) * 16),               # several rounds whatever the chunk
+])
+def test_fp32_chunks_chosen_by_their_rounds(hq, hkv, d, lens, q_lens):
+    specs = [([(0, n // 4, A_), (n // 4, n - n // 4 - 1, V_)], n, ql, (0.6, 0.3)) for n, ql in zip(lens, q_lens)]
+    _parity(_synthetic("f32", hq, hkv, d, specs, seed=85))
+
+
 @pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 4097, 8192, 8193, 12288, 12289, 16384])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_select_of_short_sequences_at_its_edges(dtype, n):
