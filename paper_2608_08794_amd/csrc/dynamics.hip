@@ -889,7 +889,6 @@ constexpr int kSpatialSplit = 4;  // and of the spatial Gram
 constexpr int64_t kSpatialBlocks = 1 << 20;  // workgroups of the spatial Gram at most (a multiple of 8)
 constexpr int kGramBlocks = 512;  // workgroups of the anchor Gram at most: two per CU
 constexpr int kFuseFrames = 192;  // frames up to which the cosines share the Grams' launch
-constexpr int64_t kDedupBlocks = 1 << 20;  // workgroups of the cosines beside it at most
 
 // Tile block (bi, bj), bj >= bi, number t of the row-major upper triangle of
 // an nb x nb grid of blocks.
@@ -1094,21 +1093,20 @@ __device__ __forceinline__ void anchor_grams(const ClipDev* __restrict__ clips, 
 // Non-anchor frames: cosine of token p of frame f with token p of its
 // anchor, one wave per position, written to sim at the token's row.  The dot
 // product and both squared norms are summed the same way, so a position that
-// repeats the anchor's token has cosine exactly 1.  Block b covers WAVES
-// positions of one frame.
+// repeats the anchor's token has cosine exactly 1.  One block covers positions
+// [WAVES group, WAVES (group + 1)) of frame `item`.
 template <class T, int WAVES>
 __device__ __forceinline__ void dedup_cosines(const ClipDev* __restrict__ clips, const FrameDev* __restrict__ frames,
                                               const FramePlanDev* __restrict__ plan, int dim,
-                                              const T* __restrict__ xv, double* __restrict__ sim, int64_t b,
-                                              int per_frame_blocks) {
-  const int64_t item = b / per_frame_blocks;
+                                              const T* __restrict__ xv, double* __restrict__ sim, unsigned item,
+                                              unsigned group) {
   const FrameDev fr = frames[item];
   const ClipDev c = clips[fr.clip];
   const FramePlanDev fp = plan[c.frame_off + fr.f];
   if (fp.is_anchor || fp.budget == 0) return;
   const int P = c.per_frame;
   const int lane = threadIdx.x & 63;
-  const int p = (int)(b - item * per_frame_blocks) * WAVES + (threadIdx.x >> 6);
+  const int p = (int)group * WAVES + (threadIdx.x >> 6);
   if (p >= P) return;
   const int64_t rowf = c.vis_off + (int64_t)fr.f * P + p, rowa = c.vis_off + (int64_t)fp.anchor * P + p;
   const T* x = xv + rowf * dim;
@@ -1144,13 +1142,13 @@ __device__ __forceinline__ void dedup_cosines(const ClipDev* __restrict__ clips,
 // a few anchors go tile by tile (60 s clip 34 us against 38 in blocks).
 template <class T>
 __global__ __launch_bounds__(kGramSplit * 64, 4) void k_gram_dedup(
-    const ClipDev* __restrict__ clips, int n_clips, const FrameDev* __restrict__ frames, int64_t n_frames,
+    const ClipDev* __restrict__ clips, int n_clips, const FrameDev* __restrict__ frames,
     const int32_t* __restrict__ anchors, const FramePlanDev* __restrict__ plan, int dim, const T* __restrict__ xv,
-    double* __restrict__ gram, double* __restrict__ sim, int gram_blocks, int per_frame_blocks) {
+    double* __restrict__ gram, double* __restrict__ sim, unsigned gram_blocks, unsigned per_frame_blocks) {
   __shared__ double red[kGramSplit - 1][16 * 64];
-  if (blockIdx.x >= (unsigned)gram_blocks) {
-    for (int64_t b = (int64_t)blockIdx.x - gram_blocks; b < n_frames * per_frame_blocks; b += gridDim.x - gram_blocks)
-      dedup_cosines<T, kGramSplit>(clips, frames, plan, dim, xv, sim, b, per_frame_blocks);
+  if (blockIdx.x >= gram_blocks) {
+    const unsigned b = blockIdx.x - gram_blocks;
+    dedup_cosines<T, kGramSplit>(clips, frames, plan, dim, xv, sim, b / per_frame_blocks, b % per_frame_blocks);
     return;
   }
   int64_t tiles = 0;
@@ -1164,13 +1162,14 @@ __global__ __launch_bounds__(kGramSplit * 64, 4) void k_gram_dedup(
     anchor_grams<T, 2>(clips, n_clips, anchors, plan, dim, xv, gram, red, blockIdx.x, gram_blocks);
 }
 
+// Frame blockIdx.x, positions of blockIdx.y.  (A loop over one index, with a
+// 64-bit division a block, took 33 us against 27 for 960 frames of 64 tokens at
+// D = 512.)
 template <class T>
 __global__ __launch_bounds__(kBlk) void k_dedup(const ClipDev* __restrict__ clips, const FrameDev* __restrict__ frames,
-                                                int64_t n_frames, const FramePlanDev* __restrict__ plan, int dim,
-                                                const T* __restrict__ xv, double* __restrict__ sim,
-                                                int per_frame_blocks) {
-  for (int64_t b = blockIdx.x; b < n_frames * per_frame_blocks; b += gridDim.x)
-    dedup_cosines<T, kBlk / 64>(clips, frames, plan, dim, xv, sim, b, per_frame_blocks);
+                                                const FramePlanDev* __restrict__ plan, int dim,
+                                                const T* __restrict__ xv, double* __restrict__ sim) {
+  dedup_cosines<T, kBlk / 64>(clips, frames, plan, dim, xv, sim, blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------------------
@@ -1842,13 +1841,11 @@ apack_status launch_t(const DynPlan& pl, const DynPtrs& dp, const DynParamsDev& 
     const int gb = (int)std::min<int64_t>((pl.gram_items + 7) / 8 * 8, kGramBlocks);
     const bool fuse = nf <= kFuseFrames;
     const int waves = fuse ? kGramSplit : kBlk / 64, pb = (pl.max_per_frame + waves - 1) / waves;
-    const unsigned db = (unsigned)std::min<int64_t>((int64_t)nf * pb, kDedupBlocks);
-    hipLaunchKernelGGL(k_gram_dedup<T>, dim3(fuse ? gb + db : gb), dim3(kGramSplit * 64), 0, s, dp.clips, nc, dp.frames,
-                       (int64_t)nf, dp.anchors, dp.plan, dim, xv, dp.gram, dp.sim, gb, pb);
+    hipLaunchKernelGGL(k_gram_dedup<T>, dim3(fuse ? gb + nf * pb : gb), dim3(kGramSplit * 64), 0, s, dp.clips, nc,
+                       dp.frames, dp.anchors, dp.plan, dim, xv, dp.gram, dp.sim, (unsigned)gb, (unsigned)pb);
     if ((st = launch_status("k_gram_dedup")) != APACK_OK) return st;
     if (!fuse) {
-      hipLaunchKernelGGL(k_dedup<T>, dim3(db), dim3(kBlk), 0, s, dp.clips, dp.frames, (int64_t)nf, dp.plan, dim, xv,
-                         dp.sim, pb);
+      hipLaunchKernelGGL(k_dedup<T>, dim3(nf, pb), dim3(kBlk), 0, s, dp.clips, dp.frames, dp.plan, dim, xv, dp.sim);
       if ((st = launch_status("k_dedup")) != APACK_OK) return st;
     }
     const bool short_lists = prm.dafps_k <= 8;
