@@ -1011,8 +1011,8 @@ template <class T, int N>
 __device__ __forceinline__ void anchor_grams(const ClipDev* __restrict__ clips, int n_clips,
                                              const int32_t* __restrict__ anchors,
                                              const FramePlanDev* __restrict__ plan, int dim, const T* __restrict__ xv,
-                                             double* __restrict__ gram, double (&red)[kGramSplit - 1][16 * 64],
-                                             int blk, int n_blk) {
+                                             double* __restrict__ gram, double (&red)[kGramSplit][16 * 64],
+                                             unsigned blk, unsigned n_blk) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, g = lane >> 4,
             r16 = lane & 15;
   // This wave's K slice, in 32-element steps.
@@ -1026,29 +1026,30 @@ __device__ __forceinline__ void anchor_grams(const ClipDev* __restrict__ clips, 
   // all of them (with whole anchors dealt to XCDs a clip of two had used two
   // of the eight, and one of nine had given the first XCD two: 10 s clip
   // 36 -> 14 us, 20 s 23 -> 14, 60 s 33 -> 22.5, 290 s 124 -> 114).
-  int64_t base = 0;
+  // A clip has fewer than 2^31 items (its Grams fit in memory).
+  unsigned base = 0;   // items of the clips before, modulo n_blk
   for (int c = 0; c < n_clips; ++c) {
     const ClipDev cc = clips[c];
     if (cc.n_frames == 0) continue;
-    const int P = cc.per_frame, nb = (P + N * kGramTile - 1) / (N * kGramTile), blocks = nb * (nb + 1) / 2;
-    const int64_t items = (int64_t)cc.n_seg * blocks, whole = (int64_t)(cc.n_seg / 8) * 8 * blocks;
-    const int64_t q0 = ((blk - base % n_blk) % n_blk + n_blk) % n_blk;
-    base += items;
-    for (int64_t q = q0; q < items; q += n_blk) {
-      int64_t an;
-      int t;
+    const int P = cc.per_frame, nb = (P + N * kGramTile - 1) / (N * kGramTile);
+    const unsigned blocks = nb * (nb + 1) / 2, n_seg = cc.n_seg;
+    const unsigned items = n_seg * blocks, whole = n_seg / 8 * 8 * blocks;
+    const unsigned q0 = (blk + n_blk - base) % n_blk;
+    base = (base + items) % n_blk;
+    for (unsigned q = q0; q < items; q += n_blk) {
+      unsigned an, t;
       if (q < whole) {
-        const int64_t r = q % (8 * blocks);
+        const unsigned r = q % (8 * blocks);
         an = q / (8 * blocks) * 8 + (r & 7);
-        t = (int)(r >> 3);
+        t = r >> 3;
       } else {
         an = whole / blocks + (q - whole) / blocks;
-        t = (int)((q - whole) % blocks);
+        t = (q - whole) % blocks;
       }
       const int f = anchors[cc.frame_off + an];
       if (plan[cc.frame_off + f].budget == 0) continue;  // the same for the whole workgroup
       int bi, bj;
-      upper_block(t, nb, bi, bj);
+      upper_block((int)t, nb, bi, bj);
       const T* x = xv + (cc.vis_off + (int64_t)f * P) * dim;
       const T* row[2 * N];
 #pragma unroll
@@ -1065,25 +1066,22 @@ __device__ __forceinline__ void anchor_grams(const ClipDev* __restrict__ clips, 
         gram_block<T, N, true, 0>(row, none, first, dim, s_begin, s_end, g, acc);
       else
         gram_block<T, N, false, 0>(row, none, first, dim, s_begin, s_end, g, acc);
-      gram_reduce<kGramSplit, N>(acc, red, wave, lane);
-      if (wave == 0) {
-        // Raw dot products: k_dafps forms the cosines from them and the
-        // diagonal, which went through the same MFMA sequence.
-        double* G = gram + cc.gram_off + (int64_t)f * P * P;
+      // The waves' partial tiles are added in wave order, by all of them.
 #pragma unroll
-        for (int u = 0; u < N; ++u)
+      for (int i = 0; i < 4 * N * N; ++i) red[wave][64 * i + lane] = acc[i / 4 / N][i / 4 % N][i % 4];
+      __syncthreads();
+      // Raw dot products: k_dafps forms the cosines from them and the
+      // diagonal, which went through the same MFMA sequence.
+      double* G = gram + cc.gram_off + (int64_t)f * P * P;
+      for (int i = threadIdx.x; i < 256 * N * N; i += kGramSplit * 64) {
+        double x = red[0][i];
 #pragma unroll
-          for (int v = 0; v < N; ++v) {
-            if (bi == bj && u > v) continue;
-            const int col = (N * bj + v) * kGramTile + r16;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int r = (N * bi + u) * kGramTile + 4 * e + g;
-              if (r >= P || col >= P) continue;
-              G[(int64_t)r * P + col] = acc[u][v][e];
-              G[(int64_t)col * P + r] = acc[u][v][e];
-            }
-          }
+        for (int w = 1; w < kGramSplit; ++w) x += red[w][i];
+        const int u = i / (256 * N), v = i / 256 % N, l = i % 64;
+        const int r = (N * bi + u) * kGramTile + 4 * (i / 64 % 4) + (l >> 4), col = (N * bj + v) * kGramTile + (l & 15);
+        if ((bi == bj && u > v) || r >= P || col >= P) continue;
+        G[(int64_t)r * P + col] = x;
+        G[(int64_t)col * P + r] = x;
       }
       __syncthreads();
     }
@@ -1145,18 +1143,21 @@ __global__ __launch_bounds__(kGramSplit * 64, 4) void k_gram_dedup(
     const ClipDev* __restrict__ clips, int n_clips, const FrameDev* __restrict__ frames,
     const int32_t* __restrict__ anchors, const FramePlanDev* __restrict__ plan, int dim, const T* __restrict__ xv,
     double* __restrict__ gram, double* __restrict__ sim, unsigned gram_blocks, unsigned per_frame_blocks) {
-  __shared__ double red[kGramSplit - 1][16 * 64];
+  __shared__ double red[kGramSplit][16 * 64];
   if (blockIdx.x >= gram_blocks) {
     const unsigned b = blockIdx.x - gram_blocks;
     dedup_cosines<T, kGramSplit>(clips, frames, plan, dim, xv, sim, b / per_frame_blocks, b % per_frame_blocks);
     return;
   }
-  int64_t tiles = 0;
-  for (int c = 0; c < n_clips; ++c) {
+  // The clips' single tiles, a clip per lane (one after another, each a round
+  // trip, they took 8 us of a batch of 16 clips).
+  double tiles = 0.0;
+  for (int c = threadIdx.x & 63; c < n_clips; c += 64) {
     const int nt = (clips[c].per_frame + kGramTile - 1) / kGramTile;
-    tiles += clips[c].n_frames > 0 ? (int64_t)clips[c].n_seg * (nt * (nt + 1) / 2) : 0;
+    tiles += clips[c].n_frames > 0 ? (double)clips[c].n_seg * (nt * (nt + 1) / 2) : 0.0;
   }
-  if (tiles <= 2 * (int64_t)gram_blocks)
+  tiles = wave_sum(tiles);
+  if (tiles <= 2.0 * gram_blocks)   // the same in every wave
     anchor_grams<T, 1>(clips, n_clips, anchors, plan, dim, xv, gram, red, blockIdx.x, gram_blocks);
   else
     anchor_grams<T, 2>(clips, n_clips, anchors, plan, dim, xv, gram, red, blockIdx.x, gram_blocks);
