@@ -151,6 +151,33 @@ def test_ragged_batch_of_clips_with_edge_shapes():
     _compare(case, _run(case), want)
 
 
+def test_batch_of_more_clips_than_lanes():
+    """70 short clips (one without frames): each one's outputs are those of the
+    clip alone, to the bit (the Grams of a batch share one list of items)."""
+    import paper_2608_08794_amd as A
+    rng = np.random.default_rng(70)
+    frames = [int(f) for f in rng.integers(1, 14, 70)]
+    frames[33] = 0
+    P, dim = 20, 72
+    xv, xa, xq = (to_dev(W.to_bf16_bits(rng.standard_normal((n, dim)).astype(np.float32)), "bf16")
+                  for n in (sum(frames) * P, 70 * 9, 70 * 2))
+    params = {"window": 3, "r_pre": 0.5}
+    clips, vo = [], 0
+    for i, f in enumerate(frames):
+        clips.append(dict(n_frames=f, per_frame=P, n_audio=9, n_query=2, vis_off=vo, aud_off=9 * i, qry_off=2 * i))
+        vo += f * P
+    batch = A.apack_score_dynamics(xv, xa, xq, clips, params)
+    f0 = k0 = 0
+    for i, clip in enumerate(clips):
+        one = A.apack_score_dynamics(xv, xa, xq, [clip], params)
+        f1, k1 = f0 + frames[i], k0 + one["n_kept"][0]
+        assert batch["n_kept"][i] == one["n_kept"][0]
+        for key in ("cka", "score", "budget", "segment"):
+            assert torch.equal(batch[key][f0:f1], one[key]), (i, key)
+        assert torch.equal(batch["kept"][k0:k1], one["kept"]), i
+        f0, k0 = f1, k1
+
+
 def test_rows_outside_every_clip_are_ignored():
     """Buffers longer than the clips need: rows before, between and after
     the clips (in X_V, X_A and X_Q alike) change nothing, and the norms and
