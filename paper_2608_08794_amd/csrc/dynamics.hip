@@ -1621,7 +1621,10 @@ __device__ __forceinline__ void dedup_pick(const double* __restrict__ simg, doub
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int p = tid / LANES, h = tid % LANES;
   const int part = (P + LANES - 1) / LANES;
-  if (tid < LANES * part) sim[tid] = tid < P ? simg[tid] : INFINITY;
+  // A NaN (a token that is not finite) ranks as most similar: left unordered it
+  // had rank 0 beside the others' ranks, and a frame with some kept more
+  // positions than its k slots.
+  if (tid < LANES * part) sim[tid] = tid < P ? fmin(simg[tid], INFINITY) : INFINITY;
   __syncthreads();
   const double mine = p < P ? sim[p] : 0.0;
   const int q0 = h * part;

@@ -178,6 +178,37 @@ def test_batch_of_more_clips_than_lanes():
         f0, k0 = f1, k1
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("row", ["anchor", "other", "many"])
+def test_tokens_that_are_not_finite_keep_within_their_budgets(row, value, dtype):
+    """Cosines with them are NaN: every frame still keeps as many different
+    tokens of its own as its budget says, finite ones first where the frame is
+    not an anchor."""
+    import paper_2608_08794_amd as A
+    case = W.dynamics_small("shared", frames=20, per_frame=24, audio=100)
+    s = case.seqs[0]
+    clean = W.bf16_bits_to_f32(case.xv).reshape(20, 24, case.dim)
+    frame = 0 if row == "anchor" else 7
+    tokens = [5] if row != "many" else list(range(0, 24, 2))
+    x = clean.copy()
+    x[frame, tokens, 3] = value
+    conv = (lambda a: W.to_bf16_bits(a)) if dtype == "bf16" else (lambda a: a)
+    xv, xa, xq = (to_dev(conv(np.ascontiguousarray(a, np.float32)), dtype) for a in
+                  (x.reshape(-1, case.dim), W.bf16_bits_to_f32(case.xa), W.bf16_bits_to_f32(case.xq)))
+    out = A.apack_score_dynamics(xv, xa, xq, case.seqs, case.params)
+    kept, budget = out["kept"].cpu().numpy(), out["budget"].cpu().numpy()
+    seg = out["segment"].cpu().numpy()
+    assert budget.min() >= 0 and budget.max() <= 24 and budget.sum() == kept.size == out["n_kept"][0]
+    at = 0
+    for f in range(20):
+        mine = kept[at:at + budget[f]] - f * 24 - s.vis_off
+        at += budget[f]
+        assert (np.diff(mine) > 0).all() and (mine >= 0).all() and (mine < 24).all(), f
+        if f == frame and f and seg[f] == seg[f - 1] and budget[f] <= 24 - len(tokens):
+            assert not set(mine) & set(tokens)
+
+
 def test_rows_outside_every_clip_are_ignored():
     """Buffers longer than the clips need: rows before, between and after
     the clips (in X_V, X_A and X_Q alike) change nothing, and the norms and
