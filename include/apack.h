@@ -352,7 +352,10 @@ typedef struct apack_av_seq {
 } apack_av_seq;
 
 /* Validates and reports each clip's visual budget B_v (n_kept_visual, HOST
- * [n_seq], may be NULL) and the workspace size apack_score_dynamics needs. */
+ * [n_seq], may be NULL) and the workspace size that serves
+ * apack_score_dynamics best in either dtype.  A workspace with room for a list
+ * of 128 x 128 audio by visual tiles (16 bytes each) in the place of the list
+ * counted here is accepted too, for the same results. */
 apack_status apack_score_dynamics_query(int32_t n_seq, const apack_av_seq* seqs, int32_t dim,
                                         const apack_dyn_params* p,
                                         int64_t* n_kept_visual, size_t* workspace_bytes);
